@@ -3,21 +3,12 @@
 // index maps and the LDS re-layout of one row across a window boundary.
 #pragma once
 
-#include <type_traits>
-
 #include "bp_geom.hpp"
 #include "internal.hpp"
+#include "lane_ops.hpp"
 
 namespace polarhip {
 namespace bp {
-
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
 
 template <int B, int E, typename F>
 __device__ __forceinline__ void static_for_rev(F&& f) {  // E-1 down to B
