@@ -20,6 +20,7 @@ namespace polarhip {
 // would be a call and the workgroup id a per-lane value.
 __device__ __forceinline__ int lid_x() { return (int)__builtin_amdgcn_workitem_id_x(); }
 __device__ __forceinline__ int64_t gid_x() { return (int64_t)__builtin_amdgcn_workgroup_id_x(); }
+__device__ __forceinline__ int64_t gid_y() { return (int64_t)__builtin_amdgcn_workgroup_id_y(); }
 __device__ __forceinline__ const hsa_kernel_dispatch_packet_t* dispatch_packet() {
     return (const hsa_kernel_dispatch_packet_t*)__builtin_amdgcn_dispatch_ptr();
 }

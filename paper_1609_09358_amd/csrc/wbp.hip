@@ -15,8 +15,8 @@
 // a), else b sgn(a); the sign factor has zero derivative.  Every operation
 // follows the CPU oracle's order, so a frame's gradient is bit-exact with the
 // oracle's float build.  The per-frame weight gradient is written over the
-// saved messages it no longer needs, and reduced over frames in frame order in
-// double precision (deterministic).
+// saved messages it no longer needs, and reduced over frames in double
+// precision, in an order fixed by the sizes (deterministic).
 #include "bp_common.hpp"
 
 namespace polarhip {
@@ -242,83 +242,184 @@ const BwdEntry* lookup_bwd(int n, int r) {
 
 namespace {
 
-// dW[q] = sum over frames, in frame order, of the per-frame gradients
-__global__ __launch_bounds__(256) void wbp_reduce_kernel(const float* __restrict__ part, int64_t B, int64_t P,
+// Sum of the per-frame gradients part[f][q] over the frames, in double.  One
+// thread per VEC columns q would leave the chip idle (P / 256 workgroups, a
+// serial chain of B loads each), so the frames are split into segments of
+// equal length: workgroup (x, s) sums the rows of segment s in frame order and
+// leaves the double in that segment's first two rows of its own columns (low
+// word, high word -- entries that no other thread reads), and a second kernel
+// adds the segments in order.  The order of additions depends on B and P
+// alone.  Bound by HBM: the B P floats are read once; with at least 32 rows a
+// segment the partial sums add at most an eighth.  Measured: T = 10, N = 256,
+// B = 4096 (671 MB) 1647 us with one thread per column, 165 us; T = 20,
+// N = 1024, B = 1024 (1.7 GB) 528 us, 326 us.
+constexpr int kReduceUnroll = 8;
+constexpr int64_t kReduceMinRows = 32;
+
+template <int VEC>
+struct alignas(4 * VEC) FloatVec {
+    float v[VEC];
+};
+
+template <int VEC, bool PARTIAL>
+__global__ __launch_bounds__(256) void wbp_reduce_kernel(float* part, int64_t B, int64_t P, int segments,
                                                          float* __restrict__ dW) {
-    const int64_t q = gid_x() * wg_size_x() + lid_x();
+    const int64_t q = (gid_x() * 256 + lid_x()) * VEC;
     if (q >= P) return;
-    double acc = 0.0;
-    for (int64_t f = 0; f < B; ++f) acc += (double)part[f * P + q];
-    dW[q] = (float)acc;
-}
-
-// per-frame loss sum_i softplus((2u_i - 1) lambda_i) * scale over non-frozen i, and
-// d loss / d lambda_i = scale (2u_i - 1) sigmoid((2u_i - 1) lambda_i); in double
-__global__ __launch_bounds__(256) void wbp_bce_kernel(CodeDev code, const float* __restrict__ lam,
-                                                      const uint8_t* __restrict__ u, int64_t B, double scale,
-                                                      float* __restrict__ loss, float* __restrict__ dlam) {
-    __shared__ double red[256 / 64];
-    const int64_t f = gid_x();
-    const int N = code.N;
-    double acc = 0.0;
-    for (int i = lid_x(); i < N; i += wg_size_x()) {
-        const bool fr = (code.frozen_bits[i >> 5] >> (i & 31)) & 1u;
-        float d = 0.0f;
-        if (!fr) {
-            const double s = u[f * N + i] ? 1.0 : -1.0;
-            const double z = s * (double)lam[f * N + i];
-            acc += z > 0 ? z + log1p(exp(-z)) : log1p(exp(z));
-            const double sig = 1.0 / (1.0 + exp(-z));
-            d = (float)(scale * s * sig);
-        }
-        dlam[f * N + i] = d;
+    const int64_t s = PARTIAL ? gid_y() : 0;
+    const int64_t r0 = PARTIAL ? B * s / segments : 0, r1 = PARTIAL ? B * (s + 1) / segments : B;
+    double acc[VEC];
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) acc[j] = 0.0;
+    using Vec = FloatVec<VEC>;
+    int64_t f = r0;
+    for (; f + kReduceUnroll <= r1; f += kReduceUnroll) {
+        Vec x[kReduceUnroll];
+#pragma unroll
+        for (int k = 0; k < kReduceUnroll; ++k) x[k] = *reinterpret_cast<const Vec*>(part + (f + k) * P + q);
+#pragma unroll
+        for (int k = 0; k < kReduceUnroll; ++k)
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) acc[j] += (double)x[k].v[j];
     }
-    if (loss) {
-        for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-        if ((lid_x() & 63) == 0) red[lid_x() >> 6] = acc;
-        __syncthreads();
-        if (lid_x() == 0) {
-            double tot = 0.0;
-            for (int w = 0; w < (int)(wg_size_x() / 64); ++w) tot += red[w];
-            loss[f] = (float)(tot * scale);
-        }
+    for (; f < r1; ++f) {
+        const Vec x = *reinterpret_cast<const Vec*>(part + f * P + q);
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) acc[j] += (double)x.v[j];
+    }
+    Vec lo, hi;
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) {
+        const uint64_t w = (uint64_t)__double_as_longlong(acc[j]);
+        lo.v[j] = PARTIAL ? __uint_as_float((uint32_t)w) : (float)acc[j];
+        hi.v[j] = __uint_as_float((uint32_t)(w >> 32));
+    }
+    if constexpr (PARTIAL) {
+        *reinterpret_cast<Vec*>(part + r0 * P + q) = lo;
+        *reinterpret_cast<Vec*>(part + (r0 + 1) * P + q) = hi;
+    } else {
+        *reinterpret_cast<Vec*>(dW + q) = lo;
     }
 }
 
-// per-iteration loss of frame f (one block): LLR(u) after iteration t = saved
-// L row 0 of iteration t + the frozen prior (0 on the non-frozen positions the
-// loss reads); the loss sums over iterations and positions in double
-__global__ __launch_bounds__(256) void wbp_bce_multi_kernel(CodeDev code, const float* __restrict__ saved,
-                                                            const uint8_t* __restrict__ u, int T, double scale,
-                                                            float* __restrict__ loss, float* __restrict__ dlam) {
-    __shared__ double red[256 / 64];
+template <int VEC>
+__global__ __launch_bounds__(256) void wbp_reduce_segments_kernel(const float* __restrict__ part, int64_t B, int64_t P,
+                                                                  int segments, float* __restrict__ dW) {
+    const int64_t q = (gid_x() * 256 + lid_x()) * VEC;
+    if (q >= P) return;
+    using Vec = FloatVec<VEC>;
+    double acc[VEC];
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) acc[j] = 0.0;
+#pragma unroll 4
+    for (int s = 0; s < segments; ++s) {
+        const int64_t r0 = B * s / segments;
+        const Vec lo = *reinterpret_cast<const Vec*>(part + r0 * P + q);
+        const Vec hi = *reinterpret_cast<const Vec*>(part + (r0 + 1) * P + q);
+#pragma unroll
+        for (int j = 0; j < VEC; ++j)
+            acc[j] += __longlong_as_double(
+                (long long)(((uint64_t)__float_as_uint(hi.v[j]) << 32) | __float_as_uint(lo.v[j])));
+    }
+    Vec o;
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) o.v[j] = (float)acc[j];
+    *reinterpret_cast<Vec*>(dW + q) = o;
+}
+
+template <int VEC>
+polar_status launch_reduce(float* part, int64_t B, int64_t P, float* dW, hipStream_t stream) {
+    const int64_t bx = (P / VEC + 255) / 256;
+    // about eight workgroups per CU
+    int64_t segments = (int64_t)device_cu_count() * 8 / bx;
+    if (segments > B / kReduceMinRows) segments = B / kReduceMinRows;
+    if (segments > 1) {
+        hipLaunchKernelGGL((wbp_reduce_kernel<VEC, true>), dim3((unsigned)bx, (unsigned)segments), dim3(256), 0, stream,
+                           part, B, P, (int)segments, dW);
+        hipLaunchKernelGGL(wbp_reduce_segments_kernel<VEC>, dim3((unsigned)bx), dim3(256), 0, stream, part, B, P,
+                           (int)segments, dW);
+    } else {
+        hipLaunchKernelGGL((wbp_reduce_kernel<VEC, false>), dim3((unsigned)bx), dim3(256), 0, stream, part, B, P, 1, dW);
+    }
+    return hip_check(hipGetLastError(), "wbp_reduce launch");
+}
+
+// ------------------------------------------------------------------ losses
+// Bound by double-precision arithmetic (one exponential and one log1p per
+// non-frozen position and iteration; the gradient of the frame-level losses
+// one exponential and one division more).  A workgroup takes one frame, its
+// wavefronts the iterations in turn, so an iteration's sum needs no workgroup
+// barrier, and the lanes walk the non-frozen positions alone, staged in LDS
+// with the frame's bits: walking all positions leaves the frozen lanes idle.
+constexpr int kLossThreads = 256;
+constexpr int kLossWaves = kLossThreads / 64;
+constexpr int kLossMaxN = 4096;
+
+// positions of the non-frozen nodes, the true bit in the top bit
+__device__ __forceinline__ void stage_positions(const CodeDev& code, const uint8_t* u, uint16_t* pos) {
+    for (int q = lid_x(); q < code.k; q += kLossThreads) {
+        const int i = code.info_pos[q];
+        pos[q] = (uint16_t)(i | (u[i] ? 0x8000 : 0));
+    }
+    __syncthreads();
+}
+
+// softplus(z) and sigmoid(z) from one exponential
+__device__ __forceinline__ double softplus_of(double z, double e) { return fmax(z, 0.0) + log1p(e); }
+__device__ __forceinline__ double sigmoid_of(double z, double e) { return (z > 0.0 ? 1.0 : e) / (1.0 + e); }
+
+// sum over the wavefront, in every lane
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+    return v;
+}
+
+// zeros at the frozen nodes of a gradient row
+__device__ __forceinline__ void zero_frozen(const CodeDev& code, float* row, int lane) {
+    for (int i = lane; i < code.N; i += 64)
+        if ((code.frozen_bits[i >> 5] >> (i & 31)) & 1u) row[i] = 0.0f;
+}
+
+// Cross-entropy losses: sum over `rows` LLR rows of the frame (LLR(u) after
+// the last iteration, or L row 0 of every iteration in `saved`: the frozen
+// prior is 0 where the loss reads) and the non-frozen i of softplus((2u_i - 1)
+// lambda_i), times scale; d loss / d lambda_i = scale (2u_i - 1)
+// sigmoid((2u_i - 1) lambda_i); in double.  Row r of frame f starts at lam +
+// f * lam_frame + r * lam_row.
+__global__ __launch_bounds__(kLossThreads) void wbp_bce_kernel(CodeDev code, const float* __restrict__ lam,
+                                                               int64_t lam_frame, int64_t lam_row,
+                                                               const uint8_t* __restrict__ u, int rows, double scale,
+                                                               float* __restrict__ loss, float* __restrict__ dlam) {
+    __shared__ uint16_t pos[kLossMaxN];
+    __shared__ double red[kLossWaves];
     const int64_t f = gid_x();
-    const int N = code.N, n = code.n;
+    const int N = code.N, k = code.k, lane = lid_x() & 63, wave = lid_x() >> 6;
+    stage_positions(code, u + f * N, pos);
+    // several rows: a wavefront takes whole rows; one row: all wavefronts share it
+    const int r_first = rows > 1 ? wave : 0, r_step = rows > 1 ? kLossWaves : 1;
+    const int q_first = rows > 1 ? lane : lid_x(), q_step = rows > 1 ? 64 : kLossThreads;
     double acc = 0.0;
-    for (int t = 0; t < T; ++t) {
-        const float* lrow = saved + (((size_t)f * T + t) * 2 * n + n) * N;
-        float* drow = dlam + ((size_t)f * T + t) * N;
-        for (int i = lid_x(); i < N; i += wg_size_x()) {
-            const bool fr = (code.frozen_bits[i >> 5] >> (i & 31)) & 1u;
-            float d = 0.0f;
-            if (!fr) {
-                const float lam = lrow[i] + 0.0f;
-                const double s = u[f * N + i] ? 1.0 : -1.0;
-                const double z = s * (double)lam;
-                acc += z > 0 ? z + log1p(exp(-z)) : log1p(exp(z));
-                const double sig = 1.0 / (1.0 + exp(-z));
-                d = (float)(scale * s * sig);
-            }
-            drow[i] = d;
+    for (int r = r_first; r < rows; r += r_step) {
+        const float* lrow = lam + f * lam_frame + r * lam_row;
+        float* drow = dlam + (f * rows + r) * N;
+        for (int q = q_first; q < k; q += q_step) {
+            const int i = pos[q] & 0x7FFF;
+            const double s = (pos[q] & 0x8000) ? 1.0 : -1.0;
+            const double z = s * (double)lrow[i];
+            const double e = exp(-fabs(z));
+            acc += softplus_of(z, e);
+            drow[i] = (float)(scale * s * sigmoid_of(z, e));
         }
+        if (rows > 1 || wave == 0) zero_frozen(code, drow, lane);
     }
     if (loss) {
-        for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-        if ((lid_x() & 63) == 0) red[lid_x() >> 6] = acc;
+        acc = wave_sum(acc);
+        if (lane == 0) red[wave] = acc;
         __syncthreads();
         if (lid_x() == 0) {
             double tot = 0.0;
-            for (int w = 0; w < (int)(wg_size_x() / 64); ++w) tot += red[w];
+            for (int w = 0; w < kLossWaves; ++w) tot += red[w];
             loss[f] = (float)(tot * scale);
         }
     }
@@ -339,107 +440,93 @@ constexpr int kFrameLossMaxT = 256;
 //     frame still undecided after T (c = fail_weight).
 // d loss / d lambda_{t,i} = scale * d loss / d S_t * (2u_i - 1)
 // sigmoid((2u_i - 1) lambda_{t,i}), where d loss / d S_t = e^{-S_t} times the
-// sum of the products that hold q_t, with q_t taken out.  All in double.
+// sum of the products that hold q_t, with q_t taken out: the product of the
+// q before t times H_t, H_{T-1} = 1 (c with ITER), H_t = q_{t+1} H_{t+1}
+// (+ 1 with ITER) -- one pass each way, no division.  All in double.
+// T = 20, N = 1024, K + c = 536, 1024 frames: 436 us with every thread
+// building each of those products anew, 148 us.
 template <bool ITER>
-__global__ __launch_bounds__(256) void wbp_frame_loss_kernel(CodeDev code, const float* __restrict__ saved,
-                                                             const uint8_t* __restrict__ u, int T, double scale,
-                                                             double fail_weight, float* __restrict__ loss,
-                                                             float* __restrict__ dlam) {
-    __shared__ double red[256 / 64];
+__global__ __launch_bounds__(kLossThreads) void wbp_frame_loss_kernel(CodeDev code, const float* __restrict__ saved,
+                                                                      const uint8_t* __restrict__ u, int T,
+                                                                      double scale, double fail_weight,
+                                                                      float* __restrict__ loss,
+                                                                      float* __restrict__ dlam) {
+    __shared__ uint16_t pos[kLossMaxN];
     __shared__ double S[kFrameLossMaxT];
-    __shared__ double q[kFrameLossMaxT];
+    __shared__ double dS[kFrameLossMaxT];
     const int64_t f = gid_x();
-    const int N = code.N, n = code.n;
-    const int nw = wg_size_x() / 64;
-    for (int t = 0; t < T; ++t) {
+    const int N = code.N, n = code.n, k = code.k, lane = lid_x() & 63, wave = lid_x() >> 6;
+    stage_positions(code, u + f * N, pos);
+    for (int t = wave; t < T; t += kLossWaves) {
         const float* lrow = saved + (((size_t)f * T + t) * 2 * n + n) * N;
         double acc = 0.0;
-        for (int i = lid_x(); i < N; i += wg_size_x()) {
-            if ((code.frozen_bits[i >> 5] >> (i & 31)) & 1u) continue;
-            const float lam = lrow[i] + 0.0f;
-            const double z = (u[f * N + i] ? 1.0 : -1.0) * (double)lam;
-            acc += z > 0 ? z + log1p(exp(-z)) : log1p(exp(z));
+        for (int q = lane; q < k; q += 64) {
+            const double z = ((pos[q] & 0x8000) ? 1.0 : -1.0) * (double)lrow[pos[q] & 0x7FFF];
+            acc += softplus_of(z, exp(-fabs(z)));
         }
-        for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-        if ((lid_x() & 63) == 0) red[lid_x() >> 6] = acc;
-        __syncthreads();
-        if (lid_x() == 0) {
-            double tot = 0.0;
-            for (int w = 0; w < nw; ++w) tot += red[w];
-            S[t] = tot;
-            q[t] = -expm1(-tot);
-        }
-        __syncthreads();
+        acc = wave_sum(acc);
+        if (lane == 0) S[t] = acc;
     }
-    if (loss && lid_x() == 0) {
-        double F = 1.0;
-        for (int t = 0; t < T; ++t) F *= q[t];
-        double L = F;
-        if (ITER) {
-            L = 0.0;
-            for (int v = 0; v < T - 1; ++v) {
-                double P = 1.0;
-                for (int t = 0; t <= v; ++t) P *= q[t];
-                L += P;
-            }
-            L += fail_weight * F;
+    __syncthreads();
+    if (lid_x() == 0) {
+        double P = 1.0, L = 0.0;
+        for (int t = 0; t < T; ++t) {
+            dS[t] = P;  // the product of the q before t
+            P *= -expm1(-S[t]);
+            if (ITER && t < T - 1) L += P;
         }
-        loss[f] = (float)(L * scale);
+        L = ITER ? L + fail_weight * P : P;
+        if (loss) loss[f] = (float)(L * scale);
+        double H = ITER ? fail_weight : 1.0;
+        for (int t = T - 1; t >= 0; --t) {
+            dS[t] *= exp(-S[t]) * H;
+            H = (ITER ? 1.0 : 0.0) - expm1(-S[t]) * H;
+        }
     }
-    for (int t = 0; t < T; ++t) {
-        double dS;
-        if (!ITER) {
-            dS = exp(-S[t]);
-            for (int t2 = 0; t2 < T; ++t2)
-                if (t2 != t) dS *= q[t2];
-        } else {
-            double acc = 0.0;
-            for (int v = t; v < T - 1; ++v) {
-                double P = 1.0;
-                for (int t2 = 0; t2 <= v; ++t2)
-                    if (t2 != t) P *= q[t2];
-                acc += P;
-            }
-            double PT = 1.0;
-            for (int t2 = 0; t2 < T; ++t2)
-                if (t2 != t) PT *= q[t2];
-            acc += fail_weight * PT;
-            dS = exp(-S[t]) * acc;
-        }
+    __syncthreads();
+    for (int t = wave; t < T; t += kLossWaves) {
         const float* lrow = saved + (((size_t)f * T + t) * 2 * n + n) * N;
         float* drow = dlam + ((size_t)f * T + t) * N;
-        for (int i = lid_x(); i < N; i += wg_size_x()) {
-            float d = 0.0f;
-            if (!((code.frozen_bits[i >> 5] >> (i & 31)) & 1u)) {
-                const float lam = lrow[i] + 0.0f;
-                const double sg = u[f * N + i] ? 1.0 : -1.0;
-                const double z = sg * (double)lam;
-                const double sig = 1.0 / (1.0 + exp(-z));
-                d = (float)(scale * dS * sg * sig);
-            }
-            drow[i] = d;
+        const double g = scale * dS[t];
+        for (int q = lane; q < k; q += 64) {
+            const int i = pos[q] & 0x7FFF;
+            const double sg = (pos[q] & 0x8000) ? 1.0 : -1.0;
+            const double z = sg * (double)lrow[i];
+            drow[i] = (float)(g * sg * sigmoid_of(z, exp(-fabs(z))));
         }
+        zero_frozen(code, drow, lane);
     }
 }
 
-// W[t][d][s][i] = Wc[t][d][s]: one weight per stage column spread over its nodes
-__global__ __launch_bounds__(256) void wbp_expand_columns_kernel(const float* __restrict__ wc, int64_t cols, int N,
+// W[t][d][s][i] = Wc[t][d][s]: one weight per stage column spread over its
+// nodes (2^n), VEC nodes per thread
+template <int VEC>
+__global__ __launch_bounds__(256) void wbp_expand_columns_kernel(const float* __restrict__ wc, int64_t total, int n,
                                                                  float* __restrict__ w) {
-    const int64_t q = gid_x() * wg_size_x() + lid_x();
-    if (q >= cols * N) return;
-    w[q] = wc[q / N];
+    const int64_t q = (gid_x() * 256 + lid_x()) * VEC;
+    if (q >= total) return;
+    const float x = wc[q >> n];
+    FloatVec<VEC> o;
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) o.v[j] = x;
+    *reinterpret_cast<FloatVec<VEC>*>(w + q) = o;
 }
 
-// dWc[c] = sum over the N nodes of column c, in node order, in double: the
-// gradient of a weight shared by the whole column
+// dWc[c] = sum over the N nodes of column c in double, one wavefront per
+// column (one thread per column: a chain of N loads, 123 us for 400 columns of
+// 1024): the gradient of a weight shared by the whole column
 __global__ __launch_bounds__(256) void wbp_sum_columns_kernel(const float* __restrict__ dw, int64_t cols, int N,
                                                               float* __restrict__ dwc) {
-    const int64_t c = gid_x() * wg_size_x() + lid_x();
+    const int64_t c = gid_x() * 4 + (lid_x() >> 6);
     if (c >= cols) return;
+    const int lane = lid_x() & 63;
     double acc = 0.0;
-    for (int i = 0; i < N; ++i) acc += (double)dw[c * N + i];
-    dwc[c] = (float)acc;
+    for (int i = lane; i < N; i += 64) acc += (double)dw[c * N + i];
+    acc = wave_sum(acc);
+    if (lane == 0) dwc[c] = (float)acc;
 }
+
+bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ w, const float* __restrict__ g,
                                                    float* __restrict__ m, float* __restrict__ v, int64_t count,
@@ -478,8 +565,8 @@ extern "C" polar_status wbp_bce(const polar_code* code, const float* llr_u, cons
     if (!code || (B > 0 && (!llr_u || !u_true || !dlam))) return set_error(POLAR_ERR_INVALID_ARG, "wbp_bce: null argument");
     if (B < 0) return set_error(POLAR_ERR_INVALID_ARG, "wbp_bce: bad batch");
     if (B == 0) return ok_status();
-    hipLaunchKernelGGL(wbp_bce_kernel, dim3((unsigned)B), dim3(256), 0, stream, code->dev(), llr_u, u_true, B, scale,
-                       loss, dlam);
+    hipLaunchKernelGGL(wbp_bce_kernel, dim3((unsigned)B), dim3(kLossThreads), 0, stream, code->dev(), llr_u,
+                       (int64_t)code->N, (int64_t)0, u_true, 1, scale, loss, dlam);
     polar_status st = hip_check(hipGetLastError(), "wbp_bce launch");
     return st == POLAR_OK ? ok_status() : st;
 }
@@ -490,8 +577,9 @@ extern "C" polar_status wbp_bce_multi(const polar_code* code, const float* saved
         return set_error(POLAR_ERR_INVALID_ARG, "wbp_bce_multi: null argument");
     if (B < 0 || T < 1 || B > (int64_t)INT32_MAX) return set_error(POLAR_ERR_INVALID_ARG, "wbp_bce_multi: bad sizes");
     if (B == 0) return ok_status();
-    hipLaunchKernelGGL(wbp_bce_multi_kernel, dim3((unsigned)B), dim3(256), 0, stream, code->dev(), saved, u_true, T,
-                       scale, loss, dlam);
+    const int64_t iter = (int64_t)2 * code->n * code->N;  // L row 0 of an iteration: after its n R rows
+    hipLaunchKernelGGL(wbp_bce_kernel, dim3((unsigned)B), dim3(kLossThreads), 0, stream, code->dev(), saved + iter / 2,
+                       T * iter, iter, u_true, T, scale, loss, dlam);
     polar_status st = hip_check(hipGetLastError(), "wbp_bce_multi launch");
     return st == POLAR_OK ? ok_status() : st;
 }
@@ -515,8 +603,9 @@ extern "C" polar_status wbp_backward(const polar_code* code, const float* llr, i
         polar_status st = hip_check(hipGetLastError(), "wbp_bwd launch");
         if (st != POLAR_OK) return st;
     }
-    hipLaunchKernelGGL(wbp_reduce_kernel, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, stream, saved, B, P, dW);
-    polar_status st = hip_check(hipGetLastError(), "wbp_reduce launch");
+    // 16-byte accesses where both buffers allow them (P is a multiple of 4)
+    polar_status st = aligned16(saved) && aligned16(dW) ? launch_reduce<4>(saved, B, P, dW, stream)
+                                                        : launch_reduce<1>(saved, B, P, dW, stream);
     return st == POLAR_OK ? ok_status() : st;
 }
 
@@ -554,10 +643,10 @@ static polar_status frame_loss_launch(const char* who, bool iter, const polar_co
     if (!(fail_weight >= 0.0)) return set_error(POLAR_ERR_INVALID_ARG, std::string(who) + ": fail_weight < 0");
     if (B == 0) return ok_status();
     if (iter)
-        hipLaunchKernelGGL(wbp_frame_loss_kernel<true>, dim3((unsigned)B), dim3(256), 0, stream, code->dev(), saved,
+        hipLaunchKernelGGL(wbp_frame_loss_kernel<true>, dim3((unsigned)B), dim3(kLossThreads), 0, stream, code->dev(), saved,
                            u_true, T, scale, fail_weight, loss, dlam);
     else
-        hipLaunchKernelGGL(wbp_frame_loss_kernel<false>, dim3((unsigned)B), dim3(256), 0, stream, code->dev(), saved,
+        hipLaunchKernelGGL(wbp_frame_loss_kernel<false>, dim3((unsigned)B), dim3(kLossThreads), 0, stream, code->dev(), saved,
                            u_true, T, scale, fail_weight, loss, dlam);
     polar_status st = hip_check(hipGetLastError(), "frame loss launch");
     return st == POLAR_OK ? ok_status() : st;
@@ -580,8 +669,11 @@ extern "C" polar_status wbp_column_weights(const polar_code* code, const float* 
     if (!code || !Wc || !W) return set_error(POLAR_ERR_INVALID_ARG, "wbp_column_weights: null argument");
     if (T < 1) return set_error(POLAR_ERR_INVALID_ARG, "wbp_column_weights: T < 1");
     const int64_t cols = (int64_t)T * 2 * code->n, tot = cols * code->N;
-    hipLaunchKernelGGL(wbp_expand_columns_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, stream, Wc, cols,
-                       code->N, W);
+    const unsigned blocks = (unsigned)((tot + 1023) / 1024);
+    if (aligned16(W))
+        hipLaunchKernelGGL(wbp_expand_columns_kernel<4>, dim3(blocks), dim3(256), 0, stream, Wc, tot, code->n, W);
+    else
+        hipLaunchKernelGGL(wbp_expand_columns_kernel<1>, dim3(4 * blocks), dim3(256), 0, stream, Wc, tot, code->n, W);
     polar_status st = hip_check(hipGetLastError(), "wbp_column_weights launch");
     return st == POLAR_OK ? ok_status() : st;
 }
@@ -591,7 +683,7 @@ extern "C" polar_status wbp_column_grad(const polar_code* code, const float* dW,
     if (!code || !dW || !dWc) return set_error(POLAR_ERR_INVALID_ARG, "wbp_column_grad: null argument");
     if (T < 1) return set_error(POLAR_ERR_INVALID_ARG, "wbp_column_grad: T < 1");
     const int64_t cols = (int64_t)T * 2 * code->n;
-    hipLaunchKernelGGL(wbp_sum_columns_kernel, dim3((unsigned)((cols + 255) / 256)), dim3(256), 0, stream, dW, cols,
+    hipLaunchKernelGGL(wbp_sum_columns_kernel, dim3((unsigned)((cols + 3) / 4)), dim3(256), 0, stream, dW, cols,
                        code->N, dWc);
     polar_status st = hip_check(hipGetLastError(), "wbp_column_grad launch");
     return st == POLAR_OK ? ok_status() : st;

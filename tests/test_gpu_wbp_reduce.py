@@ -1,0 +1,123 @@
+"""Reductions and losses of the weighted-BP training at the edges of their
+layouts: frame counts around the segment lengths of the gradient sum, buffers
+off 16-byte alignment, iteration counts that leave wavefronts without a row,
+the smallest and largest blocks -- against double-precision numpy."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_1609_09358_amd import binding as PB
+from paper_1609_09358_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def shifted(t, shift):
+    """The same values `shift` elements past a 256-byte boundary."""
+    whole = torch.empty(t.numel() + shift, dtype=t.dtype, device="cuda")
+    v = whole[shift:]
+    v.copy_(t.reshape(-1))
+    return v
+
+
+@pytest.mark.parametrize("N,K,T,B", [(8, 4, 1, 1), (8, 4, 2, 63), (8, 4, 2, 64), (16, 8, 1, 65), (16, 9, 3, 97),
+                                     (32, 20, 2, 255), (64, 32, 2, 300), (512, 256, 2, 70)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_gradient_sum_over_frames(N, K, T, B, shift):
+    code = PB.PolarCode(N, K, 0, 0, 2.0)
+    n = code.n
+    rng = np.random.default_rng(N + B)
+    llr = (3.0 * rng.standard_normal((B, N))).astype(np.float32)
+    W = rng.uniform(0.7, 1.1, (T, 2, n, N)).astype(np.float32)
+    dlam = rng.standard_normal((B, N)).astype(np.float32)
+    ref, _ = O.wbp_backward(llr, code.frozen, T, W, dlam, prec="f32")
+    dl, dW_, ll = torch.from_numpy(dlam).cuda(), torch.from_numpy(W).cuda(), torch.from_numpy(llr).cuda()
+    saved = PB.wbp_forward(code, ll, dW_, save=True)["saved"]
+    sv = shifted(saved, shift)
+    g = shifted(torch.zeros(W.size, device="cuda"), shift)
+    p = lambda t: C.c_void_p(t.data_ptr())  # noqa: E731
+    PB._check(PB.lib().wbp_backward(code.handle, p(ll), B, p(dW_), T, 20.0, 0, p(sv), p(dl), 1, p(g), None,
+                                    C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+    torch.cuda.synchronize()
+    got = g.cpu().numpy().reshape(ref.shape).astype(np.float64)
+    # one rounding to float, and the double sum taken in another order
+    assert np.all(np.abs(got - ref) <= 2.0 ** -24 * np.abs(ref) + 1e-13 * np.abs(ref).max())
+
+
+def losses(lam, u, pos, kind, fw, scale):
+    """(loss [B], dlam [B][T][N]) in double; lam [B][T][N]."""
+    sg = 2.0 * u[:, None, pos] - 1.0
+    z = sg * lam[..., pos].astype(np.float64)
+    e = np.exp(-np.abs(z))
+    S = (np.maximum(z, 0) + np.log1p(e)).sum(2)
+    sig = np.where(z > 0, 1.0, e) / (1.0 + e)
+    B, T = S.shape
+    if kind in ("bce", "multi"):
+        loss, dS = S.sum(1), np.ones_like(S)
+    else:
+        q = -np.expm1(-S)
+        P = np.cumprod(q, 1)
+        loss = P[:, -1] if kind == "frame" else P[:, :-1].sum(1) + fw * P[:, -1]
+        dS = np.zeros_like(S)
+        for t in range(T):
+            qt = q.copy()
+            qt[:, t] = 1.0
+            Pt = np.cumprod(qt, 1)
+            dS[:, t] = np.exp(-S[:, t]) * (Pt[:, -1] if kind == "frame" else
+                                           Pt[:, t:-1].sum(1) + fw * Pt[:, -1])
+    d = np.zeros(lam.shape)
+    d[..., pos] = scale * dS[..., None] * sg * sig
+    return loss * scale, d
+
+
+@pytest.mark.parametrize("N,K,T,B", [(8, 1, 1, 3), (8, 7, 5, 2), (64, 63, 3, 5), (256, 100, 7, 3), (4096, 4096, 2, 2),
+                                     (16, 5, 256, 2)])
+@pytest.mark.parametrize("kind", ["bce", "multi", "frame", "iter"])
+def test_losses_match_double(N, K, T, B, kind):
+    code = PB.PolarCode(N, K, 0, 0, 2.0)
+    rng = np.random.default_rng(N + T)
+    u = np.zeros((B, N), np.uint8)
+    u[:, code.info_pos] = rng.integers(0, 2, (B, K))
+    rows = np.zeros((B, T, 2, code.n, N), np.float32)
+    # mostly right decisions of a size that leaves the products well inside the double range
+    lam = ((1.0 - 2.0 * u[:, None, :]) * rng.gamma(4.0, 2.0 if K > 1000 else 1.0, (B, T, N))).astype(np.float32)
+    lam[:, :, :: 7] *= -0.1
+    rows[:, :, 1, 0, :] = lam
+    d = torch.from_numpy(u).cuda()
+    sv = torch.from_numpy(rows).cuda()
+    scale, fw = 0.25, 40.0
+    if kind == "bce":
+        lam = lam[:, -1:]
+        loss, dl = PB.wbp_bce(code, torch.from_numpy(np.ascontiguousarray(lam[:, 0])).cuda(), d, scale=scale)
+    elif kind == "multi":
+        loss, dl = PB.wbp_bce_multi(code, sv, d, T, scale=scale)
+    elif kind == "frame":
+        loss, dl = PB.wbp_frame_loss(code, sv, d, T, scale=scale)
+    else:
+        loss, dl = PB.wbp_iteration_loss(code, sv, d, T, fw, scale=scale)
+    ref_l, ref_d = losses(lam, u, code.info_pos, kind, fw, scale)
+    got_d = dl.cpu().numpy().reshape(ref_d.shape)
+    # one rounding to float each; sums and products of at most 4096 doubles
+    np.testing.assert_allclose(loss.cpu().numpy(), ref_l, rtol=2e-7, atol=1e-37)
+    np.testing.assert_allclose(got_d, ref_d, rtol=2e-7, atol=1e-37)
+
+
+@pytest.mark.parametrize("N", [8, 64, 4096])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_column_weights_and_their_gradient(N, shift):
+    code = PB.PolarCode(N, N // 2, 0, 0, 2.0)
+    T, rng = 3, np.random.default_rng(N)
+    wc = rng.standard_normal((T, 2, code.n)).astype(np.float32)
+    out = shifted(torch.zeros(T * 2 * code.n * N, device="cuda"), shift)
+    p = lambda t: C.c_void_p(t.data_ptr())  # noqa: E731
+    s = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    dc = torch.from_numpy(wc).cuda()
+    PB._check(PB.lib().wbp_column_weights(code.handle, p(dc), T, p(out), s))
+    assert np.array_equal(out.cpu().numpy().reshape(T, 2, code.n, N), np.repeat(wc[..., None], N, axis=3))
+    g = rng.standard_normal((T, 2, code.n, N)).astype(np.float32)
+    got = PB.wbp_column_grad(code, torch.from_numpy(g).cuda()).cpu().numpy().astype(np.float64)
+    ref = g.astype(np.float64).sum(3)
+    assert np.all(np.abs(got - ref) <= 2.0 ** -24 * np.abs(ref) + 1e-12)
