@@ -34,6 +34,11 @@ __device__ __forceinline__ void g_partials(float a, float b, float& da, float& d
     }
 }
 
+// Bound by HBM: every saved message read and its slot written once (the other
+// reads of a row come soon after the first, from the caches).  N = 1024, T = 20,
+// 1024 frames, 3.36 GB: 1275 us with each column's operands loaded when it is
+// reached, 855 us with the next column's in flight (3.9 TB/s); N = 256, T = 10,
+// 4096 frames, 1.34 GB: 441 and 324 us.
 template <int NLOG, int RLOG>
 __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
     CodeDev code, const float* __restrict__ llr, int64_t B, int T, float lmax, const float* __restrict__ W,
@@ -83,6 +88,30 @@ __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
     }
     float* S = saved + (size_t)frame * T * 2 * n * N;
 
+    // Operands of the next column, loaded before the present one is worked
+    // on: a column's loads may not pass the stores of the one before it (one
+    // buffer), so without this a wavefront waits for memory once per column.
+    // x: L row s + 1 (of iteration it for the L sweep, it - 1 for the R sweep),
+    // y: R row s, w: the column's weights, all in the layout of its window.
+    float nx[V], ny[V], nw[V];
+    auto fetch = [&](auto DC, auto SC, int it) {
+        constexpr int dir = decltype(DC)::value, s = decltype(SC)::value;
+        constexpr int k = s / G::r;
+        const int ib = idx_base<G, k>(t);
+        const float* Sy = S + (size_t)it * 2 * n * N;
+        const int lt = dir == 1 ? it : it - 1;
+        const float* Sx = S + (size_t)(lt > 0 ? lt : 0) * 2 * n * N;
+        const float* Wc = W + (size_t)(it * 2 + dir) * n * N;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const int off = ib + (v << G::wbase(k));
+            if constexpr (s + 1 < n) nx[v] = Sx[(size_t)(1 * n + s + 1) * N + off];
+            if constexpr (s > 0) ny[v] = Sy[(size_t)(0 * n + s - 1) * N + off];
+            nw[v] = Wc[(size_t)s * N + off];
+        }
+    };
+    fetch(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{}, T - 1);
+
     for (int it = T - 1; it >= 0; --it) {
         // the loss reads LLR(u) after this iteration (every iteration, or only
         // the last); row 0 of L feeds nothing else, so its adjoint is d loss / d lambda
@@ -92,9 +121,7 @@ __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
 #pragma unroll
             for (int v = 0; v < V; ++v) aL[0][v] = dl[ib + v];
         }
-        const float* Wit = W + (size_t)it * 2 * n * N;
         float* St = S + (size_t)it * 2 * n * N;
-        const float* Sprev = S + (size_t)(it > 0 ? it - 1 : 0) * 2 * n * N;
         // ---------------- undo the L sweep: columns 0..n-1
         static_for<0, G::NWIN>([&](auto KC) {
             constexpr int k = decltype(KC)::value;
@@ -109,11 +136,12 @@ __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
                 float A[V], Rr[V], Wr[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    const int off = ib + (v << wb);
-                    A[v] = (s + 1 == n) ? chanc[v] : St[(size_t)(1 * n + s + 1) * N + off];
-                    Rr[v] = (s == 0) ? prior[v] : St[(size_t)(0 * n + s - 1) * N + off];
-                    Wr[v] = Wit[(size_t)(1 * n + s) * N + off];
+                    A[v] = (s + 1 == n) ? chanc[v] : nx[v];
+                    Rr[v] = (s == 0) ? prior[v] : ny[v];
+                    Wr[v] = nw[v];
                 }
+                if constexpr (s + 1 < n) fetch(std::integral_constant<int, 1>{}, std::integral_constant<int, s + 1>{}, it);
+                else fetch(std::integral_constant<int, 0>{}, std::integral_constant<int, n - 1>{}, it);
                 float dWv[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
@@ -161,11 +189,12 @@ __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
                 float Lp[V], Rr[V], Wr[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
-                    const int off = ib + (v << wb);
-                    Rr[v] = (s == 0) ? prior[v] : St[(size_t)(0 * n + s - 1) * N + off];
-                    Lp[v] = (s + 1 == n) ? chanc[v] : (it == 0 ? 0.0f : Sprev[(size_t)(1 * n + s + 1) * N + off]);
-                    Wr[v] = Wit[(size_t)(0 * n + s) * N + off];
+                    Rr[v] = (s == 0) ? prior[v] : ny[v];
+                    Lp[v] = (s + 1 == n) ? chanc[v] : (it == 0 ? 0.0f : nx[v]);
+                    Wr[v] = nw[v];
                 }
+                if constexpr (s > 0) fetch(std::integral_constant<int, 0>{}, std::integral_constant<int, s - 1>{}, it);
+                else fetch(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{}, it > 0 ? it - 1 : 0);
                 float dWv[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
@@ -241,6 +270,14 @@ const BwdEntry* lookup_bwd(int n, int r) {
 }  // namespace bp
 
 namespace {
+
+// Register layout of the adjoint (nodes per thread 2^r): r = 2 keeps more
+// wavefronts in flight, which the adjoint, bound by its memory accesses, needs
+// where frames are few (N = 1024, T = 20: 287 against 324 us for 200 frames,
+// 1183 against 1176 us for 1024, with the sum over frames; N = 2048, T = 10,
+// 512 frames: 637 against 669 us); at N = 4096 its 1024 threads per frame leave
+// 128 registers and spill more than r = 3 (865 against 818 us for 256 frames).
+int bwd_default_variant(int n) { return n <= 11 ? 2 : 3; }
 
 // Sum of the per-frame gradients part[f][q] over the frames, in double.  One
 // thread per VEC columns q would leave the chip idle (P / 256 workgroups, a
@@ -592,7 +629,7 @@ extern "C" polar_status wbp_backward(const polar_code* code, const float* llr, i
     if (B < 0 || T < 1 || !(llr_max > 0.0f)) return set_error(POLAR_ERR_INVALID_ARG, "wbp_backward: bad sizes");
     if (dlam_iters != 1 && dlam_iters != T)
         return set_error(POLAR_ERR_INVALID_ARG, "wbp_backward: dlam_iters must be 1 or T");
-    const int v = variant ? variant : bp_default_variant(code->n);
+    const int v = variant ? variant : bwd_default_variant(code->n);
     const bp::BwdEntry* e = bp::lookup_bwd(code->n, v);
     if (!e) return set_error(POLAR_ERR_UNSUPPORTED, "wbp_backward: no kernel variant for this block length");
     const int64_t P = (int64_t)T * 2 * code->n * code->N;
