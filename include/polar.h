@@ -323,10 +323,9 @@ polar_status polar_workspace_size(const polar_code* code, int64_t B, int32_t L,
 
 /* Per-workgroup LDS budget of the list decoder in bytes, 4096..163840, or 0
  * (the default: a CU's 160 KB divided by the number of the kernel's one-wave
- * workgroups its registers let share a CU).  A list decode keeps as much of
- * its state in LDS as the budget allows: when it does not all fit, the per-bit
- * trace moves to the workspace's global slice first, then the largest LLR
- * tree levels do.  A smaller budget lets more workgroups share a CU.
+ * workgroups its registers let share a CU).  When the state of a list decode
+ * does not fit the budget, its trace moves from LDS to the workspace's global
+ * slice.  A smaller budget lets more workgroups share a CU.
  * Process-wide; it applies to plans made afterwards, so query workspace sizes
  * again after a change.  POLAR_ERR_INVALID_ARG outside the range.  Host only;
  * polar_get_scl_lds_budget returns the setting (0 = automatic). */
@@ -335,17 +334,16 @@ int64_t polar_get_scl_lds_budget(void);
 
 /* How the list decoder finds the L survivors among the 2L candidates of a
  * branching bit (Sec. II-A describes the first two): 1 the pruned pseudo sort
- * -- each candidate counts the candidates before it; 2 the bitonic sorting
- * network across the wavefront, run until the L smallest candidates are
- * separated (list sizes 8 and 32, N >= 32); 3 threshold
- * selection -- the L-th smallest metric found bit by bit with wavefront
- * ballots (list sizes 8, 16 and 32, N >= 32); other lists use the pseudo
- * sort.  0 (default) automatic: the bitonic network for L = 8 and 32, where
- * it measured fastest on MI355X, the pseudo sort otherwise.  All decide
- * survival by the strict order (metric, parent position, bit) and keep the
- * survivors in the order the candidates are listed (parent position, then
- * bit), so results are identical.  Process-wide; host only; mode outside 0..3
- * gives POLAR_ERR_INVALID_ARG. */
+ * -- each candidate counts the candidates before it; 2 a bitonic network on
+ * the metrics across the list's lanes, run until the L-th smallest is known;
+ * 3 threshold selection -- the L-th smallest metric found bit by bit with
+ * wavefront ballots.  1 and 3 exist for list sizes 8 and 32 with N >= 32;
+ * other lists use the network.  0 (default) automatic: the network, which
+ * measured fastest on MI355X.  All decide survival by the strict order
+ * (metric, parent position, bit) and keep the survivors in the order the
+ * candidates are listed (parent position, then bit), so results are
+ * identical.  Process-wide; host only; mode outside 0..3 gives
+ * POLAR_ERR_INVALID_ARG. */
 polar_status polar_set_scl_ranking(int32_t mode);
 int32_t polar_get_scl_ranking(void);
 

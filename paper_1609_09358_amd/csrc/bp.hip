@@ -569,7 +569,8 @@ __attribute__((amdgpu_waves_per_eu(bp_waves_per_eu<NLOG, RLOG, WEIGHTED, SAVE, W
 // Persistent form for ragged batches: workgroups walk the list ids[0..*count)
 // (the count lives on the device); frame id's LLR row starts at element
 // io->off[id] of io->llr, its u_hat row at id * u_stride; iters and ok are
-// indexed by id; failed frames are appended to fail_ids (one atomic each).
+// indexed by id; failed frames are appended to their code's queue (one atomic
+// each).
 // With io->codes, frame id uses the code io->codes[io->code_of[id]] (all of
 // the kernel's block length).
 // The unweighted N = 2048 gather kernel (256 threads per frame) fits three
@@ -584,7 +585,7 @@ __attribute__((amdgpu_waves_per_eu(gather_waves_per_eu<NLOG, RLOG, WEIGHTED>()))
     CodeDev code, const MixedIo* __restrict__ mio, const int32_t* __restrict__ ids, const int32_t* __restrict__ count,
     int max_iter, int stop, float lmax, const float* __restrict__ W, uint8_t* __restrict__ u_hat, int64_t u_stride,
     int32_t* __restrict__ iters_out, uint8_t* __restrict__ ok_out, int32_t* __restrict__ fail_ids,
-    int32_t* __restrict__ fail_count) {
+    int64_t fail_stride, int32_t* __restrict__ fail_count) {
     using G = Geom<NLOG, RLOG>;
     __shared__ BpShared<G> sh;
     const int tid = lid_x();
@@ -599,7 +600,8 @@ __attribute__((amdgpu_waves_per_eu(gather_waves_per_eu<NLOG, RLOG, WEIGHTED>()))
         if (G::T >= 64) __syncthreads();  // the previous frame's staging is read
         if (q >= cnt) break;             // only when T < 64: this slot's wavefront lanes leave alone
         const int id = ids[q];
-        const CodeDev cd = mio->codes ? mio->codes[mio->code_of[id]] : code;
+        const int cid = mio->codes ? mio->code_of[id] : 0;
+        const CodeDev cd = mio->codes ? mio->codes[cid] : code;
         FrameIO io;
         io.llr = llr + off[id];
         io.u_hat = u_hat + (int64_t)id * u_stride;
@@ -609,7 +611,7 @@ __attribute__((amdgpu_waves_per_eu(gather_waves_per_eu<NLOG, RLOG, WEIGHTED>()))
         io.ok = ok_out + id;
         io.saved = nullptr;
         const bool okv = bp_frame<G, WEIGHTED, false>(cd, io, max_iter, stop, lmax, W, sh, t, slot);
-        if (t == 0 && !okv) fail_ids[atomicAdd(fail_count, 1)] = id;
+        if (t == 0 && !okv) fail_ids[cid * fail_stride + atomicAdd(&fail_count[cid], 1)] = id;
     }
 }
 
@@ -619,7 +621,7 @@ using KernelFn = void (*)(CodeDev, const float*, int64_t, int, int, float, const
                           float*, int32_t*, uint8_t*, float*);
 
 using GatherFn = void (*)(CodeDev, const MixedIo*, const int32_t*, const int32_t*, int, int, float, const float*,
-                          uint8_t*, int64_t, int32_t*, uint8_t*, int32_t*, int32_t*);
+                          uint8_t*, int64_t, int32_t*, uint8_t*, int32_t*, int64_t, int32_t*);
 
 struct Entry {
     KernelFn plain, weighted, weighted_save, exact, weighted_stage;
@@ -719,13 +721,14 @@ polar_status bp_gather_grid(const polar_code* code, const bp_params* p, int64_t 
 
 polar_status launch_bp_gather(const polar_code* code, const MixedIo* io, const int32_t* ids, const int32_t* count,
                               const bp_params* p, uint8_t* u_hat, int64_t u_stride, int32_t* iters, uint8_t* ok,
-                              int32_t* fail_ids, int32_t* fail_count, int grid, hipStream_t stream) {
+                              int32_t* fail_ids, int64_t fail_stride, int32_t* fail_count, int grid,
+                              hipStream_t stream) {
     const int variant = p->variant ? p->variant : bp_default_variant(code->n);
     const bp::Entry* e = bp::lookup(code->n, variant);
     if (!e) return set_error(POLAR_ERR_UNSUPPORTED, "bp: no kernel variant for this block length");
     bp::GatherFn fn = p->weights ? e->gather_weighted : e->gather_plain;
     hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(e->wg), 0, stream, code->dev(), io, ids, count, p->max_iter,
-                       p->stop, p->llr_max, p->weights, u_hat, u_stride, iters, ok, fail_ids, fail_count);
+                       p->stop, p->llr_max, p->weights, u_hat, u_stride, iters, ok, fail_ids, fail_stride, fail_count);
     return hip_check(hipGetLastError(), "bp_gather_kernel launch");
 }
 

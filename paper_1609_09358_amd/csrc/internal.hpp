@@ -105,36 +105,65 @@ struct MixedIo {
     const CodeDev* codes;
 };
 
-// persistent BP over a device list of frame ids with ragged row offsets;
-// failed frames are appended to fail_ids
+// persistent BP over a device list of frame ids with ragged row offsets; a
+// failed frame of code c (0 without io->codes) is appended to the queue at
+// fail_ids + c * fail_stride, of length fail_count[c]
 polar_status bp_gather_grid(const polar_code* code, const bp_params* p, int64_t max_frames, int* grid);
 // u_hat row of frame f: f * u_stride
 polar_status launch_bp_gather(const polar_code* code, const MixedIo* io, const int32_t* ids, const int32_t* count,
                               const bp_params* p, uint8_t* u_hat, int64_t u_stride, int32_t* iters, uint8_t* ok,
-                              int32_t* fail_ids, int32_t* fail_count, int grid, hipStream_t stream);
+                              int32_t* fail_ids, int64_t fail_stride, int32_t* fail_count, int grid,
+                              hipStream_t stream);
 bool bp_variant_supported(int n, int variant);
 int bp_default_variant(int n);
 int bp_list_variants(int n, int32_t* ids, int cap);
 
 struct SclPlan {
-    int gl;              // LLR levels >= gl live in the global slice
+    int slots;           // path slots per workgroup: L times the frames it may decode at once
     size_t lds_bytes;    // dynamic LDS per workgroup
+    int surv_off;        // LDS byte offset of the survivor list
     int trace_glob;      // 1: the per-block trace lives in the global slice
     int tb_off;          // LDS byte offset of the trace when !trace_glob
     size_t trace_off;    // byte offset of the trace inside the global slice
-    size_t glob_per_wg;  // global slice bytes per workgroup (levels >= gl, trace)
+    size_t glob_per_wg;  // global slice bytes per workgroup (levels > 5, trace)
     int grid;            // workgroups launched
+    int target;          // wavefronts to fill before one takes a second frame
     int lay_n;           // log2 of the largest block length the layout holds
 };
-polar_status scl_plan(const polar_code* code, int L, int64_t max_frames, SclPlan* plan);
+// at most max_fpw frames per workgroup at once (their state then takes no more
+// room than that)
+polar_status scl_plan(const polar_code* code, int L, int64_t max_frames, SclPlan* plan, int max_fpw = 64);
 // a plan that holds any code with n <= max_n (n >= 5)
-polar_status scl_plan_dims(int max_n, int L, int64_t max_frames, SclPlan* plan);
+polar_status scl_plan_dims(int max_n, int L, int64_t max_frames, SclPlan* plan, int max_fpw = 64);
+
+// The frames of one list-decoder launch: queue k holds the frame ids
+// ids[code_ids[k] * queue_stride + i] of code code_ids[k], i < its length
+// (count_dev[code_ids[k]], or count_host without count_dev).  One plain list
+// is queue 0 with code id 0; without ids frame i is i.
+constexpr int kSclQueues = 16;
+struct SclWork {
+    const int32_t* ids;
+    const int32_t* count_dev;
+    int64_t count_host;
+    int64_t queue_stride;
+    int32_t n_queues;
+    int32_t code_ids[kSclQueues];
+    static SclWork list(const int32_t* ids, const int32_t* count_dev, int64_t count_host) {
+        SclWork w{};
+        w.ids = ids;
+        w.count_dev = count_dev;
+        w.count_host = count_host;
+        w.n_queues = 1;
+        return w;
+    }
+};
+
 // io (optional): LLR rows of a ragged batch (frame f at element io->off[f]),
-// u_hat rows then at f * u_stride
-polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float* llr, int L,
-                        const int32_t* frame_ids, const int32_t* count_dev, int64_t count_host,
-                        uint8_t* u_hat, uint8_t* crc_ok, float* pm, void* glob,
-                        hipStream_t stream, const MixedIo* io = nullptr, int64_t u_stride = 0);
+// u_hat rows then at f * u_stride; with io->codes queue k's frames are decoded
+// with io->codes[code_ids[k]]
+polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float* llr, int L, const SclWork& work,
+                        uint8_t* u_hat, uint8_t* crc_ok, float* pm, void* glob, hipStream_t stream,
+                        const MixedIo* io = nullptr, int64_t u_stride = 0);
 
 int device_cu_count();
 

@@ -7,9 +7,9 @@
 // block length; then, per block length, as concurrent branches on the plan's
 // streams: a persistent BP kernel walks the list (its length read on the
 // device) decoding every frame with its own code and appends the frames whose
-// verdict is not ok to the group's queue, and a persistent CA-SCL kernel
-// drains that queue, again with each frame's own code (its layout holds the
-// group's largest block length).  After the branches join, a merge kernel
+// verdict is not ok to their code's queue, and a persistent CA-SCL kernel
+// drains the queues of the group's codes (a wavefront decodes several frames
+// of one code at once).  After the branches join, a merge kernel
 // writes every frame's information bits, its list-decoder flag and the
 // statistics.  (Codes shorter than 32 bits form one group each.)  No host round trip and no per-call
 // allocation: the plan owns its workspace.  Because the kernels read the
@@ -25,6 +25,7 @@ namespace {
 
 constexpr int kMaxCodes = 16;
 constexpr int kMaxBranches = 4;
+static_assert(kMaxCodes <= kSclQueues, "a group's codes are queues of one list-decoder launch");
 
 struct MixedArgs {
     MixedIo io;                    // llr, llr_off
@@ -99,6 +100,7 @@ struct polar_mixed {
     // groups: codes of one block length (one code each below 32 bits)
     int n_groups = 0;
     std::vector<int> rep;           // per group: its first code
+    std::vector<SclWork> work;      // per group: the failure queues of its codes
     std::vector<bp_params> params;  // per group (the first code's variant)
     std::vector<SclPlan> scl;       // per group
     std::vector<int> bp_grid;       // per group
@@ -107,9 +109,9 @@ struct polar_mixed {
     MixedArgs* dargs = nullptr;
     CodeDev* dcodes = nullptr;
     int32_t* gmap = nullptr;    // [n_codes] group of each code
-    int32_t* counts = nullptr;  // [2 * n_codes]: bucket sizes, then queue sizes
+    int32_t* counts = nullptr;  // [2 * n_codes]: bucket sizes by group, then queue sizes by code
     int32_t* lists = nullptr;   // [n_groups][cap]
-    int32_t* queues = nullptr;  // [n_groups][cap]
+    int32_t* queues = nullptr;  // [n_codes][cap] failed frames of each code
     uint8_t* ok = nullptr;
     int32_t* iters = nullptr;
     uint8_t* scl_ok = nullptr;
@@ -217,7 +219,7 @@ extern "C" polar_status polar_mixed_create(const polar_code* const* codes, int32
     const size_t o_gmap = take(sizeof(int32_t) * n_codes);
     const size_t o_cnt = take(sizeof(int32_t) * 2 * n_codes);
     const size_t o_lists = take(sizeof(int32_t) * m->n_groups * max_frames);
-    const size_t o_queues = take(sizeof(int32_t) * m->n_groups * max_frames);
+    const size_t o_queues = take(sizeof(int32_t) * n_codes * max_frames);
     const size_t o_ok = take(max_frames);
     const size_t o_it = take(sizeof(int32_t) * max_frames);
     const size_t o_sok = take(max_frames);
@@ -240,6 +242,15 @@ extern "C" polar_status polar_mixed_create(const polar_code* const* codes, int32
     m->iters = reinterpret_cast<int32_t*>(b + o_it);
     m->scl_ok = reinterpret_cast<uint8_t*>(b + o_sok);
     m->u = reinterpret_cast<uint8_t*>(b + o_u);
+    for (int g = 0; g < m->n_groups; ++g) {
+        SclWork w{};
+        w.ids = m->queues;
+        w.queue_stride = max_frames;
+        w.count_dev = m->counts + n_codes;
+        for (int c = 0; c < n_codes; ++c)
+            if (gmap[c] == g) w.code_ids[w.n_queues++] = c;
+        m->work.push_back(w);
+    }
     for (size_t j = 0; j < m->scl.size(); ++j) m->glob.push_back(m->scl[j].glob_per_wg ? (void*)(b + o_g[j]) : nullptr);
     std::vector<CodeDev> hc(n_codes);
     for (int c = 0; c < n_codes; ++c) hc[c] = codes[c]->dev();
@@ -286,12 +297,11 @@ static polar_status mixed_pipeline(polar_mixed* m, hipStream_t st) {
     for (int g = 0; g < ng; ++g) {
         hipStream_t bs = m->br[g % m->nbr];
         const polar_code* code = m->codes[m->rep[g]];
-        int32_t* queue = m->queues + (int64_t)g * m->cap;
-        int32_t* qcount = m->counts + nc + g;
         if ((r = launch_bp_gather(code, &m->dargs->io, m->lists + (int64_t)g * m->cap, m->counts + g, &m->params[g],
-                                  m->u, m->maxN, m->iters, m->ok, queue, qcount, m->bp_grid[g], bs)) != POLAR_OK)
+                                  m->u, m->maxN, m->iters, m->ok, m->queues, m->cap, m->counts + nc, m->bp_grid[g],
+                                  bs)) != POLAR_OK)
             return r;
-        if ((r = launch_scl(code, m->scl[g], nullptr, m->L, queue, qcount, 0, m->u, m->scl_ok, nullptr, m->glob[g], bs,
+        if ((r = launch_scl(code, m->scl[g], nullptr, m->L, m->work[g], m->u, m->scl_ok, nullptr, m->glob[g], bs,
                             &m->dargs->io, m->maxN)) != POLAR_OK)
             return r;
     }

@@ -1,34 +1,44 @@
 // scl.hip -- CRC-aided successive-cancellation list decoder (Sec. II-A).
 //
-// One wavefront decodes one frame at a time; workgroups stay resident and walk
-// a list of frames whose length may live on the device (the hybrid decoder
-// feeds it the compacted BP failures without a host round trip).
+// One wavefront decodes up to 64 / L frames of one code at a time; workgroups
+// stay resident and walk lists of frames whose lengths may live on the device
+// (the hybrid decoder feeds it the compacted BP failures without a host round
+// trip).  Frames of one code take the same branches -- which bits are frozen,
+// how long the list is -- so path slot l of the wavefront's frame s is lane
+// s L + l, and every instruction and lane exchange of the bit loop serves all
+// of them.  Where there are fewer frames than wavefronts the chip runs at once,
+// a wavefront takes fewer (down to one): a frame's latency is shortest when
+// its block starts have the wavefront to themselves.
 //
-// Path slot l is owned by lane l.  The LLR tree of a path (level d holds 2^d
-// values, level n is the channel) and its partial sums (level d holds 2^d
-// bits) are split in two:
+// The LLR tree of a path (level d holds 2^d values, level n is the channel) and
+// its partial sums (level d holds 2^d bits) are split in two:
 //   - levels below BL = min(n, 5) live in the registers of the owning lane;
 //   - level BL lives in LDS and the levels above it in the workgroup's global
-//     slice (partial sums of levels >= 5 in LDS); they are shared lazily:
-//     each slot keeps, per level, the slot whose array it reads.  Bit i rewrites levels ctz(i)..BL of every path into the
-//     path's own slot and reads level ctz(i)+1 through the pointer, which no
-//     path writes during bit i; partial sums are handled the same way.
+//     slice, but for the two below the channel, which are computed from the
+//     channel again when they are needed (partial sums of levels 5 and 6 in LDS,
+//     the others in the slice); they are shared lazily:
+//     each slot keeps, per level, the slot whose array it reads.  A block start
+//     rewrites levels ctz(i)..BL of every path into the path's own slot and
+//     reads level ctz(i)+1 through the pointer, which no path writes there;
+//     partial sums are handled the same way.  The pointers change at block
+//     boundaries only: inside a block a path keeps the slot it held at the
+//     block start, and takes that slot's pointers at the block's end.
 // Bits are processed in blocks of 2^BL.  Inside a block, ctz(i) and the number
 // of trailing ones of i are compile-time constants, so a block is unrolled
 // into straight-line code: a bit recomputes levels ctz(i)..0 in registers
 // (level BL is read from LDS at the block start and once in the middle),
 // decides, and folds the decided bit into the partial sums held in registers.
 // A branching path is copied by pulling from the parent's lane exactly the
-// registers that later bits of the block still read, plus the two pointer
-// vectors.  The candidates of a branching bit are listed parent by parent
-// (bit 0 first); the L smallest under the strict order (metric, parent list
-// position, bit) survive -- the pruned pseudo sort of Sec. II-A with a strict
-// tie rule -- and keep that candidate order, so a survivor's slot is the
-// number of survivors listed before it (found with a wavefront ballot) and
-// slot index and list position coincide.  Which candidates survive is found
-// by counting (each candidate counts the smaller ones), a bitonic sort across
-// the wavefront, or threshold selection (the L-th smallest metric found bit by
-// bit with ballots).  The CRC is tracked per path as a
+// registers that later bits of the block still read.  The candidates of a
+// branching bit are listed parent by parent (bit 0 first); the L smallest under
+// the strict order (metric, parent list position, bit) survive -- the pruned
+// pseudo sort of Sec. II-A with a strict tie rule -- and keep that candidate
+// order, so a survivor's slot is the number of survivors listed before it
+// (found with two wavefront ballots) and slot index and list position coincide.
+// Each lane holds its path's two candidates.  Which survive follows from the
+// L-th smallest metric of the frame, found by a sorting network on the metrics
+// alone (or bit by bit, or by counting, see select below); candidates that tie
+// with it are taken in candidate order.  The CRC is tracked per path as a
 // running syndrome (linear in the decided bits).  Each path carries its
 // decided bits of the current block in a register word and the slot it held
 // at the block start (both pulled from the parent on a branch); at every
@@ -38,13 +48,13 @@
 //
 // A frame's decode is a long chain of dependent steps, so throughput comes
 // from many frames in flight: the kernel is held to 128 VGPRs (four waves per
-// SIMD) and the LDS state is sized to let sixteen one-wave workgroups share a
-// CU; the trace (5 bytes per block and path) moves to the workgroup's global
-// slice when it does not fit.
+// SIMD); the trace (5 bytes per block and path) moves to the workgroup's
+// global slice when it does not fit the LDS budget.
 #include <atomic>
 #include <type_traits>
 
 #include "internal.hpp"
+#include "lane_ops.hpp"
 
 namespace polarhip {
 namespace scl {
@@ -59,11 +69,12 @@ __device__ __forceinline__ float f_ms(float a, float b) {
 }
 
 // g(a, b) = b + (1 - 2u) a with the partial-sum bit u at bit position q of
-// word w (q known at compile time where it is called): the bit moved onto
-// a's sign, b - a being b + (-a), rounded alike
+// word w (q known at compile time where it is called): the bit becomes the
+// sign of a 1.0 and one fused multiply-add does the rest (the product with
+// +-1 is exact, so the sum rounds as b + a or b - a does)
 __device__ __forceinline__ float g_bit(float a, float b, uint32_t w, int q) {
-    const uint32_t sb = (w << (31 - q)) & 0x80000000u;
-    return b + __uint_as_float(__float_as_uint(a) ^ sb);
+    const float sg = __uint_as_float(((w << (31 - q)) & 0x80000000u) | 0x3F800000u);
+    return __fmaf_rn(a, sg, b);
 }
 
 __device__ __forceinline__ void wave_mem_order() {
@@ -90,7 +101,7 @@ using glb_ptr = __attribute__((address_space(1))) T*;
 // plain 4-lane vectors (the HIP vector classes do not bind to pointers of a
 // named address space)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 template <typename T>
 __device__ __forceinline__ lds_ptr<T> as_lds(void* p) {
@@ -141,21 +152,46 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src) {
     return (uint64_t)__shfl((unsigned long long)v, src, 64);
 }
 
-// word offset of partial-sum level d >= 5 inside a slot's LDS words
-__device__ __forceinline__ int ps_off(int d) { return (1 << (d - 5)) - 1; }
+// A slot's row of the workgroup's global slice, 2^row_log words: LLR level d
+// >= 6 at word 2^d and, in the words the levels leave free, the partial-sum
+// levels from 7 on.  Partial-sum level d >= 5 is 2^(d - 5) words: levels 5 and
+// 6, read and written at half and a quarter of the block starts, live in LDS,
+// levels 7 to 10 in words 0..59 of the row, level 11 (N = 4096) in the middle
+// of the row.  With all of them in LDS (12 KB more at N = 1024 with 64 slots)
+// nine instead of sixteen wavefronts fit a CU.
+// Two forms, by the frames a wavefront takes:
+//   - several (deep): levels 6 .. n - 3 are kept; n - 2 and n - 1 are computed
+//     from the channel row, which all paths share, whenever a block start needs
+//     them.  The slices of a full chip go through HBM, and the top levels are
+//     40 % of that traffic, which bounds large batches at L = 32;
+//   - one: every level is kept (at N = 4096 up to n - 2), which has the shorter
+//     chain of operations.
+// 8192 frames of N = 1024 at L = 32: 1342 us with all levels kept, 1225 us deep;
+// one frame: 429 and 465 us.
+constexpr int kPsLds = 7;     // first partial-sum level outside LDS
+constexpr int kPsWords = 3;   // LDS words per slot, levels 5 and 6
+__host__ __device__ __forceinline__ constexpr int row_log(int n, bool deep) {
+    return deep ? (n == 12 ? 11 : n > 8 ? n - 2 : 6) : n;
+}
+// whether LLR level d > 5 of block length 2^n is kept
+__device__ __forceinline__ constexpr bool kept(int n, int d, bool deep) {
+    return deep ? d <= n - 3 : n < 12 || d <= n - 2;
+}
+// word offset inside a slot's LDS words (d < 7) or its row
+__device__ __forceinline__ constexpr int ps_off(int d, int rlog) {
+    return d < kPsLds ? (1 << (d - 5)) - 1 : d == 11 ? 1 << (rlog - 1) : (1 << (d - 5)) - (1 << (kPsLds - 5));
+}
+
+// Level 5 of a slot is 32 floats in LDS, without padding: the 16-byte group e
+// is kept at e ^ swz(slot), so that the same group of 8 (32 banks) or 16 (64
+// banks) neighbouring slots is spread over all banks
+constexpr int kSlotFloats = 32;
+__device__ __forceinline__ int swz(int slot) { return ((slot >> 1) ^ (slot << 2)) & 7; }
 
 constexpr int ctz_c(int v) {
     int c = 0;
     while (((v >> c) & 1) == 0) ++c;
     return c;
-}
-
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
 }
 
 // partial-sum block of 2^T bits finished by `bit`, from the T levels below it
@@ -171,54 +207,21 @@ __device__ __forceinline__ uint32_t combine(uint32_t bit, const uint32_t (&ps)[5
     return cur;
 }
 
-// rank of this lane's candidate among the first ncand lanes under
-// (metric, lane); metrics are non-negative, so their bit patterns order them.
-// The metrics go through LDS once; each lane then reads them back as uint4
-// broadcasts, four at a time, so the reads overlap.
-template <int L>
-__device__ __forceinline__ int candidate_rank(lds_ptr<uint32_t> mets, int ncand, float met, int lane) {
-    constexpr int NC = 2 * L;
-    constexpr int G = NC / 4 < 1 ? 1 : (NC / 4 > 4 ? 4 : NC / 4);  // uint4 reads in flight
-    if (lane < ncand) mets[lane] = __float_as_uint(met);
-    wave_mem_order();
-    const uint32_t mb = __float_as_uint(met);
-    int rank = 0;
-    for (int c0 = 0; c0 < ncand; c0 += 4 * G) {
-        u32x4 v[G];
-#pragma unroll
-        for (int g = 0; g < G; ++g) v[g] = ((lds_ptr<const u32x4>)(mets + c0))[g];
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int c = c0 + 4 * g;
-            rank += (c + 0 < ncand && (v[g].x < mb || (v[g].x == mb && c + 0 < lane))) ? 1 : 0;
-            rank += (c + 1 < ncand && (v[g].y < mb || (v[g].y == mb && c + 1 < lane))) ? 1 : 0;
-            rank += (c + 2 < ncand && (v[g].z < mb || (v[g].z == mb && c + 2 < lane))) ? 1 : 0;
-            rank += (c + 3 < ncand && (v[g].w < mb || (v[g].w == mb && c + 3 < lane))) ? 1 : 0;
-        }
-    }
-    return rank;
-}
+// ------------------------------------------------------------ survivors
+// A lane holds the two candidates of its path as metric bits (metrics are
+// non-negative, so their bit patterns order them): kh, the hard decision of
+// the path's LLR, which keeps the path metric, and kf >= kh, the other.
 
-// Bitonic sorting network over the candidates across the wavefront (the
-// alternative to the pruned pseudo sort that Sec. II-A also describes): keys
-// (metric bits, lane) in the same strict order as candidate_rank, lanes
-// without a candidate last; only the stages that separate the L smallest keys
-// from the rest are run (survivors keep the candidate order, so the order
-// among them is not needed).
+enum : int { kRankCount = 0, kRankNetwork = 1, kRankThreshold = 2 };
 
-// The keys of lane and of lane ^ J, all in VALU: data-parallel-primitive
-// moves inside a row of 16 lanes for J <= 8 (J = 1, 2: one quad permute;
-// J = 4: half-row mirror, then quad reversal; J = 8: row mirror, then
-// half-row mirror), giving (own, partner); for J = 16, 32 the gfx950 row
-// swaps, which exchange the upper rows of their first operand with the lower
-// rows of the second -- with the key in both, every lane ends up holding its
-// own key and its partner's, in an order that depends on the lane, which a
-// compare-exchange does not need to know.
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_mov(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, false);
 }
 
+// the value of lane ^ J, all in VALU: data-parallel-primitive moves inside a
+// row of 16 lanes (J = 4: half-row mirror, then quad reversal; J = 8: row
+// rotation by 8)
 template <int J>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
     if constexpr (J == 1) {
@@ -226,75 +229,87 @@ __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
     } else if constexpr (J == 2) {
         return dpp_mov<0x4E>(v);  // quad_perm [2,3,0,1]
     } else if constexpr (J == 4) {
-        return dpp_mov<0x1B>(dpp_mov<0x141>(v));  // half mirror, quad_perm [3,2,1,0]
+        return dpp_mov<0x1B>(dpp_mov<0x141>(v));
     } else {
         static_assert(J == 8, "distance");
-        return dpp_mov<0x141>(dpp_mov<0x140>(v));  // row mirror, half mirror
+        return dpp_mov<0x128>(v);  // row_ror:8
     }
 }
 
-template <int J>
-__device__ __forceinline__ void key_pair(uint32_t lo, uint32_t hi, uint64_t& a, uint64_t& b) {
-    if constexpr (J <= 8) {
-        a = ((uint64_t)hi << 32) | lo;
-        b = ((uint64_t)lane_xor<J>(hi) << 32) | lane_xor<J>(lo);
-    } else if constexpr (J == 16) {
-        const auto rl = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-        const auto rh = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-        a = ((uint64_t)rh[0] << 32) | rl[0];
-        b = ((uint64_t)rh[1] << 32) | rl[1];
-    } else {
-        static_assert(J == 32, "distance");
-        const auto rl = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-        const auto rh = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-        a = ((uint64_t)rh[0] << 32) | rl[0];
-        b = ((uint64_t)rh[1] << 32) | rl[1];
-    }
+// the value of the mirrored lane of each group of 2^M lanes, M <= 4
+template <int M>
+__device__ __forceinline__ uint32_t lane_mirror(uint32_t v) {
+    if constexpr (M == 1) return dpp_mov<0xB1>(v);        // quad_perm [1,0,3,2]
+    else if constexpr (M == 2) return dpp_mov<0x1B>(v);   // quad_perm [3,2,1,0]
+    else if constexpr (M == 3) return dpp_mov<0x141>(v);  // row_half_mirror
+    else return dpp_mov<0x140>(v);                        // row_mirror
 }
 
-// one compare-exchange at distance J while merging runs into sorted runs of
-// K: the lane keeps the smaller key of {a, b} or the larger, by its position
-// (keys are distinct: every one carries its lane)
-template <int K, int J>
-__device__ __forceinline__ void bitonic_cx(uint32_t& lo, uint32_t& hi, int lane) {
-    uint64_t a, b;
-    key_pair<J>(lo, hi, a, b);
-    const bool keep_max = ((lane & K) == 0) != ((lane & J) == 0);
-    const uint64_t r = ((b < a) != keep_max) ? b : a;
-    lo = (uint32_t)r;
-    hi = (uint32_t)(r >> 32);
+__device__ __forceinline__ uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
+__device__ __forceinline__ uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
+// the smaller of a and b where k = 0, the larger where k = ~0 (one median)
+__device__ __forceinline__ uint32_t pick_minmax(uint32_t a, uint32_t b, uint32_t k) {
+    return umax(umin(a, b), umin(umax(a, b), k));
+}
+// ~0 where bit b of the lane is set, else 0
+__device__ __forceinline__ uint32_t lane_bit_mask(int lane, int b) {
+    return (uint32_t)((int32_t)((uint32_t)lane << (31 - b)) >> 31);
 }
 
-// the stages J = K/2 .. 1 that merge bitonic runs into sorted runs of K
-template <int K, int J>
-__device__ __forceinline__ void bitonic_merge(uint32_t& lo, uint32_t& hi, int lane) {
-    bitonic_cx<K, J>(lo, hi, lane);
-    if constexpr (J > 1) bitonic_merge<K, J / 2>(lo, hi, lane);
-}
-
-// every merge from runs of 2 up to sorted runs of K_END, in alternating
-// directions
-template <int K, int K_END>
-__device__ __forceinline__ void bitonic_merge_upto(uint32_t& lo, uint32_t& hi, int lane) {
-    bitonic_merge<K, K / 2>(lo, hi, lane);
-    if constexpr (K < K_END) bitonic_merge_upto<K * 2, K_END>(lo, hi, lane);
-}
-
-// The L smallest keys of lanes 0..2L-1 gathered in lanes 0..L-1, in no
-// particular order (lanes without a candidate carry the largest keys): the
-// bitonic sort's merges up to sorted runs of L, which leave lanes 0..2L-1 one
-// bitonic sequence, then the first compare-exchange of the next merge, at
-// distance L, which puts the smaller key of each pair below -- the sort's
-// remaining stages would only order the halves.  Returns the lane of the
-// candidate whose key this lane now holds (the keys stay a permutation of the
-// lanes' own).
+// The L-th smallest of the 2 L metrics of each frame's L lanes (x0 <= x1 in
+// every lane), in all of them: a bitonic network over the metrics alone.
+// Element 2 l + r of a frame is register r of its lane l; runs are merged in
+// ascending order, the first exchange of each merge being the mirror of the
+// run (so no lane sorts the other way round), up to two sorted runs of L;
+// the smaller ones of the pairs (i, 2 L - 1 - i) are then the L smallest, and
+// their largest is the answer.  Every exchange is one lane move and one median
+// per register: about 60 VALU instructions for L = 32 and 25 for L = 8,
+// whatever the number of frames, where a 64-bit (metric, lane) network took
+// 16 stages of seven for one frame.
 template <int L>
-__device__ __forceinline__ int bitonic_partition(float met, int ncand, int lane) {
-    uint32_t hi = lane < ncand ? __float_as_uint(met) : 0xFFFFFFFFu;
-    uint32_t lo = (uint32_t)lane;
-    bitonic_merge_upto<2, L>(lo, hi, lane);
-    bitonic_cx<2 * L, L>(lo, hi, lane);
-    return (int)(lo & 63u);
+__device__ __forceinline__ uint32_t lth_smallest(uint32_t x0, uint32_t x1, int lane) {
+    constexpr int LOGL = ctz_c(L);
+    static_for<1, (LOGL > 0 ? LOGL : 1)>([&](auto MC) {
+        constexpr int m = decltype(MC)::value;  // merge into runs of 2^m lanes
+        {
+            const uint32_t k = lane_bit_mask(lane, m - 1);
+            const uint32_t p0 = lane_mirror<m>(x0), p1 = lane_mirror<m>(x1);
+            x0 = pick_minmax(x0, p1, k);
+            x1 = pick_minmax(x1, p0, k);
+        }
+        static_for<0, m - 1>([&](auto JC) {
+            constexpr int j = m - 2 - decltype(JC)::value;  // lane distance 2^j
+            const uint32_t k = lane_bit_mask(lane, j);
+            const uint32_t p0 = lane_xor<(1 << j)>(x0), p1 = lane_xor<(1 << j)>(x1);
+            x0 = pick_minmax(x0, p0, k);
+            x1 = pick_minmax(x1, p1, k);
+        });
+        const uint32_t lo = umin(x0, x1), hi = umax(x0, x1);
+        x0 = lo;
+        x1 = hi;
+    });
+    if constexpr (LOGL == 0) {
+        return x0;
+    } else {
+        uint32_t p0, p1;
+        if constexpr (LOGL == 5) {
+            // the mirror of 32 lanes: the row mirror of the other row
+            const auto r0 = __builtin_amdgcn_permlane16_swap(lane_mirror<4>(x0), lane_mirror<4>(x0), false, false);
+            const auto r1 = __builtin_amdgcn_permlane16_swap(lane_mirror<4>(x1), lane_mirror<4>(x1), false, false);
+            p0 = (lane & 16) ? r0[0] : r0[1];
+            p1 = (lane & 16) ? r1[0] : r1[1];
+        } else {
+            p0 = lane_mirror<LOGL>(x0);
+            p1 = lane_mirror<LOGL>(x1);
+        }
+        uint32_t v = umax(umin(x0, p1), umin(x1, p0));
+        // a lane and its mirror hold the same pairs, so half the lanes do
+        if constexpr (LOGL >= 5) v = umax(v, lane_mirror<4>(v));
+        if constexpr (LOGL >= 4) v = umax(v, lane_mirror<3>(v));
+        if constexpr (LOGL >= 3) v = umax(v, lane_xor<2>(v));
+        if constexpr (LOGL >= 2) v = umax(v, lane_xor<1>(v));
+        return v;
+    }
 }
 
 // set bits of a wavefront mask, counted in two 32-bit halves (a uniform
@@ -308,75 +323,126 @@ __device__ __forceinline__ int mask_below(uint64_t m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Threshold selection: whether this lane's candidate is among the L smallest
-// of the ncand > L candidates under (metric, lane).  The L-th smallest metric
-// tau is found bit by bit from the top (metrics are non-negative, so their
-// bit patterns order them): the largest value with fewer than L metrics
-// below it.  Candidates below tau survive, and of those equal to tau the
-// lowest lanes, as many as are still missing.  One compare per bit in VALU;
-// the counts are scalar.
+// the lanes of this lane's frame
 template <int L>
-__device__ __forceinline__ bool threshold_keep(float met, int ncand, int lane) {
-    const uint32_t key = lane < ncand ? __float_as_uint(met) : 0xFFFFFFFFu;
-    uint32_t tau = 0u;
-#pragma unroll
-    for (int b = 30; b >= 0; --b) {
-        const uint32_t trial = tau | (1u << b);
-        tau = mask_count(__ballot(key < trial)) < (uint32_t)L ? trial : tau;
-    }
-    const int need = L - (int)mask_count(__ballot(key < tau));
-    const uint64_t eq = __ballot(key == tau);
-    return key < tau || (key == tau && mask_below(eq) < need);
+__device__ __forceinline__ uint64_t frame_lanes(int lane) {
+    return ((1ull << L) - 1ull) << (lane & ~(L - 1));
 }
 
-// ranking of the candidates: the pruned pseudo sort (each candidate counts
-// those before it), a bitonic sort, or threshold selection
-enum : int { kRankCount = 0, kRankBitonic = 1, kRankThreshold = 2 };
-
-// The survivors of one branching bit.  Lane c holds candidate c (parent
-// c >> 1 of the list, bit c & 1) with metric met, c < ncand.  Which
-// candidates survive follows the strict order (metric, parent, bit); the
-// survivors keep the candidate order, so the new list's slot s holds the s-th
-// surviving candidate.  Returns, for lane s, the lane of that candidate
-// (lanes past the new list size get a discarded candidate, whose state no one
-// reads).
-template <int L, int RANK>
-__device__ __forceinline__ int select_survivors(lds_ptr<uint32_t> mets, float met, int ncand, int lane) {
-    if (ncand <= L) return lane;  // every candidate survives in place
-    bool keep;
-    if constexpr (RANK == kRankCount) {
-        keep = lane < ncand && candidate_rank<L>(mets, ncand, met, lane) < L;
-    } else if constexpr (RANK == kRankBitonic) {
-        // lanes 0..L-1 hold the L smallest candidates and tell them so
-        const int c = bitonic_partition<L>(met, ncand, lane);
-        keep = __builtin_amdgcn_ds_permute(c << 2, lane < L ? 1 : 0) != 0;
-    } else {
-        keep = threshold_keep<L>(met, ncand, lane);
+// Threshold selection of the same value: found bit by bit from the top as the
+// largest value with fewer than L metrics of the frame below it.
+template <int L>
+__device__ __forceinline__ uint32_t lth_smallest_by_bits(uint32_t kh, uint32_t kf, bool alive, int lane) {
+    const uint64_t mine = frame_lanes<L>(lane);
+    uint32_t tau = 0u;
+    for (int b = 30; b >= 0; --b) {
+        const uint32_t trial = tau | (1u << b);
+        const uint64_t h = __ballot(alive && kh < trial), f = __ballot(alive && kf < trial);
+        tau = mask_count(h & mine) + mask_count(f & mine) < (uint32_t)L ? trial : tau;
     }
-    // exactly L survivors: they go to slots 0..L-1 in lane order, the others
-    // to L..63, so the push below has distinct destinations
-    const uint64_t m = __ballot(keep);
-    const int dest = keep ? mask_below(m) : L + mask_below(~m);
-    return __builtin_amdgcn_ds_permute(dest << 2, lane);
+    return tau;
+}
+
+// Which of this lane's candidates are among the frame's L smallest under
+// (metric, parent, bit), given the L-th smallest metric tau: all below it, and
+// of those equal to it the first in candidate order, as many as are missing.
+template <int L>
+__device__ __forceinline__ void keep_ties(uint32_t kh, uint32_t kf, uint32_t tau, bool hard1, bool alive, int lane,
+                                          bool& keep_h, bool& keep_f) {
+    const uint64_t mine = frame_lanes<L>(lane);
+    const bool lt_h = alive && kh < tau, lt_f = alive && kf < tau;
+    const bool eq_h = alive && kh == tau, eq_f = alive && kf == tau;
+    const uint64_t qh = __ballot(eq_h) & mine, qf = __ballot(eq_f) & mine;
+    const int need = L - (int)(mask_count(__ballot(lt_h) & mine) + mask_count(__ballot(lt_f) & mine));
+    const int before = mask_below(qh) + mask_below(qf);
+    keep_h = lt_h || (eq_h && before + (hard1 && eq_f ? 1 : 0) < need);
+    keep_f = lt_f || (eq_f && before + (!hard1 && eq_h ? 1 : 0) < need);
+}
+
+// The pruned pseudo sort: each candidate counts the frame's candidates before
+// it.  The metrics go through LDS once, candidate by candidate.
+template <int L>
+__device__ __forceinline__ void keep_by_count(lds_ptr<u32x2> cand, uint32_t kh, uint32_t kf, bool hard1, bool alive,
+                                              int lane, bool& keep_h, bool& keep_f) {
+    const uint32_t k0 = hard1 ? kf : kh, k1 = hard1 ? kh : kf;
+    if (alive) cand[lane] = u32x2{k0, k1};
+    wave_mem_order();
+    const int first = lane & ~(L - 1), pl = lane & (L - 1);
+    int r0 = 0, r1 = 0;
+    if (alive) {
+#pragma unroll 4
+        for (int i = 0; i < L; ++i) {
+            const u32x2 v = cand[first + i];
+            r0 += (v.x < k0 || (v.x == k0 && i < pl)) ? 1 : 0;
+            r0 += (v.y < k0 || (v.y == k0 && i < pl)) ? 1 : 0;
+            r1 += (v.x < k1 || (v.x == k1 && i <= pl)) ? 1 : 0;
+            r1 += (v.y < k1 || (v.y == k1 && i < pl)) ? 1 : 0;
+        }
+    }
+    wave_mem_order();
+    const bool keep0 = alive && r0 < L, keep1 = alive && r1 < L;
+    keep_h = hard1 ? keep1 : keep0;
+    keep_f = hard1 ? keep0 : keep1;
+}
+
+// The survivors of one branching bit of frames with full lists (nf frames).
+// They keep the candidate order, so a survivor goes to the slot with as many
+// survivors before it; frames before this one hold L each, so the count over
+// the wavefront is the lane.  Returns, for this lane's new path, (parent lane
+// << 1 | bit) and the metric; lanes without a path get some valid lane.
+template <int L, int RANK>
+__device__ __forceinline__ uint32_t select_survivors(lds_ptr<u32x2> surv, float lam0, float& PM, int nf, bool alive,
+                                                     int lane) {
+    const bool hard1 = lam0 < 0.0f;
+    const uint32_t kh = __float_as_uint(PM), kf = __float_as_uint(PM + fabsf(lam0));
+    bool keep_h, keep_f;
+    if constexpr (RANK == kRankCount) {
+        keep_by_count<L>(surv, kh, kf, hard1, alive, lane, keep_h, keep_f);
+    } else {
+        const uint32_t tau = RANK == kRankNetwork ? lth_smallest<L>(kh, kf, lane)
+                                                  : lth_smallest_by_bits<L>(kh, kf, alive, lane);
+        keep_h = alive && kh <= tau;
+        keep_f = alive && kf <= tau;
+        // every frame keeps at least L this way; more only where metrics tie
+        if (mask_count(__ballot(keep_h)) + mask_count(__ballot(keep_f)) != (uint32_t)(L * nf))
+            keep_ties<L>(kh, kf, tau, hard1, alive, lane, keep_h, keep_f);
+    }
+    const bool keep0 = hard1 ? keep_f : keep_h, keep1 = hard1 ? keep_h : keep_f;
+    const int d0 = mask_below(__ballot(keep_h)) + mask_below(__ballot(keep_f));
+    if (keep0) surv[d0 & 63] = u32x2{(uint32_t)lane << 1, hard1 ? kf : kh};
+    if (keep1) surv[(d0 + (keep0 ? 1 : 0)) & 63] = u32x2{((uint32_t)lane << 1) | 1u, hard1 ? kh : kf};
+    wave_mem_order();
+    u32x2 r{0u, 0u};
+    if (alive) r = surv[lane];
+    wave_mem_order();
+    PM = __uint_as_float(r.y);
+    return r.x;
 }
 
 struct Layout {
-    int gl;      // LLR levels < gl in LDS (gl = min(n, 6)), the others in the workgroup's global slice
-    int sl;      // LDS floats per slot: levels BL..gl-1, level d at offset 2^d - 2^BL, padded
-    int pw;      // partial-sum words per slot (levels >= 5)
-    int tg;      // 1: the trace lives in the global slice and is read back in chunks
+    int slots;   // path slots of a workgroup: L times the most frames it decodes at once, a power of two
+    int fpw;     // slots / L
+    int target;  // wavefronts to fill before one takes a second frame
+    int soff;    // LDS byte offset of the survivor list
+    int tg;      // 1: the trace lives in the global slice
     int64_t gbytes;  // bytes of the global slice per workgroup
     int64_t toff;    // byte offset of the trace inside the slice
-    int tboff;       // byte offset of the LDS trace (the traceback's block chain sits below it)
+    int tboff;       // byte offset of the LDS trace (the traceback's block words sit below it)
     int nblk;        // blocks of the largest block length the layout holds (trace rows)
     int64_t u_stride;  // u_hat row stride of a ragged batch
 };
 
+// Active path a of the wavefront's frames (lists of 2^lg paths, L slots a frame)
+template <int L>
+__device__ __forceinline__ int slot_of(int a, int lg) {
+    return ((a >> lg) << ctz_c(L)) | (a & ((1 << lg) - 1));
+}
+
 // Levels top..5 of every path at a block start (top = the highest level whose
 // index bit changed).  Level 5 of a path is 32 items, taken as eight groups of
-// four; group g of path p is one chain, run by lane 8 (p mod 8) + g as its
-// chain p / 8.  A chain's items of level d are the items e + 32 k of its group
-// e, and each depends only on the same chain's items of level d + 1, so a
+// four; group g of active path a is one chain, run by lane 8 (a mod 8) + g as
+// its chain a / 8.  A chain's items of level d are the items e + 32 k of its
+// group e, and each depends only on the same chain's items of level d + 1, so a
 // lane computes its chains from level top + 1 alone, in registers: the level
 // top items are the leaves, taken in bit-reversed order so that each pair of
 // consecutive results at one level combines at once into the level below
@@ -387,26 +453,58 @@ struct Layout {
 // leaves in flight (two where the stack is deep, N >= 2048, to stay within the
 // register budget).  Every load is issued unconditionally (a load past the
 // stream's end repeats the last leaf's), so the waits for one leaf's data
-// leave the later leaves' loads outstanding.  With L >= 8 the chains of
-// paths past the list's end (slots below 8 * chains <= L) store too: those
-// slots' levels top..5 are rewritten before any path reads them.  H = top - 5.
+// leave the later leaves' loads outstanding.  Chains past the last path repeat
+// the last path's, with the same values to the same places, so no store waits
+// on a lane mask.  H = top - 5.
+//
+// Where level top + 1 comes from (SRC): the slots' rows of the slice, or, for
+// the top levels, the frame's channel row: SRC = 0 itself (top = n - 1), 1 or 2
+// with the one or two levels between computed again (top = n - 2, n - 3).
+enum : int { kSrcSlice = 3 };
+
+// 16 bytes of a channel row, which may start at any float (vector loads take
+// 4-byte alignment)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int SRC>
 struct Leaf {
-    f32x4 a, b;   // items e and e + 2^top of level top + 1
-    uint32_t w;   // partial-sum bits of the four items (g at the top level)
+    static constexpr int kVecs = SRC == kSrcSlice ? 2 : 2 << SRC;
+    f32x4 v[kVecs];                          // SRC < 3: channel items e + i 2^top, i ascending; else level top + 1
+    uint32_t w;                              // partial-sum bits of level top
+    uint32_t w1[SRC == 1 ? 2 : SRC == 2 ? 2 : 1];  // of level top + 1 (SRC 1, 2)
+    uint32_t w2[SRC == 2 ? 4 : 1];           // of level top + 2 (SRC 2)
 };
 
-template <int L, int H, bool CHAN1>
-__device__ __forceinline__ void block_levels(const int act, const int lane, const int N, const int SL, const int PW,
+// f (psum = false) or g of two groups of four items
+__device__ __forceinline__ f32x4 fg4(const f32x4& a, const f32x4& b, uint32_t w, bool psum) {
+    f32x4 v;
+    if (psum) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = g_bit(a[i], b[i], w, i);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = f_ms(a[i], b[i]);
+    }
+    return v;
+}
+
+// psum, psum1, psum2: whether levels top, top + 1, top + 2 are g of their
+// source here (the block is in the right half of the level above).  myslots: the
+// slots this lane's path reads -- byte 0 LLR level top + 1, bytes 1, 2, 3
+// partial sums of levels top, top + 1, top + 2; a chain takes them from its
+// path's lane when it is begun (all chains' at once would take eight registers
+// here, of which there are none to spare).
+template <int L, int H, int SRC>
+__device__ __forceinline__ void block_levels(const int paths, const int lg, const int lane, const int rlog,
                                              const lds_ptr<float> slam, const glb_ptr<float> glam,
-                                             const glb_ptr<const float> gsrc, const int gstride,
-                                             const lds_ptr<uint32_t> psw, const bool psum, const uint32_t srcpack,
-                                             const uint32_t psspack) {
+                                             const uint64_t chan, const lds_ptr<uint32_t> psw, const bool psum,
+                                             const bool psum1, const bool psum2, const bool deep, const int myslots) {
     constexpr int TOP = H + 5;
-    constexpr int M = 1 << H;             // leaves per chain
-    constexpr int P = H <= 4 ? 4 : 2;     // leaves in flight
-    constexpr int LP = P == 4 ? 2 : 1;    // log2 P
+    constexpr int M = 1 << H;                                  // leaves per chain
+    constexpr int P = SRC == 2 ? 1 : (SRC == 1 || H > 4) ? 2 : 4;  // leaves in flight
+    constexpr int LP = P == 4 ? 2 : P == 2 ? 1 : 0;            // log2 P
     constexpr int SZT = 1 << TOP;
-    const int C = (act + 7) >> 3;         // chains per lane
+    const int C = (paths + 7) >> 3;       // chains per lane
     const int S = C << H;                 // leaves per lane
     // the lane index made opaque here, so that the lane offsets below are
     // computed at each block start instead of being hoisted out of the frame
@@ -414,57 +512,90 @@ __device__ __forceinline__ void block_levels(const int act, const int lane, cons
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int e4 = (ln & 7) << 2;         // the group's first item
+    const glb_ptr<const char> gsrc = (glb_ptr<const char>)(glam + (2 << TOP));
     auto leaf_k = [](int m) -> int { return H == 0 ? 0 : (int)(__builtin_bitreverse32((uint32_t)m) >> (32 - H)); };
-    auto load = [&](int st) -> Leaf {
-        Leaf o;
-        const int c = st >> H;
+    auto slot_c = [&](int c) -> int {
+        const int a = (ln >> 3) + 8 * c;
+        return slot_of<L>(a < paths ? a : paths - 1, lg);
+    };
+    // word k of partial-sum level D of a slot
+    auto ps_word = [&](auto DC, int slot, int k) -> uint32_t {
+        constexpr int d = decltype(DC)::value;
+        if constexpr (d < kPsLds) return psw[slot * kPsWords + ps_off(d, 0) + k];
+        else return ((glb_ptr<uint32_t>)glam)[(uint32_t)((slot << rlog) + ps_off(d, rlog) + k)];
+    };
+    auto slots_of_chain = [&](int c) -> uint32_t { return (uint32_t)__shfl(myslots, slot_c(c), 64); };
+    // leaf st of the lane, whose chain's slots are sv
+    auto load = [&](int st, uint32_t sv) {
+        Leaf<SRC> o;
         const int k = leaf_k(st & (M - 1));
         const int it = e4 + 32 * k;
-        if constexpr (!CHAN1) {
-            // level top + 1 of the chain's source slot (stride 0: the channel
-            // row), 32-bit byte offsets from the uniform base
-            const int src = (int)((srcpack >> (8 * c)) & 0xFFu);
-            const uint32_t off = (uint32_t)(src * gstride + it) * 4u;
-            o.a = *(glb_ptr<const f32x4>)((glb_ptr<const char>)gsrc + off);
-            o.b = *(glb_ptr<const f32x4>)((glb_ptr<const char>)gsrc + off + 4u * SZT);
+        if constexpr (SRC == kSrcSlice) {
+            // level top + 1 of the chain's source slot, 32-bit byte offsets
+            // from the uniform base
+            const uint32_t off = (uint32_t)((int)((sv & 0xFFu) << rlog) + it) * 4u;
+            o.v[0] = *(glb_ptr<const f32x4>)(gsrc + off);
+            o.v[1] = *(glb_ptr<const f32x4>)(gsrc + off + 4u * SZT);
         } else {
-            const glb_ptr<const float> q = gsrc + it;
-            o.a = f32x4{q[0], q[1], q[2], q[3]};
-            o.b = f32x4{q[SZT], q[SZT + 1], q[SZT + 2], q[SZT + 3]};
+            // the channel row of the chain's frame
+            const glb_ptr<const float> q = (glb_ptr<const float>)shfl64(chan, slot_c(st >> H)) + it;
+#pragma unroll
+            for (int i = 0; i < Leaf<SRC>::kVecs; ++i) o.v[i] = *(glb_ptr<const f32x4_any>)(q + i * SZT);
         }
         // the partial sums (read also where they are not used: the slot
         // pointers of the first block are valid)
-        const int pss = (int)((psspack >> (8 * c)) & 0xFFu);
-        o.w = psw[pss * PW + ps_off(TOP) + k] >> e4;
+        o.w = ps_word(std::integral_constant<int, TOP>{}, (int)((sv >> 8) & 0xFFu), k) >> e4;
+        if constexpr (SRC == 1 || SRC == 2) {
+            const int s1 = (int)((sv >> 16) & 0xFFu);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                o.w1[i] = ps_word(std::integral_constant<int, TOP + 1>{}, s1, k + i * (SZT / 32)) >> e4;
+        }
+        if constexpr (SRC == 2) {
+            const int s2 = (int)(sv >> 24);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                o.w2[i] = ps_word(std::integral_constant<int, TOP + 2>{}, s2, k + i * (SZT / 32)) >> e4;
+        }
         return o;
     };
-    Leaf ring[P];
+    Leaf<SRC> ring[P];
     f32x4 stk[H > 0 ? H : 1];
     // leaf s0 + q, s0 a multiple of P: the chain and the low bits of the leaf's
     // index in it are known at compile time where the chain is at least P long
-    auto step = [&](const int s0, auto QC, Leaf& slotq) {
+    // (sv_next: the slots of the chain of leaf s0 + P, where chains are at least P long)
+    auto step = [&](const int s0, auto QC, Leaf<SRC>& slotq, const uint32_t sv_next) {
         constexpr int q = decltype(QC)::value;
-        const Leaf x = slotq;
-        slotq = load(s0 + q + P < S ? s0 + q + P : S - 1);
+        // the levels that are computed again, before the next load takes the
+        // registers of their sources
+        f32x4 a, b;
+        if constexpr (SRC == kSrcSlice || SRC == 0) {
+            a = slotq.v[0];
+            b = slotq.v[1];
+        } else if constexpr (SRC == 1) {
+            a = fg4(slotq.v[0], slotq.v[2], slotq.w1[0], psum1);
+            b = fg4(slotq.v[1], slotq.v[3], slotq.w1[1], psum1);
+        } else {
+            a = fg4(fg4(slotq.v[0], slotq.v[4], slotq.w2[0], psum2), fg4(slotq.v[2], slotq.v[6], slotq.w2[2], psum2),
+                    slotq.w1[0], psum1);
+            b = fg4(fg4(slotq.v[1], slotq.v[5], slotq.w2[1], psum2), fg4(slotq.v[3], slotq.v[7], slotq.w2[3], psum2),
+                    slotq.w1[1], psum1);
+        }
+        const uint32_t wt = slotq.w;
+        const int nx = s0 + q + P < S ? s0 + q + P : S - 1;
+        slotq = load(nx, M >= P ? sv_next : slots_of_chain(nx >> H));
         const int m = M >= P ? ((s0 & (M - 1)) | q) : (q & (M - 1));
         const int c = M >= P ? (s0 >> H) : ((s0 >> H) + (q >> H));
         const int k = leaf_k(m);
-        const int slot = (ln >> 3) + 8 * c;
-        const bool live = L >= 8 || slot < act;
+        const int slot = slot_c(c);
         auto put = [&](auto DC, int kk, const f32x4& v) {
             constexpr int d = decltype(DC)::value;
-            if (!live) return;
-            if constexpr (d == 5) *(lds_ptr<f32x4>)(slam + slot * SL + e4 + 32 * kk) = v;
-            else *(glb_ptr<f32x4>)((glb_ptr<char>)glam + (uint32_t)(slot * N + (1 << d) + e4 + 32 * kk) * 4u) = v;
+            // with the channel as the source n = TOP + 1 + SRC
+            if constexpr (d == 5) *(lds_ptr<f32x4>)(slam + slot * kSlotFloats + (e4 ^ (swz(slot) << 2))) = v;
+            else if (SRC == kSrcSlice || kept(TOP + 1 + SRC, d, deep))
+                *(glb_ptr<f32x4>)((glb_ptr<char>)glam + (uint32_t)((slot << rlog) + (1 << d) + e4 + 32 * kk) * 4u) = v;
         };
-        f32x4 v;
-        if (psum) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = g_bit(x.a[i], x.b[i], x.w, i);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = f_ms(x.a[i], x.b[i]);
-        }
+        f32x4 v = fg4(a, b, wt, psum);
         put(std::integral_constant<int, TOP>{}, k, v);
         bool go = true;
         static_for<0, H>([&](auto LC) {
@@ -473,10 +604,7 @@ __device__ __forceinline__ void block_levels(const int act, const int lane, cons
             const bool one = (M >= P && l < LP) ? ((q >> l) & 1) != 0 : ((m >> l) & 1) != 0;
             if (go) {
                 if (one) {
-                    f32x4 u;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) u[i] = f_ms(stk[l][i], v[i]);
-                    v = u;
+                    v = fg4(stk[l], v, 0u, false);
                     put(std::integral_constant<int, TOP - l - 1>{}, k & ((M >> (l + 1)) - 1), v);
                 } else {
                     stk[l] = v;
@@ -485,59 +613,105 @@ __device__ __forceinline__ void block_levels(const int act, const int lane, cons
             }
         });
     };
+    {
+        const uint32_t sv0 = slots_of_chain(0);
 #pragma unroll
-    for (int q = 0; q < P; ++q) ring[q] = load(q < S ? q : S - 1);
-    if (S % P == 0) {
-        for (int s0 = 0; s0 < S; s0 += P)
-            static_for<0, P>([&](auto QC) { step(s0, QC, ring[decltype(QC)::value]); });
+        for (int q = 0; q < P; ++q) {
+            const int st = q < S ? q : S - 1;
+            ring[q] = load(st, M >= P ? sv0 : slots_of_chain(st >> H));
+        }
+    }
+    if (M >= P || S % P == 0) {
+        for (int s0 = 0; s0 < S; s0 += P) {
+            const uint32_t sv = M >= P ? slots_of_chain((s0 + P < S ? s0 + P : S - 1) >> H) : 0u;
+            static_for<0, P>([&](auto QC) { step(s0, QC, ring[decltype(QC)::value], sv); });
+        }
     } else {
-        // a stream not a multiple of P (fewer than 25 paths, lowest levels)
+        // a stream not a multiple of P (few paths, lowest levels)
         for (int s0 = 0; s0 < S; s0 += P)
             static_for<0, P>([&](auto QC) {
-                if (s0 + decltype(QC)::value < S) step(s0, QC, ring[decltype(QC)::value]);
+                if (s0 + decltype(QC)::value < S) step(s0, QC, ring[decltype(QC)::value], 0u);
             });
     }
 }
 
-template <int L, int BL, int RANK = kRankCount>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void scl_kernel(CodeDev code_in, const float* __restrict__ llr,
-                                                 const int32_t* __restrict__ frame_ids,
-                                                 const int32_t* __restrict__ count_dev, int64_t count_host,
-                                                 uint8_t* __restrict__ u_hat, uint8_t* __restrict__ crc_ok,
-                                                 float* __restrict__ pm_out, unsigned char* __restrict__ glob_all,
-                                                 Layout lay, const MixedIo* __restrict__ mio) {
+// the decided-bit words of the trace, in LDS or in the global slice
+struct TraceRows {
+    lds_ptr<uint32_t> l;
+    glb_ptr<uint32_t> g;
+    bool glob;
+    __device__ __forceinline__ uint32_t get(int i) const { return glob ? g[i] : l[i]; }
+    __device__ __forceinline__ void set(int i, uint32_t v) const {
+        if (glob) g[i] = v;
+        else l[i] = v;
+    }
+};
+
+template <int L, int BL, int RANK>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void scl_kernel(
+    CodeDev code_in, const float* __restrict__ llr, SclWork work, uint8_t* __restrict__ u_hat,
+    uint8_t* __restrict__ crc_ok, float* __restrict__ pm_out, unsigned char* __restrict__ glob_all, Layout lay,
+    const MixedIo* __restrict__ mio) {
     constexpr int BS = 1 << BL;  // bits per block
+    constexpr int LOGL = ctz_c(L);
     extern __shared__ __attribute__((aligned(16))) unsigned char sm[];
     const int lane = lid_x();
-    const int gl = lay.gl, SL = lay.sl, PW = lay.pw;
+    const int sub = lane >> LOGL, pl = lane & (L - 1);  // the lane's frame and path
+    const int SLOTS = lay.slots;
 
-    const lds_ptr<float> slam = as_lds<float>(sm);                          // [L][SL]
-    const lds_ptr<uint32_t> psw = (lds_ptr<uint32_t>)(slam + L * SL);       // [L][PW]
-    const lds_ptr<uint32_t> mets = psw + L * PW;                            // [64]
-    const lds_ptr<int> chain = as_lds<int>(sm);                             // [nblk], reuses the LLR area at the end
+    const lds_ptr<float> slam = as_lds<float>(sm);                          // [slots][32]
+    const lds_ptr<uint32_t> psw = (lds_ptr<uint32_t>)(slam + SLOTS * kSlotFloats);   // [slots][3]
+    const lds_ptr<u32x2> surv = as_lds<u32x2>(sm + lay.soff);               // [slots]
+    const lds_ptr<uint32_t> words = as_lds<uint32_t>(sm);                   // [fpw][nblk], reuses the LLR area at the end
 
     unsigned char* gbase = glob_all ? glob_all + (size_t)gid_x() * (size_t)lay.gbytes : nullptr;
-    const glb_ptr<float> glam = as_glb<float>(gbase);         // [L][N], levels >= gl
+    const glb_ptr<float> glam = as_glb<float>(gbase);         // [slots][2^rlog]
     // the trace, per block and slot: the block's decided bits (bit r = bit r of
     // the block) and the slot the path held at the block start; in LDS or, when
     // tg, in the global slice
-    const size_t tra_off = (size_t)lay.nblk * L * sizeof(uint32_t);
-    const lds_ptr<uint32_t> tru_l = as_lds<uint32_t>(sm + lay.tboff);   // [nblk][L]
-    const lds_ptr<uint8_t> tra_l = as_lds<uint8_t>(sm + lay.tboff + tra_off);
-    const glb_ptr<uint32_t> tru_g = as_glb<uint32_t>(gbase + lay.toff);
-    const glb_ptr<uint8_t> tra_g = as_glb<uint8_t>(gbase + lay.toff + tra_off);
+    const size_t tra_off = (size_t)lay.nblk * SLOTS * sizeof(uint32_t);
     const bool tg = lay.tg != 0;
+    const TraceRows tru{as_lds<uint32_t>(sm + lay.tboff), as_glb<uint32_t>(gbase + lay.toff), tg};  // [nblk][slots]
+    const lds_ptr<uint8_t> tra_l = as_lds<uint8_t>(sm + lay.tboff + tra_off);
+    const glb_ptr<uint8_t> tra_g = as_glb<uint8_t>(gbase + lay.toff + tra_off);
 
-    const int64_t count = count_dev ? (int64_t)(*count_dev) : count_host;
     const float* const llr_base = mio ? mio->llr : llr;
     const int64_t* const row_off = mio ? mio->off : nullptr;
-    for (int64_t q = gid_x(); q < count; q += num_groups_x()) {
-        const int64_t f = frame_ids ? (int64_t)uniform_int(frame_ids[q]) : q;
-        // the frame's code (several codes in one launch: the layout holds the
-        // largest; level offsets inside a slot do not depend on n)
+    auto queue_len = [&](int k) -> int64_t {
+        return work.count_dev ? (int64_t)work.count_dev[work.code_ids[k]] : work.count_host;
+    };
+    // frames per wavefront: one as long as that fills `target` wavefronts
+    int64_t all = 0;
+    for (int k = 0; k < work.n_queues; ++k) all += queue_len(k);
+    const int64_t want = (all + lay.target - 1) / lay.target;
+    const int nf_max = uniform_int((int)(want < 1 ? 1 : want > lay.fpw ? lay.fpw : want));
+    const bool deep = nf_max > 1;
+
+    for (int64_t unit = gid_x();; unit += num_groups_x()) {
+        // the unit's queue and its first entry there
+        int64_t q0 = unit, len = 0;
+        int k = 0;
+        for (; k < work.n_queues; ++k) {
+            len = queue_len(k);
+            const int64_t units = (len + nf_max - 1) / nf_max;
+            if (q0 < units) break;
+            q0 -= units;
+        }
+        if (k == work.n_queues) break;
+        q0 *= nf_max;
+        const int code_id = uniform_int(work.code_ids[k]);
+        const int nf = uniform_int((int)(len - q0 < nf_max ? len - q0 : nf_max));
+        const int32_t* const ids = work.ids ? work.ids + code_id * work.queue_stride : nullptr;
+        // the frame of a lane (lanes without one: the last frame's)
+        auto frame_of = [&](int s) -> int64_t {
+            const int64_t q = q0 + (s < nf ? s : nf - 1);
+            return ids ? (int64_t)ids[q] : q;
+        };
         CodeDev code = code_in;
         if (mio && mio->codes) {
-            code = mio->codes[uniform_int(mio->code_of[f])];
+            // (several codes in one launch: the layout holds the largest;
+            // level offsets inside a slot do not depend on n)
+            code = mio->codes[code_id];
             code.frozen_bits = uniform_ptr(code.frozen_bits);
             code.da_bits = uniform_ptr(code.da_bits);
             code.syn = uniform_ptr(code.syn);
@@ -545,7 +719,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
             code.N = uniform_int(code.N);
         }
         const int n = code.n, N = code.N;
-        // the frame's frozen and decision-aided words, lane w holding word w
+        const int rlog = row_log(n, deep);
+        // the code's frozen and decision-aided words, lane w holding word w
         // (and word 64 + w): a block reads its word from the lanes
         const int nw = N >= 32 ? N >> 5 : 1;
         const glb_ptr<const uint32_t> fzb = as_glb<const uint32_t>(code.frozen_bits);
@@ -555,24 +730,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
         const glb_ptr<const uint32_t> synp = as_glb<const uint32_t>(code.syn);
         // rows of frame f: LLRs at row_off[f] (ragged batch) or f * N; u_hat at
         // f * u_stride (ragged batch) or f * N
-        const float* const chan_g = llr_base + (row_off ? row_off[f] : f * N);
-        const glb_ptr<const float> chan = as_glb<const float>(chan_g);
-        const bool chan16 = (reinterpret_cast<uintptr_t>(chan_g) & 15u) == 0;  // 16-byte loads possible
-        const int64_t urow = f * (row_off ? lay.u_stride : (int64_t)N);
+        auto chan_of = [&]() -> const float* {
+            const int64_t f = frame_of(sub);
+            return llr_base + (row_off ? row_off[f] : f * N);
+        };
 
-        int act = 1;
+        int act = 1, lgact = 0;  // paths per list, 2^lgact
         float PM = 0.0f;
         uint32_t SYN = 0u;
-        PtrVec ptrL{0ull};  // slot read at each LLR level >= BL
-        PtrVec ptrP{0ull};  // slot read at each partial-sum level >= 5
+        // slot read at each LLR level >= BL and partial-sum level >= 5 (their
+        // start values are only read by lanes without a path)
+        PtrVec ptrL{0ull};
+        PtrVec ptrP{0ull};
         float lv[32];             // levels 0..BL-1, heap order: level d at [2^d, 2^(d+1))
         uint32_t ps[5];           // partial-sum levels 0..BL-1: bit e of word d
-#pragma unroll
-        for (int e = 0; e < 32; ++e) lv[e] = 0.0f;
-#pragma unroll
-        for (int d = 0; d < 5; ++d) ps[d] = 0u;
         uint32_t ublk = 0u;  // this path's decided bits of the current block
-        int anc = lane;      // the slot this path held at the block start
+        int anc = 0;         // the slot this path held at the block start
 
         for (int j = 0; j < (N >> BL); ++j) {
             const int i0 = j << BL;
@@ -590,47 +763,64 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
             if constexpr (BL == 5) {
                 if (BL < n) {
                     const int top = (j == 0) ? n - 1 : __builtin_ctz((unsigned)i0);
-                    // slots read at level top + 1 and partial sums at level top,
-                    // of each chain's path: byte c for chain c of this lane
-                    const int myp = get_byte(ptrL, top + 1);
-                    const int mypp = get_byte(ptrP, top);
-                    uint32_t srcpack = 0u, psspack = 0u;
-#pragma unroll
-                    for (int c = 0; c < (L + 7) / 8; ++c) {
-                        const int pth = (lane >> 3) + 8 * c;
-                        srcpack |= (uint32_t)__shfl(myp, pth, 64) << (8 * c);
-                        psspack |= (uint32_t)__shfl(mypp, pth, 64) << (8 * c);
-                    }
+                    const int paths = nf << lgact;
+                    // levels between top + 1 and the channel, as far as they
+                    // are computed again (3: level top + 1 is kept)
+                    const int depth = top + 1 == n ? 0 : kept(n, top + 1, deep) ? 3 : n - 1 - top;
+                    const int my = get_byte(ptrL, top + 1) | (get_byte(ptrP, top) << 8) |
+                                   (get_byte(ptrP, top + 1) << 16) | (get_byte(ptrP, top + 2 < 12 ? top + 2 : 12) << 24);
+                    // the block's index bit of level top is set (but at the
+                    // frame's start), those above tell the levels above
                     const bool psum = j != 0;
-                    // level top + 1: the channel row (same for every path) or
-                    // the workgroup's global slice
-                    const bool in_chan = top + 1 == n;
-                    const bool chan1 = in_chan && !chan16;
-                    const glb_ptr<const float> gsrc =
-                        uniform_glb(in_chan ? chan : (glb_ptr<const float>)(glam + (2 << top)));
-                    const int gstride = in_chan ? 0 : N;
+                    const bool psum1 = ((i0 >> (top + 1)) & 1) != 0, psum2 = ((i0 >> (top + 2)) & 1) != 0;
+                    const uint64_t chan = depth <= 2 ? reinterpret_cast<uint64_t>(chan_of()) : 0ull;
                     // the levels above were written by other lanes at earlier
                     // block starts
                     wg_mem_order();
                     synv = synp[i0 + (lane & (BS - 1))];
                     syn_loaded = true;
-#define POLAR_BLOCK_LEVELS(HH)                                                                                   \
-    (chan1 ? block_levels<L, HH, true>(act, lane, N, SL, PW, slam, glam, gsrc, gstride, psw, psum, srcpack, psspack) \
-           : block_levels<L, HH, false>(act, lane, N, SL, PW, slam, glam, gsrc, gstride, psw, psum, srcpack, psspack))
-                    switch (top - BL) {
-                        case 0: POLAR_BLOCK_LEVELS(0); break;
-                        case 1: POLAR_BLOCK_LEVELS(1); break;
-                        case 2: POLAR_BLOCK_LEVELS(2); break;
-                        case 3: POLAR_BLOCK_LEVELS(3); break;
-                        case 4: POLAR_BLOCK_LEVELS(4); break;
-                        case 5: POLAR_BLOCK_LEVELS(5); break;
-                        default: POLAR_BLOCK_LEVELS(6); break;
+#define POLAR_BLOCK_LEVELS(HH, SS) \
+    block_levels<L, HH, SS>(paths, lgact, lane, rlog, slam, glam, chan, psw, psum, psum1, psum2, deep, my)
+                    if (depth == 0) {
+                        switch (top - BL) {
+                            case 0: POLAR_BLOCK_LEVELS(0, 0); break;
+                            case 1: POLAR_BLOCK_LEVELS(1, 0); break;
+                            case 2: POLAR_BLOCK_LEVELS(2, 0); break;
+                            case 3: POLAR_BLOCK_LEVELS(3, 0); break;
+                            case 4: POLAR_BLOCK_LEVELS(4, 0); break;
+                            case 5: POLAR_BLOCK_LEVELS(5, 0); break;
+                            default: POLAR_BLOCK_LEVELS(6, 0); break;
+                        }
+                    } else if (depth == 1) {
+                        switch (top - BL) {
+                            case 0: POLAR_BLOCK_LEVELS(0, 1); break;
+                            case 1: POLAR_BLOCK_LEVELS(1, 1); break;
+                            case 2: POLAR_BLOCK_LEVELS(2, 1); break;
+                            case 3: POLAR_BLOCK_LEVELS(3, 1); break;
+                            case 4: POLAR_BLOCK_LEVELS(4, 1); break;
+                            default: POLAR_BLOCK_LEVELS(5, 1); break;
+                        }
+                    } else if (depth == 2) {
+                        switch (top - BL) {
+                            case 0: POLAR_BLOCK_LEVELS(0, 2); break;
+                            case 1: POLAR_BLOCK_LEVELS(1, 2); break;
+                            case 2: POLAR_BLOCK_LEVELS(2, 2); break;
+                            case 3: POLAR_BLOCK_LEVELS(3, 2); break;
+                            default: POLAR_BLOCK_LEVELS(4, 2); break;
+                        }
+                    } else {
+                        switch (top - BL) {
+                            case 0: POLAR_BLOCK_LEVELS(0, kSrcSlice); break;
+                            case 1: POLAR_BLOCK_LEVELS(1, kSrcSlice); break;
+                            case 2: POLAR_BLOCK_LEVELS(2, kSrcSlice); break;
+                            case 3: POLAR_BLOCK_LEVELS(3, kSrcSlice); break;
+                            default: POLAR_BLOCK_LEVELS(4, kSrcSlice); break;
+                        }
                     }
 #undef POLAR_BLOCK_LEVELS
                     // level 5 (LDS) is read by the block's bits
                     wave_mem_order();
-                    if (lane < act)
-                        for (int d = top; d >= BL; --d) set_byte(ptrL, d, lane);
+                    for (int d = top; d >= BL; --d) set_byte(ptrL, d, lane & (SLOTS - 1));
                 }
             }
             if (!syn_loaded) synv = synp[i0 + (lane & (BS - 1))];
@@ -643,8 +833,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
 #pragma unroll
             for (int d = 0; d < 5; ++d) ps[d] = 0u;
             ublk = 0u;
-            anc = lane;
-            // ---------------- the 2^BL bits of the block, unrolled
+            anc = lane & (SLOTS - 1);
+            // ---------------- the 2^BL bits of the block, unrolled.  Lanes
+            // without a path compute along on whatever they hold; nothing of
+            // theirs is stored or kept
             static_for<0, BS>([&](auto RC) {
                 constexpr int r = decltype(RC)::value;
                 // lowest level whose index bit changed at this bit (BL: block start)
@@ -658,19 +850,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
                 constexpr int tb = (r + 1 < BS) ? ctz_c(~r) : BL;
 
                 // ---- LLR levels min(top, BL-1)..0 of this lane's path
-                if (lane < act) {
+                {
                     float src[32];
                     constexpr int sl_lv = (r == 0) ? BL : top + 1;  // level read
                     if constexpr (sl_lv == BL) {
                         if (BL == n) {
+                            const glb_ptr<const float> chan = as_glb<const float>(chan_of());
 #pragma unroll
                             for (int e = 0; e < BS; ++e) src[e] = chan[e];
                         } else {
-                            const int sl = (r == 0) ? lane : get_byte(ptrL, BL);
-                            const lds_ptr<float> p = slam + sl * SL;
+                            // written by this path's lane of the block start
+                            const lds_ptr<float> p = slam + anc * kSlotFloats;
+                            const int sw = swz(anc);
 #pragma unroll
                             for (int e4 = 0; e4 < BS / 4; ++e4) {
-                                const f32x4 t4 = ((lds_ptr<const f32x4>)p)[e4];
+                                const f32x4 t4 = ((lds_ptr<const f32x4>)p)[e4 ^ sw];
                                 src[4 * e4] = t4.x;
                                 src[4 * e4 + 1] = t4.y;
                                 src[4 * e4 + 2] = t4.z;
@@ -699,33 +893,34 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
                 // ---- decision
                 uint32_t bit = 0;
                 if ((fw >> r) & 1u) {
-                    if (lane < act) PM = PM + (lam0 < 0.0f ? fabsf(lam0) : 0.0f);
+                    PM = PM + (lam0 < 0.0f ? fabsf(lam0) : 0.0f);
                 } else if ((dw >> r) & 1u) {
                     // decision-aided position (Sec. II-A): every path keeps its
                     // hard decision; no branching, no metric change, same slots
-                    if (lane < act) {
-                        bit = lam0 < 0.0f ? 1u : 0u;
-                        SYN ^= bit ? (uint32_t)__builtin_amdgcn_readlane((int)synv, r) : 0u;
-                        ublk |= bit << r;
-                    }
+                    bit = lam0 < 0.0f ? 1u : 0u;
+                    SYN ^= bit ? (uint32_t)__builtin_amdgcn_readlane((int)synv, r) : 0u;
+                    ublk |= bit << r;
                 } else {
-                    const int ncand = 2 * act;
-                    const int p = lane >> 1, b = lane & 1;
-                    const float lp = __shfl(lam0, p, 64);
-                    const float pmp = __shfl(PM, p, 64);
-                    const float pen = (b != (lp < 0.0f ? 1 : 0)) ? fabsf(lp) : 0.0f;
-                    const float met = pmp + pen;
-                    const int nact = ncand < L ? ncand : L;
-                    const int c = select_survivors<L, RANK>(mets, met, ncand, lane);
-                    const int par = c >> 1;
-                    const uint32_t cb = (uint32_t)(c & 1);
+                    uint32_t src;  // parent lane << 1 | bit
+                    if (act == L) {
+                        src = select_survivors<L, RANK>(surv, lam0, PM, nf, sub < nf, lane);
+                    } else {
+                        // the list is not full: every candidate survives in place
+                        const int p = (lane & ~(L - 1)) | (pl >> 1);
+                        const uint32_t b = (uint32_t)pl & 1u;
+                        const float lp = __shfl(lam0, p, 64);
+                        const float pmp = __shfl(PM, p, 64);
+                        PM = pmp + ((b != (lp < 0.0f ? 1u : 0u)) ? fabsf(lp) : 0.0f);
+                        src = ((uint32_t)p << 1) | b;
+                        act *= 2;
+                        lgact += 1;
+                    }
+                    const int par = (int)(src >> 1);
+                    bit = src & 1u;
                     const uint32_t syn_i = (uint32_t)__builtin_amdgcn_readlane((int)synv, r);
-                    // pull the parent's state: metric, syndrome, pointers, live registers
-                    // (lanes past the new list size pull lane 0's state, which no one reads)
-                    PM = __shfl(met, c, 64);
-                    SYN = __shfl(SYN, par, 64) ^ (cb ? syn_i : 0u);
-                    ptrL.w = shfl64(ptrL.w, par);
-                    ptrP.w = shfl64(ptrP.w, par);
+                    // pull the parent's state: syndrome and live registers
+                    // (lanes without a path pull some lane's state, which no one reads)
+                    SYN = __shfl(SYN, par, 64) ^ (bit ? syn_i : 0u);
                     // partial-sum level d is written at the bits r with r mod
                     // 2^(d+1) = 2^d - 1 and read at those with r mod 2^(d+1) in
                     // [2^d, 2^(d+1) - 1] (g at level d, then the fold at the
@@ -743,167 +938,171 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
                         }
                     });
                     anc = __shfl(anc, par, 64);
-                    ublk = __shfl(ublk, par, 64) | (cb << r);
-                    if (lane < nact) bit = cb;
-                    act = nact;
+                    ublk = (r > 0 ? __shfl(ublk, par, 64) : 0u) | (bit << r);
                 }
                 // ---- partial sums: the finished block of 2^t bits becomes level t
-                if constexpr (tb < BL) {
-                    if (lane < act) ps[tb] = combine<tb>(bit, ps);
-                } else {
-                    const int t = (BL == n) ? n : BL + __builtin_ctz(~(unsigned)j);
-                    if (t < n) {
-                        // level t >= 5 lives in LDS: W = 2^(t-5) words built in place
-                        // from the end, starting with this 32-bit block
-                        const int W = 1 << (t - 5);
-                        const int ot = ps_off(t);
-                        if (lane < act) psw[lane * PW + ot + W - 1] = combine<BL>(bit, ps);
-                        wave_mem_order();
-                        for (int d = 5; d < t; ++d) {
-                            const int sz = 1 << (d - 5);
-                            const int items = act * sz;
-                            const int mypp = get_byte(ptrP, d);
-                            for (int it = lane; it < items; it += 64) {
-                                const int slot = it >> (d - 5), w = it & (sz - 1);
-                                const int pss = __shfl(mypp, slot, 64);
-                                const uint32_t v = psw[pss * PW + ps_off(d) + w] ^ psw[slot * PW + ot + W - sz + w];
-                                psw[slot * PW + ot + W - 2 * sz + w] = v;
-                            }
-                            wave_mem_order();
-                        }
-                        if (lane < act) set_byte(ptrP, t, lane);
-                        wave_mem_order();
-                    }
-                }
+                if constexpr (tb < BL) ps[tb] = combine<tb>(bit, ps);
+                else ps[0] = combine<BL>(bit, ps);
             });
-            // ---- the block's trace entry of every path
-            if (lane < act) {
-                if (tg) {
-                    tru_g[j * L + lane] = ublk;
-                    tra_g[j * L + lane] = (uint8_t)anc;
-                } else {
-                    tru_l[j * L + lane] = ublk;
-                    tra_l[j * L + lane] = (uint8_t)anc;
+            // ---------------- block end: the pointers of the path's slot at
+            // the block start, the finished partial sums, the trace entry
+            const bool alive = sub < nf && pl < act;
+            if (BL == 5 && BL < n) {
+                ptrL.w = shfl64(ptrL.w, anc);
+                ptrP.w = shfl64(ptrP.w, anc);
+                const int t = BL + __builtin_ctz(~(unsigned)j);
+                if (t < n) {
+                    // X_0 = this 32-bit block, X_{b+1} = [level 5 + b xor X_b, X_b];
+                    // level t is X_{t-5}.  Word p of it is found from the top:
+                    // in the first half of X_{b+1} it takes word p of level 5 + b
+                    if (t == 5) {
+                        if (alive) psw[lane * kPsWords] = ps[0];
+                    } else {
+                        const int W = 1 << (t - 5);
+                        const int items = (nf << lgact) * W;
+                        if (t > kPsLds) wg_mem_order();
+                        for (int it0 = 0; it0 < items; it0 += 64) {
+                            const int it = it0 + lane;
+                            const int slot = slot_of<L>(it < items ? it >> (t - 5) : 0, lgact);
+                            const int word = it & (W - 1);
+                            PtrVec pp{shfl64(ptrP.w, slot)};
+                            uint32_t v = __shfl(ps[0], slot, 64);
+                            int w = word;
+                            for (int d = t - 1; d >= 5; --d) {
+                                const int half = 1 << (d - 5);
+                                const int pss = get_byte(pp, d);
+                                if (w < half) {
+                                    if (d < kPsLds) v ^= psw[pss * kPsWords + ps_off(d, 0) + w];
+                                    else v ^= ((glb_ptr<uint32_t>)glam)[(uint32_t)((pss << rlog) + ps_off(d, rlog) + w)];
+                                } else {
+                                    w -= half;
+                                }
+                            }
+                            // a path's level t may be read by no one any more, so
+                            // its own slot's words are free
+                            if (it < items) {
+                                if (t < kPsLds) psw[slot * kPsWords + ps_off(t, 0) + word] = v;
+                                else ((glb_ptr<uint32_t>)glam)[(uint32_t)((slot << rlog) + ps_off(t, rlog) + word)] = v;
+                            }
+                        }
+                    }
+                    set_byte(ptrP, t, lane & (SLOTS - 1));
+                    wave_mem_order();
                 }
             }
+            if (alive) {
+                tru.set(j * SLOTS + lane, ublk);
+                if (tg) tra_g[j * SLOTS + lane] = (uint8_t)anc;
+                else tra_l[j * SLOTS + lane] = (uint8_t)anc;
+            }
         }
-        // ---------------- selection: smallest (CRC fails, metric, position)
+        // ---------------- selection per frame: smallest (CRC fails, metric, position)
         uint64_t key = ~0ull;
-        if (lane < act)
+        if (sub < nf && pl < act)
             key = ((uint64_t)(SYN != 0u) << 40) | ((uint64_t)__float_as_uint(PM) << 8) | (uint64_t)lane;
-        for (int m = 32; m >= 1; m >>= 1) {
+        for (int m = L / 2; m >= 1; m >>= 1) {
             const uint64_t o = (uint64_t)__shfl_xor((unsigned long long)key, m, 64);
             key = o < key ? o : key;
         }
-        const int best = (int)(key & 0xFF);
+        const int best = (int)(key & 63);
         const bool best_ok = ((key >> 40) & 1ull) == 0;
         const float best_pm = __shfl(PM, best, 64);
-        // ---------------- trace the chosen path back, one block at a time: the
-        // slot it held at each block's end, then every bit from its block's word
-        // (frozen bits are 0 there)
-        if (lay.tg) wg_mem_order();
+        // ---------------- trace the chosen paths back, one block at a time: the
+        // slot held at each block's end and that block's decided bits (frozen
+        // bits are 0 there)
+        if (tg) wg_mem_order();
         else wave_mem_order();
-        if (lane == 0) {
+        const int nblk = N >> BL;
+        if (pl == 0 && sub < nf) {
             int s = best;
-            for (int jj = (N >> BL) - 1; jj >= 0; --jj) {
-                chain[jj] = s;
-                s = tg ? tra_g[jj * L + s] : tra_l[jj * L + s];
+            for (int jj = nblk - 1; jj >= 0; --jj) {
+                words[sub * nblk + jj] = tru.get(jj * SLOTS + s);
+                s = tg ? tra_g[jj * SLOTS + s] : tra_l[jj * SLOTS + s];
             }
-        }
-        wave_mem_order();
-        const glb_ptr<uint8_t> urow_p = as_glb<uint8_t>(u_hat + urow);
-        const bool aligned4 = (reinterpret_cast<uintptr_t>(u_hat + urow) & 3u) == 0;
-        for (int it = 4 * lane; it < N; it += 256) {
-            const int jj = it >> BL;
-            const int s = chain[jj];
-            const uint32_t w = (tg ? tru_g[jj * L + s] : tru_l[jj * L + s]) >> (it & (BS - 1));
-            if (aligned4) {
-                *(glb_ptr<uint32_t>)(urow_p + it) =
-                    (w & 1u) | ((w & 2u) << 7) | ((w & 4u) << 14) | ((w & 8u) << 21);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) urow_p[it + k] = (uint8_t)((w >> k) & 1u);
-            }
-        }
-        if (lane == 0) {
+            const int64_t f = frame_of(sub);
             crc_ok[f] = best_ok ? 1 : 0;
             if (pm_out) pm_out[f] = best_pm;
         }
         wave_mem_order();
+        for (int s = 0; s < nf; ++s) {
+            const int64_t f = frame_of(s);
+            uint8_t* const urow = u_hat + f * (row_off ? lay.u_stride : (int64_t)N);
+            const glb_ptr<uint8_t> urow_p = as_glb<uint8_t>(urow);
+            const bool aligned4 = (reinterpret_cast<uintptr_t>(urow) & 3u) == 0;
+            for (int it = 4 * lane; it < N; it += 256) {
+                const uint32_t w = words[s * nblk + (it >> BL)] >> (it & (BS - 1));
+                if (aligned4) {
+                    *(glb_ptr<uint32_t>)(urow_p + it) =
+                        (w & 1u) | ((w & 2u) << 7) | ((w & 4u) << 14) | ((w & 8u) << 21);
+                } else {
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) urow_p[it + b] = (uint8_t)((w >> b) & 1u);
+                }
+            }
+        }
+        wave_mem_order();
     }
 }
 
-using KernelFn = void (*)(CodeDev, const float*, const int32_t*, const int32_t*, int64_t, uint8_t*, uint8_t*,
-                          float*, unsigned char*, Layout, const MixedIo*);
+using KernelFn = void (*)(CodeDev, const float*, SclWork, uint8_t*, uint8_t*, float*, unsigned char*, Layout,
+                          const MixedIo*);
 
-template <int L>
+template <int L, int RANK>
 KernelFn pick_bl(int bl) {
     switch (bl) {
-        case 3: return &scl_kernel<L, 3>;
-        case 4: return &scl_kernel<L, 4>;
-        case 5: return &scl_kernel<L, 5>;
+        case 3: return &scl_kernel<L, 3, kRankNetwork>;
+        case 4: return &scl_kernel<L, 4, kRankNetwork>;
+        case 5: return &scl_kernel<L, 5, RANK>;
         default: return nullptr;
     }
 }
 
-// the bitonic sort is instantiated for the list sizes the comparisons use and
-// threshold selection for the larger lists, both with BL = 5; the counting
-// rank serves every list
+// the counting and threshold forms are instantiated for the list sizes the
+// comparisons use, with BL = 5; the network serves every list
 KernelFn pick(int L, int n, int rank) {
     const int bl = n < 5 ? n : 5;
-    if (rank == kRankBitonic && bl == 5) {
-        if (L == 8) return &scl_kernel<8, 5, kRankBitonic>;
-        if (L == 32) return &scl_kernel<32, 5, kRankBitonic>;
-    }
-    if (rank == kRankThreshold && bl == 5) {
-        if (L == 8) return &scl_kernel<8, 5, kRankThreshold>;
-        if (L == 16) return &scl_kernel<16, 5, kRankThreshold>;
-        if (L == 32) return &scl_kernel<32, 5, kRankThreshold>;
-    }
+    if (rank == kRankCount && L == 8) return pick_bl<8, kRankCount>(bl);
+    if (rank == kRankCount && L == 32) return pick_bl<32, kRankCount>(bl);
+    if (rank == kRankThreshold && L == 8) return pick_bl<8, kRankThreshold>(bl);
+    if (rank == kRankThreshold && L == 32) return pick_bl<32, kRankThreshold>(bl);
     switch (L) {
-        case 1: return pick_bl<1>(bl);
-        case 2: return pick_bl<2>(bl);
-        case 4: return pick_bl<4>(bl);
-        case 8: return pick_bl<8>(bl);
-        case 16: return pick_bl<16>(bl);
-        case 32: return pick_bl<32>(bl);
+        case 1: return pick_bl<1, kRankNetwork>(bl);
+        case 2: return pick_bl<2, kRankNetwork>(bl);
+        case 4: return pick_bl<4, kRankNetwork>(bl);
+        case 8: return pick_bl<8, kRankNetwork>(bl);
+        case 16: return pick_bl<16, kRankNetwork>(bl);
+        case 32: return pick_bl<32, kRankNetwork>(bl);
         default: return nullptr;
     }
-}
-
-int ps_words(int n) { return n <= 5 ? 1 : (1 << (n - 5)) - 1; }
-
-// LDS floats per slot of the LLR heap: levels BL..gl-1 (level d at 2^d - 2^BL)
-int slot_floats(int n, int gl) {
-    const int bl = n < 5 ? n : 5;
-    return (gl > bl ? (1 << gl) - (1 << bl) : 0) + 4;
 }
 
 // bytes of the trace: per block of 2^BL bits and path, the block's decided
 // bits (32-bit word) and the slot the path held at the block start (byte)
-size_t trace_bytes(int L, int N, int n) {
+size_t trace_bytes(int slots, int n) {
     const int bl = n < 5 ? n : 5;
-    return (size_t)(N >> bl) * L * 5;
+    return ((size_t)1 << (n - bl)) * slots * 5;
 }
 
 struct LdsPlan {
     size_t bytes;
-    int tboff;   // LDS trace offset (tg == 0)
+    int soff;    // survivor list
+    int tboff;   // LDS trace (tg == 0)
 };
 
-LdsPlan lds_plan(int L, int N, int n, int gl, bool tg) {
+LdsPlan lds_plan(int L, int slots, int n, bool tg) {
     LdsPlan p{};
     const int bl = n < 5 ? n : 5;
-    size_t b = (size_t)L * slot_floats(n, gl) * 4;  // LLR heap
-    b += (size_t)L * ps_words(n) * 4;                // partial sums of levels >= 5
-    b += 64 * 4;                                      // candidate metrics
-    // the traceback's block chain reuses the space from 0
-    const size_t chain_end = align_up((size_t)(N >> bl) * 4, 16);
-    b = align_up(b > chain_end ? b : chain_end, 16);
+    size_t b = (size_t)slots * (kSlotFloats + kPsWords) * 4;  // level 5, partial sums of levels 5 and 6
+    b = align_up(b, 16);
+    p.soff = (int)b;
+    b += (size_t)slots * 8;
+    // the traceback's block words reuse the space from 0
+    const size_t words_end = (size_t)(slots / L) * ((size_t)1 << (n - bl)) * 4;
+    b = align_up(b > words_end ? b : words_end, 16);
     p.tboff = 0;
     if (!tg) {
         p.tboff = (int)b;
-        b += trace_bytes(L, N, n);
+        b += trace_bytes(slots, n);
     }
     p.bytes = align_up(b, 16);
     return p;
@@ -911,17 +1110,16 @@ LdsPlan lds_plan(int L, int N, int n, int gl, bool tg) {
 
 }  // namespace scl
 
-// candidate ranking: 0 automatic (the bitonic network for L = 8 and 32, where
-// it measured fastest on MI355X; the counting rank otherwise), 1 pruned pseudo
-// sort (counting), 2 bitonic network, 3 threshold selection
+// candidate ranking: 0 automatic (the network, which measured fastest on
+// MI355X at every list size), 1 pruned pseudo sort (counting), 2 network, 3
+// threshold selection
 static std::atomic<int> g_scl_rank_mode{0};
 
-static int rank_kind(int L) {
+static int rank_kind() {
     switch (g_scl_rank_mode.load(std::memory_order_relaxed)) {
         case 1: return scl::kRankCount;
-        case 2: return scl::kRankBitonic;
         case 3: return scl::kRankThreshold;
-        default: return (L == 32 || L == 8) ? scl::kRankBitonic : scl::kRankCount;
+        default: return scl::kRankNetwork;
     }
 }
 
@@ -930,21 +1128,31 @@ static int rank_kind(int L) {
 static std::atomic<int64_t> g_scl_lds_budget{0};
 constexpr size_t kLdsPerCu = 160 * 1024;
 
-polar_status scl_plan(const polar_code* code, int L, int64_t max_frames, SclPlan* plan) {
-    return scl_plan_dims(code->n, L, max_frames, plan);
+// Wavefronts to fill before one takes a second frame: two per SIMD.  Up to
+// there a frame's latency decides, which a second frame in the wavefront makes
+// longer (2048 frames of N = 1024, L = 32: 610 us with one frame each, 714 us
+// with two on half the wavefronts); beyond, issue slots and memory do (4096
+// frames of L = 8: 497 us with two each, 665 us with one).
+static int64_t scl_target() { return (int64_t)device_cu_count() * 8; }
+
+polar_status scl_plan(const polar_code* code, int L, int64_t max_frames, SclPlan* plan, int max_fpw) {
+    return scl_plan_dims(code->n, L, max_frames, plan, max_fpw);
 }
 
-polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan) {
-    const int N = 1 << n;
-    scl::KernelFn fn = scl::pick(L, n, rank_kind(L));
+polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan, int max_fpw) {
+    scl::KernelFn fn = scl::pick(L, n, rank_kind());
     if (!fn) return set_error(POLAR_ERR_INVALID_ARG, "scl: L must be a power of two in [1, 32]");
+    // frames a wavefront may take at once: as many as its lanes hold lists,
+    // if there can be that many frames
+    int fpw = 1;
+    while (2 * fpw <= 64 / L && 2 * fpw <= max_fpw && fpw * scl_target() < max_frames) fpw *= 2;
+    const int slots = L * fpw;
     // tree levels: level 5 in LDS (read by every bit of a block), the levels
     // above in the workgroup's global slice (each written and read once per
     // block start that reaches it, as a stream); the trace in LDS if it fits
     // the budget, else in the global slice
-    const int gl = n < 6 ? n : 6;
     bool tg = false;
-    scl::LdsPlan lp = scl::lds_plan(L, N, n, gl, tg);
+    scl::LdsPlan lp = scl::lds_plan(L, slots, n, tg);
     size_t budget = (size_t)g_scl_lds_budget.load(std::memory_order_relaxed);
     if (budget == 0) {
         int by_regs = 0;
@@ -954,7 +1162,7 @@ polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan) {
     }
     if (lp.bytes > budget) {
         tg = true;
-        lp = scl::lds_plan(L, N, n, gl, tg);
+        lp = scl::lds_plan(L, slots, n, tg);
     }
     if (lp.bytes > 160 * 1024) return set_error(POLAR_ERR_UNSUPPORTED, "scl: list too large for LDS");
     int per_cu = 0;
@@ -963,27 +1171,33 @@ polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan) {
     int64_t grid = (int64_t)device_cu_count() * per_cu;
     if (max_frames < grid) grid = max_frames;
     if (grid < 1) grid = 1;
-    plan->gl = gl;
+    plan->slots = slots;
     plan->lds_bytes = lp.bytes;
     plan->trace_glob = tg ? 1 : 0;
+    plan->surv_off = lp.soff;
     plan->tb_off = lp.tboff;
-    const size_t lam_b = (gl < n) ? (size_t)L * N * 4 : 0;
+    size_t lam_b = 0;
+    if (n > 6) {  // (level 5 alone needs no row)
+        const size_t one = (size_t)L << scl::row_log(n, false), many = (size_t)slots << scl::row_log(n, true);
+        lam_b = (fpw > 1 && many > one ? many : one) * 4;
+    }
     plan->trace_off = lam_b;
-    plan->glob_per_wg = align_up(lam_b + (tg ? scl::trace_bytes(L, N, n) : 0), 256);
+    plan->glob_per_wg = align_up(lam_b + (tg ? scl::trace_bytes(slots, n) : 0), 256);
     plan->grid = (int)grid;
+    plan->target = (int)scl_target();
     plan->lay_n = n;
     return POLAR_OK;
 }
 
-polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float* llr, int L,
-                        const int32_t* frame_ids, const int32_t* count_dev, int64_t count_host, uint8_t* u_hat,
-                        uint8_t* crc_ok, float* pm, void* glob, hipStream_t stream, const MixedIo* io,
+polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float* llr, int L, const SclWork& work,
+                        uint8_t* u_hat, uint8_t* crc_ok, float* pm, void* glob, hipStream_t stream, const MixedIo* io,
                         int64_t u_stride) {
-    scl::KernelFn fn = scl::pick(L, plan.lay_n, rank_kind(L));
+    scl::KernelFn fn = scl::pick(L, plan.lay_n, rank_kind());
     scl::Layout lay;
-    lay.gl = plan.gl;
-    lay.sl = scl::slot_floats(plan.lay_n, plan.gl);
-    lay.pw = scl::ps_words(plan.lay_n);
+    lay.slots = plan.slots;
+    lay.fpw = plan.slots / L;
+    lay.target = plan.target < plan.grid ? plan.target : plan.grid;
+    lay.soff = plan.surv_off;
     lay.tg = plan.trace_glob;
     lay.nblk = (1 << plan.lay_n) >> (plan.lay_n < 5 ? plan.lay_n : 5);
     lay.gbytes = (int64_t)plan.glob_per_wg;
@@ -991,8 +1205,8 @@ polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float
     lay.tboff = plan.tb_off;
     lay.u_stride = u_stride;
     unsigned char* gb = plan.glob_per_wg ? reinterpret_cast<unsigned char*>(glob) : nullptr;
-    hipLaunchKernelGGL(fn, dim3(plan.grid), dim3(64), plan.lds_bytes, stream, code->dev(), llr, frame_ids,
-                       count_dev, count_host, u_hat, crc_ok, pm, gb, lay, io);
+    hipLaunchKernelGGL(fn, dim3(plan.grid), dim3(64), plan.lds_bytes, stream, code->dev(), llr, work, u_hat, crc_ok,
+                       pm, gb, lay, io);
     return hip_check(hipGetLastError(), "scl_kernel launch");
 }
 
@@ -1012,7 +1226,7 @@ extern "C" polar_status scl_decode_batch(const polar_code* code, const float* ll
     if (B == 0) return ok_status();
     const size_t need = plan.glob_per_wg * plan.grid;
     if (need && (!ws || ws_bytes < need)) return set_error(POLAR_ERR_WORKSPACE, "scl_decode_batch: workspace too small");
-    st = launch_scl(code, plan, llr, L, frame_ids, nullptr, B, u_hat, crc_ok, pm, ws, stream);
+    st = launch_scl(code, plan, llr, L, SclWork::list(frame_ids, nullptr, B), u_hat, crc_ok, pm, ws, stream);
     return st == POLAR_OK ? ok_status() : st;
 }
 

@@ -1,0 +1,129 @@
+"""Several frames per wavefront in the list decoder: batches large enough that
+wavefronts take two or more frames, with a remainder in the last one, against
+the same frames decoded in batches small enough to take one each, and against
+the oracle at small block lengths."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_1609_09358_amd import binding as PB
+from paper_1609_09358_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+POLY = {0: 0, 8: 0x07, 16: 0x1021, 24: 0x864CFB}
+KEYS = ("u_hat", "crc_ok", "pm")
+
+
+def cus():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def llrs(code, B, ebn0, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    bits = torch.randint(0, 2, (B, code.K), generator=g, device="cuda", dtype=torch.uint8)
+    x = PB.polar_encode(code, bits).float()
+    s2 = O.sigma2(ebn0, code.K / code.N)
+    return (2.0 * (1.0 - 2.0 * x + s2 ** 0.5 * torch.randn(x.shape, generator=g, device="cuda")) / s2).contiguous()
+
+
+# frames per wavefront: 2 with the first count, more (as many as lists fit) with the second
+@pytest.mark.parametrize("N,c", [(8, 0), (16, 0), (32, 8), (64, 8), (128, 8), (256, 16), (512, 16), (1024, 24),
+                                 (2048, 16), (4096, 16)])
+@pytest.mark.parametrize("L", [1, 2, 4, 8, 16, 32])
+@pytest.mark.parametrize("per_cu,extra", [(8, 3), (56, 5)])
+def test_packed_equals_single(N, c, L, per_cu, extra):
+    B = per_cu * cus() + extra
+    if N * B * L > 1 << 30:
+        B = 8 * cus() + extra  # two frames each
+    code = PB.PolarCode(N, N // 2 - (c if N <= 32 else 0), c, 0, 2.0, da_bits=N // 8)
+    llr = llrs(code, B, 1.5, N + L)
+    # a few exact ties at every list boundary: LLRs on a coarse grid
+    llr[: B // 4] = torch.round(llr[: B // 4] * 2) / 2
+    all_ = PB.scl_decode_batch(code, llr, L)
+    step = 4 * cus()
+    for f in range(0, B, step):
+        one = PB.scl_decode_batch(code, llr[f: f + step].contiguous(), L)
+        for k in KEYS:
+            assert torch.equal(all_[k][f: f + step], one[k]), (k, f)
+
+
+@pytest.mark.parametrize("N,K,c,L", [(16, 8, 0, 8), (64, 32, 8, 32), (128, 64, 8, 8), (256, 100, 16, 16)])
+def test_packed_matches_oracle(N, K, c, L):
+    B = 24 * cus() + 1
+    code = PB.PolarCode(N, K, c, 0, 2.0)
+    llr = llrs(code, B, 1.5, 3)
+    out = {k: v.cpu().numpy() for k, v in PB.scl_decode_batch(code, llr, L).items()}
+    rows = np.r_[0:20, B // 2: B // 2 + 20, B - 20: B]
+    ref = O.scl_batch(llr.cpu().numpy()[rows], code.frozen, L, c, POLY[c], prec="f32")
+    assert np.array_equal(out["u_hat"][rows], ref["u_hat"])
+    assert np.array_equal(out["crc_ok"][rows], ref["crc_ok"])
+    assert np.array_equal(out["pm"][rows], ref["pm"].astype(np.float32))
+
+
+def test_packed_frame_ids_and_ranking_modes():
+    N, K, c, L, rows = 128, 64, 8, 8, 30 * 256
+    code = PB.PolarCode(N, K, c, 0, 2.0)
+    llr = llrs(code, rows, 1.5, 11)
+    ids = torch.randperm(rows, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))[: rows - 77]
+    ref = PB.scl_decode_batch(code, llr, L)
+    try:
+        for mode in (0, 1, 2, 3):
+            PB.polar_set_scl_ranking(mode)
+            out = PB.scl_decode_batch(code, llr, L, frame_ids=ids.to(torch.int32).contiguous())
+            for k in KEYS:
+                assert torch.equal(out[k][ids], ref[k][ids]), (mode, k)
+            untouched = torch.ones(rows, dtype=torch.bool, device="cuda")
+            untouched[ids] = False
+            assert int(out["u_hat"][untouched].sum()) == 0
+    finally:
+        PB.polar_set_scl_ranking(0)
+
+
+def test_infinite_and_huge_llrs_stay_in_bounds():
+    """Infinite and very large LLRs: the decode ends, packed and single agree where the arithmetic has no NaN."""
+    N, K, c, L = 64, 32, 8, 8
+    B = 20 * cus()
+    code = PB.PolarCode(N, K, c, 0, 2.0)
+    llr = llrs(code, B, 1.5, 2)
+    llr[::3] *= 1e30
+    out = PB.scl_decode_batch(code, llr, L)
+    one = PB.scl_decode_batch(code, llr[: 4 * cus()].contiguous(), L)
+    for k in KEYS:
+        assert torch.equal(out[k][: 4 * cus()], one[k])
+    llr[::5, ::7] = float("inf")
+    out = PB.scl_decode_batch(code, llr, L)
+    torch.cuda.synchronize()
+    assert int((out["u_hat"] > 1).sum()) == 0
+
+
+def test_mixed_queue_of_several_codes_packs_per_code():
+    """More failed frames than wavefronts in a plan whose codes share one block length."""
+    codes = [PB.PolarCode(64, K, 8, 0, 2.0) for K in (16, 32, 44)]
+    B = 30 * cus() + 7
+    rng = np.random.default_rng(4)
+    cf = rng.integers(0, 3, B).astype(np.int32)
+    plan = PB.MixedPlan(codes, B, max_iter=2, L=8)
+    llr_off, out_off, nl, nk = plan.layout(cf)
+    llr = torch.empty(nl, device="cuda")
+    rows = [llrs(code, B, 1.0, 20 + i) for i, code in enumerate(codes)]
+    idx = torch.from_numpy(cf.astype(np.int64)).cuda()
+    allr = torch.stack(rows)[idx, torch.arange(B, device="cuda")]
+    llr.copy_(allr.reshape(-1))
+    info = torch.zeros(nk, dtype=torch.uint8, device="cuda")
+    used = torch.zeros(B, dtype=torch.uint8, device="cuda")
+    stats = torch.zeros(8, dtype=torch.int64, device="cuda")
+    plan(llr, torch.from_numpy(cf).cuda(), torch.from_numpy(llr_off).cuda(), torch.from_numpy(out_off).cuda(), info,
+         used, stats, graph=True)
+    info, used = info.cpu().numpy(), used.cpu().numpy()
+    assert int(used.sum()) > 8 * cus()
+    for c, code in enumerate(codes):
+        sel = np.flatnonzero(cf == c)
+        dec = PB.HybridDecoder(code, max_iter=2, L=8)
+        st = dec(rows[c][torch.from_numpy(sel).cuda()].contiguous())
+        gi, gu = st["info"].cpu().numpy(), st["used_scl"].cpu().numpy()
+        assert np.array_equal(used[sel], gu)
+        got = np.stack([info[out_off[f]: out_off[f] + code.K] for f in sel])
+        assert np.array_equal(got, gi)
