@@ -514,12 +514,16 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
 
 // PERSIST: a grid smaller than the batch walks it (frame slots advance by the
 // grid size), so a capped grid leaves room on every CU for other kernels.
-// The N = 1024 inference kernel with one weight per stage column (128
-// threads per frame) fits 128 VGPRs without spilling inside its loop, which
-// lets four waves share a SIMD instead of three.
+// From N = 1024 on the inference kernels with eight nodes per thread are held
+// to 128 VGPRs (from 126 to 162), so that four waves share a SIMD instead of
+// three, at N = 4096 two frames a CU instead of one; what they spill (0 to 80
+// bytes per lane) is read outside the iteration loop or once per iteration.
+// Plain BP, re-encoding stop: N = 1024, 65536 frames 2509 -> 2402 us, N = 4096,
+// 4096 frames 4619 -> 3689 us; exact rule, N = 4096: 5788 -> 5177 us.  A weight
+// per node needs more registers.
 template <int NLOG, int RLOG, bool WEIGHTED, bool SAVE, bool WSTAGE, bool PERSIST>
 constexpr int bp_waves_per_eu() {
-    return (NLOG == 10 && RLOG == 3 && WEIGHTED && WSTAGE && !SAVE && !PERSIST) ? 4 : 1;
+    return (NLOG >= 10 && RLOG == 3 && (!WEIGHTED || WSTAGE) && !SAVE && !PERSIST) ? 4 : 1;
 }
 
 template <int NLOG, int RLOG, bool WEIGHTED, bool SAVE, int RULE = 0, bool WSTAGE = false, bool PERSIST = false>
@@ -573,11 +577,12 @@ __attribute__((amdgpu_waves_per_eu(bp_waves_per_eu<NLOG, RLOG, WEIGHTED, SAVE, W
 // each).
 // With io->codes, frame id uses the code io->codes[io->code_of[id]] (all of
 // the kernel's block length).
-// The unweighted N = 2048 gather kernel (256 threads per frame) fits three
-// waves per SIMD instead of two without spilling: its failing frames run every iteration, so more frames in
-// flight shorten the mixed batch's longest chain.
+// The unweighted gather kernels from N = 512 on are held to four waves per SIMD
+// too: their failing frames run every iteration, so more frames in flight
+// shorten the mixed batch's longest chain (twelve codes, 4096 frames: 2692 ->
+// 2498 us).
 template <int NLOG, int RLOG, bool WEIGHTED>
-constexpr int gather_waves_per_eu() { return (NLOG == 11 && RLOG == 3 && !WEIGHTED) ? 3 : 1; }
+constexpr int gather_waves_per_eu() { return (NLOG >= 9 && RLOG == 3 && !WEIGHTED) ? 4 : 1; }
 
 template <int NLOG, int RLOG, bool WEIGHTED>
 __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG))
@@ -668,6 +673,28 @@ bool bp_variant_supported(int n, int variant) { return bp::lookup(n, variant) !=
 
 int bp_default_variant(int n) { return n >= 9 ? 3 : 2; }
 
+// The default layout of a batch.  Eight nodes per thread (r = 3) issue fewer
+// instructions per frame; four (r = 2) spread a frame over twice the threads,
+// which ends its iterations sooner as long as the chip holds all frames at once:
+// N = 1024 up to three frames per CU (256 frames, at most 100 iterations: 160
+// against 202 us; 768: 213 against 230; 8192: 674 both; 65536: 4253 against
+// 4040), N = 2048 one (256: 236 against 245 us; 512: 322 against 277); never
+// at N = 4096 (16 frames: 376 against 339 us).  With a weight per node the
+// registers r = 3 holds weights in cost it wavefronts: N = 512 is faster with
+// r = 2 at every size (16 frames 25 against 42 us, 65536: 699 against 876) and
+// so is N = 4096 (768: 227 against 566 us), N = 1024 and 2048 up to three
+// frames per CU (768: 38 against 40, 77 against 87 us).
+static int bp_auto_variant(int n, int64_t B, const bp_params* p) {
+    const int64_t cus = device_cu_count();
+    if (p->rule == 0 && p->weights && p->weight_layout == 0) {
+        if (n == 9 || n == 12) return 2;
+        if ((n == 10 || n == 11) && B <= 3 * cus) return 2;
+    } else if (p->rule == 0) {
+        if ((n == 10 && B <= 3 * cus) || (n == 11 && B <= cus)) return 2;
+    }
+    return bp_default_variant(n);
+}
+
 int bp_list_variants(int n, int32_t* ids, int cap) {
     int c = 0;
     for (int r = 2; r <= 3; ++r)
@@ -681,7 +708,7 @@ int bp_list_variants(int n, int32_t* ids, int cap) {
 polar_status launch_bp(const polar_code* code, const float* llr, int64_t B, const bp_params* p, uint8_t* u_hat,
                        float* llr_u, int32_t* iters, uint8_t* ok, hipStream_t stream, int wgs_per_cu,
                        uint8_t* info_out) {
-    const int variant = p->variant ? p->variant : bp_default_variant(code->n);
+    const int variant = p->variant ? p->variant : bp_auto_variant(code->n, B, p);
     const bp::Entry* e = bp::lookup(code->n, variant);
     if (!e) return set_error(POLAR_ERR_UNSUPPORTED, "bp: no kernel variant for this block length");
     if (B == 0) return POLAR_OK;

@@ -46,14 +46,28 @@ __device__ __forceinline__ float wave_max(float v) {
 // min(max(v, -m), m) for every non-NaN v, signed zeros included
 __device__ __forceinline__ float clipf(float v, float m) { return __builtin_amdgcn_fmed3f(v, -m, m); }
 
+// ln y for y in [1, 2]: the hardware base-2 logarithm times ln 2, the product
+// taken with ln 2 as the sum of two floats so that it rounds like one of twice
+// the precision.  The general logarithm returns the same bits here; what it
+// spends on tiny, infinite and negative arguments (seven of its instructions)
+// cannot act.
+__device__ __forceinline__ float ln_1_to_2(float y) {
+    constexpr float kLn2Hi = 0x1.62e42ep-1f, kLn2Lo = 0x1.efa39ep-25f;
+    const float l = __builtin_amdgcn_logf(y);
+    const float h = l * kLn2Hi;
+    return h + __fmaf_rn(l, kLn2Lo, __fmaf_rn(l, kLn2Hi, -h));
+}
+
 // The exact check-node rule of Sec. II-B, ln((1 + e^(a+b)) / (e^a + e^b)),
 // through the identity sgn(a) sgn(b) min(|a|,|b|) + ln(1 + e^-|a+b|) -
 // ln(1 + e^-|a-b|), which never overflows.  The two correction terms use the
 // hardware base-2 exponential and logarithm (a few ulp; the terms are below
-// ln 2, so the absolute error stays near 1e-7).
+// ln 2, so the absolute error stays near 1e-7).  The rule is bound by these
+// (four quarter-rate instructions per term): with the general logarithm 50
+// iterations of N = 4096 at 2 dB took 5177 us for 4096 frames, 4276 us this way.
 __device__ __forceinline__ float g_exact(float a, float b) {
     const float m = g_ms(a, b);
-    return (m + __logf(1.0f + __expf(-fabsf(a + b)))) - __logf(1.0f + __expf(-fabsf(a - b)));
+    return (m + ln_1_to_2(1.0f + __expf(-fabsf(a + b)))) - ln_1_to_2(1.0f + __expf(-fabsf(a - b)));
 }
 
 template <int RULE>
