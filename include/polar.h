@@ -242,17 +242,17 @@ polar_status hybrid_decode_batch_static(const polar_code* code, const float* llr
 
 /* ---------------------------------------------------------------------------
  * Pipelined hybrid over a sequence of batches: the asynchronous BP / SCL
- * scheduling of Sec. III (Fig. 3) on two streams.  For batch j, BP and the
- * compaction of its failed frames run on stream_bp; its CA-SCL and the merge
- * run on stream_scl once they are done, so the list decoding of batch j
+ * scheduling of Sec. III (Fig. 3) on two streams.  For batch j, BP,
+ * which queues its failed frames, runs on stream_bp; its CA-SCL runs on
+ * stream_scl once that is done, so the list decoding of batch j
  * overlaps the BP of the following batches.  The workspace holds two
- * per-batch states (batch j + 2 waits for the merge of batch j); the list
+ * per-batch states (batch j + 2 waits for the CA-SCL of batch j); the list
  * decoder's global slice is shared, since list decodes follow one another on
  * stream_scl.
  * llr, info_hat, used_scl: host arrays of nbatch device pointers ([B][N],
  * [B][K], [B]; used_scl may be NULL or hold NULL entries); batches may share
  * an input buffer, not an output buffer (the BP of batch j + 1 writes its
- * kept frames' information bits while batch j's list-decoded ones are merged).  Results and stats (accumulated as in hybrid_decode_batch)
+ * kept frames' information bits while batch j's list-decoded ones are written).  Results and stats (accumulated as in hybrid_decode_batch)
  * are complete when work enqueued on stream_bp after the call completes:
  * stream_bp finally waits for stream_scl.  The two streams must differ.
  * ws: at least polar_pipeline_workspace_size(code, B, L, params) bytes.
@@ -297,8 +297,8 @@ int32_t polar_get_pipeline_scl_occupancy(void);
  * 32 bits: by code); each bucket's BP is a persistent kernel that decodes
  * every frame with its own code and appends the failed frames to a queue
  * drained by one persistent CA-SCL kernel, again per frame's code; the
- * buckets' chains are concurrent branches on the plan's streams; a merge
- * writes the results.
+ * buckets' chains are concurrent branches on the plan's streams; both decoders
+ * write their frames' information bits, a last kernel the flags and statistics.
  * polar_mixed_decode enqueues the kernels; polar_mixed_decode_graph replays
  * the same work as one hipGraph, captured on its first call on the plan
  * (the kernels read the per-call buffers through a device argument block

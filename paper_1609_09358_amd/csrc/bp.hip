@@ -532,7 +532,7 @@ __attribute__((amdgpu_waves_per_eu(bp_waves_per_eu<NLOG, RLOG, WEIGHTED, SAVE, W
     CodeDev code, const float* __restrict__ llr, int64_t B, int max_iter, int stop, float lmax,
     const float* __restrict__ W, uint8_t* __restrict__ u_hat, uint8_t* __restrict__ info_out,
     float* __restrict__ llr_u, int32_t* __restrict__ iters_out, uint8_t* __restrict__ ok_out,
-    float* __restrict__ saved) {
+    float* __restrict__ saved, BpQueue queue) {
     using G = Geom<NLOG, RLOG>;
     constexpr int N = G::N;
     __shared__ BpShared<G> sh;
@@ -560,23 +560,31 @@ __attribute__((amdgpu_waves_per_eu(bp_waves_per_eu<NLOG, RLOG, WEIGHTED, SAVE, W
         io.iters = iters_out ? iters_out + frame : nullptr;
         io.ok = ok_out ? ok_out + frame : nullptr;
         io.saved = SAVE ? saved + (size_t)frame * max_iter * 2 * G::n * N : nullptr;
+        bool okv;
         if constexpr (WEIGHTED && WSTAGE && RULE == 0 && !SAVE) {
-            if (unit) bp_frame<G, true, false, 0, true, true>(code, io, max_iter, stop, lmax, W, sh, t, slot);
-            else bp_frame<G, true, false, 0, true, false>(code, io, max_iter, stop, lmax, W, sh, t, slot);
+            if (unit) okv = bp_frame<G, true, false, 0, true, true>(code, io, max_iter, stop, lmax, W, sh, t, slot);
+            else okv = bp_frame<G, true, false, 0, true, false>(code, io, max_iter, stop, lmax, W, sh, t, slot);
         } else {
-            bp_frame<G, WEIGHTED, SAVE, RULE, WSTAGE>(code, io, max_iter, stop, lmax, W, sh, t, slot);
+            okv = bp_frame<G, WEIGHTED, SAVE, RULE, WSTAGE>(code, io, max_iter, stop, lmax, W, sh, t, slot);
+        }
+        if (!SAVE && queue.ids && t == 0) {
+            if (queue.used_scl) queue.used_scl[frame] = okv ? 0 : 1;
+            if (!okv) queue.ids[atomicAdd(queue.count, 1)] = (int32_t)frame;
         }
         if (!PERSIST) break;
     }
 }
 
 // Persistent form for ragged batches: workgroups walk the list ids[0..*count)
-// (the count lives on the device); frame id's LLR row starts at element
-// io->off[id] of io->llr, its u_hat row at id * u_stride; iters and ok are
-// indexed by id; failed frames are appended to their code's queue (one atomic
+// (the count lives on the device), each taking its first frames by its number
+// and the next ones as it gets there (a frame runs 5 iterations or 200, and a
+// fixed share of the list kept some workgroups busy with two long frames after
+// the others had ended); frame id's LLR row starts at element
+// io->off[id] of io->llr, its information bits go to io->info + io->out_off[id];
+// iters and ok are indexed by id; failed frames are appended to their code's queue (one atomic
 // each).
-// With io->codes, frame id uses the code io->codes[io->code_of[id]] (all of
-// the kernel's block length).
+// Frame id uses the code io->codes[io->code_of[id]] (all of the kernel's block
+// length).
 // The unweighted gather kernels from N = 512 on are held to four waves per SIMD
 // too: their failing frames run every iteration, so more frames in flight
 // shorten the mixed batch's longest chain (twelve codes, 4096 frames: 2692 ->
@@ -587,8 +595,8 @@ constexpr int gather_waves_per_eu() { return (NLOG >= 9 && RLOG == 3 && !WEIGHTE
 template <int NLOG, int RLOG, bool WEIGHTED>
 __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG))
 __attribute__((amdgpu_waves_per_eu(gather_waves_per_eu<NLOG, RLOG, WEIGHTED>()))) void bp_gather_kernel(
-    CodeDev code, const MixedIo* __restrict__ mio, const int32_t* __restrict__ ids, const int32_t* __restrict__ count,
-    int max_iter, int stop, float lmax, const float* __restrict__ W, uint8_t* __restrict__ u_hat, int64_t u_stride,
+    const MixedIo* __restrict__ mio, const int32_t* __restrict__ ids, const int32_t* __restrict__ count,
+    int32_t* __restrict__ ticket, int max_iter, int stop, float lmax, const float* __restrict__ W,
     int32_t* __restrict__ iters_out, uint8_t* __restrict__ ok_out, int32_t* __restrict__ fail_ids,
     int64_t fail_stride, int32_t* __restrict__ fail_count) {
     using G = Geom<NLOG, RLOG>;
@@ -599,34 +607,39 @@ __attribute__((amdgpu_waves_per_eu(gather_waves_per_eu<NLOG, RLOG, WEIGHTED>()))
     const int64_t cnt = *count;
     const float* llr = mio->llr;
     const int64_t* off = mio->off;
-    const int64_t stride = num_groups_x() * G::FPW;
-    for (int64_t q0 = gid_x() * G::FPW; q0 < cnt; q0 += stride) {
+    __shared__ int next_first;
+    for (int64_t q0 = gid_x() * G::FPW; q0 < cnt;) {
         const int64_t q = q0 + slot;
-        if (G::T >= 64) __syncthreads();  // the previous frame's staging is read
+        if (G::T >= 64) __syncthreads();  // the previous frame's staging and next_first are read
+        int ticket_now = 0;
+        if (tid == 0) ticket_now = atomicAdd(ticket, G::FPW);  // not waited for before the frame is decoded
         if (q >= cnt) break;             // only when T < 64: this slot's wavefront lanes leave alone
         const int id = ids[q];
-        const int cid = mio->codes ? mio->code_of[id] : 0;
-        const CodeDev cd = mio->codes ? mio->codes[cid] : code;
+        const int cid = mio->code_of[id];
+        const CodeDev cd = mio->codes[cid];
         FrameIO io;
         io.llr = llr + off[id];
-        io.u_hat = u_hat + (int64_t)id * u_stride;
-        io.info = nullptr;
+        io.u_hat = nullptr;
+        io.info = mio->info + mio->out_off[id];
         io.llr_u = nullptr;
         io.iters = iters_out + id;
         io.ok = ok_out + id;
         io.saved = nullptr;
         const bool okv = bp_frame<G, WEIGHTED, false>(cd, io, max_iter, stop, lmax, W, sh, t, slot);
         if (t == 0 && !okv) fail_ids[cid * fail_stride + atomicAdd(&fail_count[cid], 1)] = id;
+        if (tid == 0) next_first = ticket_now;
+        frame_sync<G>();
+        q0 = num_groups_x() * G::FPW + next_first;
     }
 }
 
 // ------------------------------------------------------------------ dispatch
 
 using KernelFn = void (*)(CodeDev, const float*, int64_t, int, int, float, const float*, uint8_t*, uint8_t*,
-                          float*, int32_t*, uint8_t*, float*);
+                          float*, int32_t*, uint8_t*, float*, BpQueue);
 
-using GatherFn = void (*)(CodeDev, const MixedIo*, const int32_t*, const int32_t*, int, int, float, const float*,
-                          uint8_t*, int64_t, int32_t*, uint8_t*, int32_t*, int64_t, int32_t*);
+using GatherFn = void (*)(const MixedIo*, const int32_t*, const int32_t*, int32_t*, int, int, float, const float*,
+                          int32_t*, uint8_t*, int32_t*, int64_t, int32_t*);
 
 struct Entry {
     KernelFn plain, weighted, weighted_save, exact, weighted_stage;
@@ -707,7 +720,7 @@ int bp_list_variants(int n, int32_t* ids, int cap) {
 
 polar_status launch_bp(const polar_code* code, const float* llr, int64_t B, const bp_params* p, uint8_t* u_hat,
                        float* llr_u, int32_t* iters, uint8_t* ok, hipStream_t stream, int wgs_per_cu,
-                       uint8_t* info_out) {
+                       uint8_t* info_out, BpQueue queue) {
     const int variant = p->variant ? p->variant : bp_auto_variant(code->n, B, p);
     const bp::Entry* e = bp::lookup(code->n, variant);
     if (!e) return set_error(POLAR_ERR_UNSUPPORTED, "bp: no kernel variant for this block length");
@@ -728,7 +741,7 @@ polar_status launch_bp(const polar_code* code, const float* llr, int64_t B, cons
         }
     }
     hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(e->wg), 0, stream, code->dev(), llr, B, p->max_iter, p->stop,
-                       p->llr_max, p->weights, u_hat, info_out, llr_u, iters, ok, (float*)nullptr);
+                       p->llr_max, p->weights, u_hat, info_out, llr_u, iters, ok, (float*)nullptr, queue);
     return hip_check(hipGetLastError(), "bp_kernel launch");
 }
 
@@ -747,15 +760,14 @@ polar_status bp_gather_grid(const polar_code* code, const bp_params* p, int64_t 
 }
 
 polar_status launch_bp_gather(const polar_code* code, const MixedIo* io, const int32_t* ids, const int32_t* count,
-                              const bp_params* p, uint8_t* u_hat, int64_t u_stride, int32_t* iters, uint8_t* ok,
-                              int32_t* fail_ids, int64_t fail_stride, int32_t* fail_count, int grid,
-                              hipStream_t stream) {
+                              int32_t* ticket, const bp_params* p, int32_t* iters, uint8_t* ok, int32_t* fail_ids,
+                              int64_t fail_stride, int32_t* fail_count, int grid, hipStream_t stream) {
     const int variant = p->variant ? p->variant : bp_default_variant(code->n);
     const bp::Entry* e = bp::lookup(code->n, variant);
     if (!e) return set_error(POLAR_ERR_UNSUPPORTED, "bp: no kernel variant for this block length");
     bp::GatherFn fn = p->weights ? e->gather_weighted : e->gather_plain;
-    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(e->wg), 0, stream, code->dev(), io, ids, count, p->max_iter,
-                       p->stop, p->llr_max, p->weights, u_hat, u_stride, iters, ok, fail_ids, fail_stride, fail_count);
+    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(e->wg), 0, stream, io, ids, count, ticket, p->max_iter,
+                       p->stop, p->llr_max, p->weights, iters, ok, fail_ids, fail_stride, fail_count);
     return hip_check(hipGetLastError(), "bp_gather_kernel launch");
 }
 
@@ -773,7 +785,7 @@ polar_status launch_bp_save(const polar_code* code, const float* llr, int64_t B,
     const int64_t blocks = (B + e->fpw - 1) / e->fpw;
     bp::KernelFn fn = saved ? e->weighted_save : e->weighted;
     hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(e->wg), 0, stream, code->dev(), llr, B, T, 0, llr_max, W,
-                       u_hat, (uint8_t*)nullptr, llr_u, (int32_t*)nullptr, ok, saved);
+                       u_hat, (uint8_t*)nullptr, llr_u, (int32_t*)nullptr, ok, saved, BpQueue());
     return hip_check(hipGetLastError(), "bp_kernel launch");
 }
 

@@ -88,9 +88,16 @@ polar_status hip_check(hipError_t e, const char* what);
 // persistent grid), where such a kernel exists (min-sum, unweighted or
 // per-stage weights); otherwise one workgroup per frame group
 // info_out (or null): [B][K] information bits of the frames whose verdict is ok
+// queue: where the ids of the other frames go
+struct BpQueue {
+    int32_t* ids = nullptr;       // or null: no queue
+    int32_t* count = nullptr;     // its length, 0 before the launch
+    uint8_t* used_scl = nullptr;  // [B] 1 for a queued frame, 0 for the others, or null
+};
 polar_status launch_bp(const polar_code* code, const float* llr, int64_t B, const bp_params* p,
                        uint8_t* u_hat, float* llr_u, int32_t* iters, uint8_t* ok,
-                       hipStream_t stream, int wgs_per_cu = 0, uint8_t* info_out = nullptr);
+                       hipStream_t stream, int wgs_per_cu = 0, uint8_t* info_out = nullptr,
+                       BpQueue queue = BpQueue());
 polar_status launch_bp_save(const polar_code* code, const float* llr, int64_t B, int T, float llr_max,
                             const float* W, int variant, uint8_t* u_hat, float* llr_u, uint8_t* ok, float* saved,
                             hipStream_t stream);
@@ -103,17 +110,18 @@ struct MixedIo {
     // codes[code_of[f]] instead of the kernel's code argument
     const int32_t* code_of;
     const CodeDev* codes;
+    uint8_t* info;           // K information bits of frame f from element out_off[f] on
+    const int64_t* out_off;
 };
 
-// persistent BP over a device list of frame ids with ragged row offsets; a
-// failed frame of code c (0 without io->codes) is appended to the queue at
-// fail_ids + c * fail_stride, of length fail_count[c]
+// persistent BP over a device list of frame ids with ragged row offsets: the
+// information bits of the frames whose verdict is ok go to io->info; a failed
+// frame of code c is appended to the queue at fail_ids + c * fail_stride, of
+// length fail_count[c].  *ticket (0 before the launch) hands out the list.
 polar_status bp_gather_grid(const polar_code* code, const bp_params* p, int64_t max_frames, int* grid);
-// u_hat row of frame f: f * u_stride
 polar_status launch_bp_gather(const polar_code* code, const MixedIo* io, const int32_t* ids, const int32_t* count,
-                              const bp_params* p, uint8_t* u_hat, int64_t u_stride, int32_t* iters, uint8_t* ok,
-                              int32_t* fail_ids, int64_t fail_stride, int32_t* fail_count, int grid,
-                              hipStream_t stream);
+                              int32_t* ticket, const bp_params* p, int32_t* iters, uint8_t* ok, int32_t* fail_ids,
+                              int64_t fail_stride, int32_t* fail_count, int grid, hipStream_t stream);
 bool bp_variant_supported(int n, int variant);
 int bp_default_variant(int n);
 int bp_list_variants(int n, int32_t* ids, int cap);
@@ -135,6 +143,9 @@ struct SclPlan {
 polar_status scl_plan(const polar_code* code, int L, int64_t max_frames, SclPlan* plan, int max_fpw = 64);
 // a plan that holds any code with n <= max_n (n >= 5)
 polar_status scl_plan_dims(int max_n, int L, int64_t max_frames, SclPlan* plan, int max_fpw = 64);
+
+// bytes beside the per-batch state that hybrid_decode_batch_static asks for
+size_t scl_static_share(int n, int L);
 
 // The frames of one list-decoder launch: queue k holds the frame ids
 // ids[code_ids[k] * queue_stride + i] of code code_ids[k], i < its length
@@ -158,12 +169,20 @@ struct SclWork {
     }
 };
 
-// io (optional): LLR rows of a ragged batch (frame f at element io->off[f]),
-// u_hat rows then at f * u_stride; with io->codes queue k's frames are decoded
-// with io->codes[code_ids[k]]
+// Where the results go; each may be null but crc_ok.  info: the K information
+// bits of frame f at f * K.
+struct SclOut {
+    uint8_t* u_hat = nullptr;
+    uint8_t* info = nullptr;
+    uint8_t* crc_ok = nullptr;
+    float* pm = nullptr;
+};
+
+// io (optional): a ragged batch -- LLR rows at io->off[f], information bits at
+// io->info + io->out_off[f] (and no u_hat); queue k's frames are decoded with
+// io->codes[code_ids[k]]
 polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float* llr, int L, const SclWork& work,
-                        uint8_t* u_hat, uint8_t* crc_ok, float* pm, void* glob, hipStream_t stream,
-                        const MixedIo* io = nullptr, int64_t u_stride = 0);
+                        const SclOut& out, void* glob, hipStream_t stream, const MixedIo* io = nullptr);
 
 int device_cu_count();
 

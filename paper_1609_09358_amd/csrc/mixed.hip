@@ -9,12 +9,13 @@
 // device) decoding every frame with its own code and appends the frames whose
 // verdict is not ok to their code's queue, and a persistent CA-SCL kernel
 // drains the queues of the group's codes (a wavefront decodes several frames
-// of one code at once).  After the branches join, a merge kernel
-// writes every frame's information bits, its list-decoder flag and the
-// statistics.  (Codes shorter than 32 bits form one group each.)  No host round trip and no per-call
+// of one code at once).  Both write their frames' information bits; after the
+// branches join, a kernel writes the list-decoder flags and the statistics.
+// (Codes shorter than 32 bits form one group each.)  No host round trip and no per-call
 // allocation: the plan owns its workspace.  Because the kernels read the
 // per-call buffers through the argument block, the same captured graph
 // serves every call.
+#include <algorithm>
 #include <cstring>
 #include <vector>
 
@@ -28,11 +29,9 @@ constexpr int kMaxBranches = 4;
 static_assert(kMaxCodes <= kSclQueues, "a group's codes are queues of one list-decoder launch");
 
 struct MixedArgs {
-    MixedIo io;                    // llr, llr_off
+    MixedIo io;                    // LLR rows, information bits and codes
     int64_t B;
     const int32_t* code_of_frame;  // [B]
-    const int64_t* out_off;        // [B]
-    uint8_t* info_hat;
     uint8_t* used_scl;             // [B] or null
     int64_t* stats;                // [8] or null
 };
@@ -46,42 +45,59 @@ __global__ void clear_kernel(int32_t* c, int n) {
 }
 
 // ids of group g (the group of the frame's code): lists[g * cap + ...], cnt[g] of them
-__global__ __launch_bounds__(256) void bucket_kernel(const MixedArgs* __restrict__ a, int n_codes, int64_t cap,
+__global__ __launch_bounds__(256) void bucket_kernel(const MixedArgs* __restrict__ a, int n_codes, int n_groups,
+                                                     int64_t cap,
                                                      const int32_t* __restrict__ group_of_code,
                                                      int32_t* __restrict__ lists, int32_t* __restrict__ cnt) {
-    const int64_t f = gid_x() * wg_size_x() + lid_x();
-    if (f >= a->B || f >= cap) return;
-    const int c = a->code_of_frame[f];
-    if (c < 0 || c >= n_codes) return;
-    const int g = group_of_code[c];
-    lists[(int64_t)g * cap + atomicAdd(&cnt[g], 1)] = (int32_t)f;
+    const int64_t f = gid_x() * 256 + lid_x();
+    int g = -1;
+    if (f < a->B && f < cap) {
+        const int c = a->code_of_frame[f];
+        if (c >= 0 && c < n_codes) g = group_of_code[c];
+    }
+    // one atomic per wavefront and group
+    const int lane = lid_x() & 63;
+    for (int h = 0; h < n_groups; ++h) {
+        const uint64_t m = __ballot(g == h);
+        if (m == 0) continue;
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&cnt[h], (int)__popcll(m));
+        base = __shfl(base, 0, 64);
+        if (g == h) lists[(int64_t)h * cap + base + __popcll(m & ((1ull << lane) - 1ull))] = (int32_t)f;
+    }
 }
 
-// one wavefront per frame
-__global__ __launch_bounds__(64) void mixed_merge_kernel(const MixedArgs* __restrict__ a, const CodeDev* __restrict__ codes,
-                                                         int n_codes, const uint8_t* __restrict__ u, int64_t u_stride,
-                                                         const uint8_t* __restrict__ ok,
-                                                         const int32_t* __restrict__ iters,
-                                                         const uint8_t* __restrict__ scl_ok) {
-    const int64_t f = gid_x();
-    if (f >= a->B) return;
-    const int c = a->code_of_frame[f];
-    if (c < 0 || c >= n_codes) return;
-    const CodeDev& cd = codes[c];
-    const uint8_t* uf = u + f * u_stride;
-    uint8_t* dst = a->info_hat + a->out_off[f];
-    for (int q = lid_x(); q < cd.K; q += 64) dst[q] = uf[cd.info_pos[q]];
-    if (lid_x() == 0) {
-        const bool good = ok[f] != 0;
-        if (a->used_scl) a->used_scl[f] = good ? 0 : 1;
-        if (a->stats) {
-            unsigned long long* st = reinterpret_cast<unsigned long long*>(a->stats);
-            atomicAdd(&st[0], 1ull);
-            if (good) atomicAdd(&st[1], 1ull);
-            else atomicAdd(&st[2], 1ull);
-            atomicAdd(&st[3], (unsigned long long)iters[f]);
-            if (!good && !scl_ok[f]) atomicAdd(&st[4], 1ull);
+// list-decoder flags and statistics (the decoders wrote the information bits);
+// one set of atomics per workgroup
+__global__ __launch_bounds__(256) void mixed_flags_kernel(const MixedArgs* __restrict__ a, int n_codes,
+                                                          const uint8_t* __restrict__ ok,
+                                                          const int32_t* __restrict__ iters,
+                                                          const uint8_t* __restrict__ scl_ok) {
+    __shared__ unsigned long long red[5][4];
+    unsigned long long s[5] = {0, 0, 0, 0, 0};  // frames, BP ok, list-decoded, iterations, CRC failures
+    const int64_t f = gid_x() * 256 + lid_x();
+    if (f < a->B) {
+        const int c = a->code_of_frame[f];
+        if (c >= 0 && c < n_codes) {
+            const bool good = ok[f] != 0;
+            if (a->used_scl) a->used_scl[f] = good ? 0 : 1;
+            s[0] = 1;
+            s[1] = good;
+            s[2] = !good;
+            s[3] = (unsigned long long)iters[f];
+            s[4] = !good && !scl_ok[f];
         }
+    }
+    if (!a->stats) return;
+    for (int i = 0; i < 5; ++i) {
+        for (int m = 32; m >= 1; m >>= 1) s[i] += __shfl_xor(s[i], m, 64);
+        if ((lid_x() & 63) == 0) red[i][lid_x() >> 6] = s[i];
+    }
+    __syncthreads();
+    if (lid_x() < 5) {
+        const int i = lid_x();
+        const unsigned long long v = red[i][0] + red[i][1] + red[i][2] + red[i][3];
+        if (v) atomicAdd(reinterpret_cast<unsigned long long*>(a->stats) + i, v);
     }
 }
 
@@ -95,11 +111,11 @@ struct polar_mixed {
     int n_codes = 0;
     int64_t cap = 0;  // max frames per call
     int L = 0;
-    int maxN = 0;
     std::vector<const polar_code*> codes;
     // groups: codes of one block length (one code each below 32 bits)
     int n_groups = 0;
     std::vector<int> rep;           // per group: its first code
+    std::vector<int> order;         // groups by block length, longest first
     std::vector<SclWork> work;      // per group: the failure queues of its codes
     std::vector<bp_params> params;  // per group (the first code's variant)
     std::vector<SclPlan> scl;       // per group
@@ -109,13 +125,12 @@ struct polar_mixed {
     MixedArgs* dargs = nullptr;
     CodeDev* dcodes = nullptr;
     int32_t* gmap = nullptr;    // [n_codes] group of each code
-    int32_t* counts = nullptr;  // [2 * n_codes]: bucket sizes by group, then queue sizes by code
+    int32_t* counts = nullptr;  // [3 * n_codes]: bucket sizes by group, queue sizes by code, tickets by group
     int32_t* lists = nullptr;   // [n_groups][cap]
     int32_t* queues = nullptr;  // [n_codes][cap] failed frames of each code
     uint8_t* ok = nullptr;
     int32_t* iters = nullptr;
     uint8_t* scl_ok = nullptr;
-    uint8_t* u = nullptr;  // [cap][maxN]
     std::vector<void*> glob;  // per list-decoder launch: its global slice
     int nbr = 0;
     hipStream_t br[kMaxBranches] = {};
@@ -176,7 +191,6 @@ extern "C" polar_status polar_mixed_create(const polar_code* const* codes, int32
             return set_error(POLAR_ERR_INVALID_ARG, "polar_mixed_create: unknown BP variant");
         }
         m->codes.push_back(code);
-        if (code->N > m->maxN) m->maxN = code->N;
     }
     // groups: one per block length (one BP kernel and one list-decoder kernel
     // serve the group's codes); a code shorter than 32 bits forms its own
@@ -207,6 +221,9 @@ extern "C" polar_status polar_mixed_create(const polar_code* const* codes, int32
         m->bp_grid.push_back(grid);
         m->scl.push_back(sp);
     }
+    for (int g = 0; g < m->n_groups; ++g) m->order.push_back(g);
+    std::stable_sort(m->order.begin(), m->order.end(),
+                     [&](int x, int y) { return codes[m->rep[x]]->N > codes[m->rep[y]]->N; });
     // one device allocation, carved
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -217,13 +234,12 @@ extern "C" polar_status polar_mixed_create(const polar_code* const* codes, int32
     const size_t o_args = take(sizeof(MixedArgs));
     const size_t o_codes = take(sizeof(CodeDev) * n_codes);
     const size_t o_gmap = take(sizeof(int32_t) * n_codes);
-    const size_t o_cnt = take(sizeof(int32_t) * 2 * n_codes);
+    const size_t o_cnt = take(sizeof(int32_t) * 3 * n_codes);
     const size_t o_lists = take(sizeof(int32_t) * m->n_groups * max_frames);
     const size_t o_queues = take(sizeof(int32_t) * n_codes * max_frames);
     const size_t o_ok = take(max_frames);
     const size_t o_it = take(sizeof(int32_t) * max_frames);
     const size_t o_sok = take(max_frames);
-    const size_t o_u = take((size_t)m->maxN * max_frames);
     std::vector<size_t> o_g(m->scl.size());
     for (size_t j = 0; j < m->scl.size(); ++j) o_g[j] = take(m->scl[j].glob_per_wg * m->scl[j].grid);
     if ((st = hip_check(hipMalloc(&m->mem, off), "polar_mixed_create: hipMalloc")) != POLAR_OK) {
@@ -241,7 +257,6 @@ extern "C" polar_status polar_mixed_create(const polar_code* const* codes, int32
     m->ok = reinterpret_cast<uint8_t*>(b + o_ok);
     m->iters = reinterpret_cast<int32_t*>(b + o_it);
     m->scl_ok = reinterpret_cast<uint8_t*>(b + o_sok);
-    m->u = reinterpret_cast<uint8_t*>(b + o_u);
     for (int g = 0; g < m->n_groups; ++g) {
         SclWork w{};
         w.ids = m->queues;
@@ -286,32 +301,35 @@ extern "C" void polar_mixed_free(polar_mixed* m) {
 static polar_status mixed_pipeline(polar_mixed* m, hipStream_t st) {
     polar_status r;
     const int nc = m->n_codes, ng = m->n_groups;
-    hipLaunchKernelGGL(clear_kernel, dim3(1), dim3(64), 0, st, m->counts, 2 * nc);
+    hipLaunchKernelGGL(clear_kernel, dim3(1), dim3(64), 0, st, m->counts, 3 * nc);
     const unsigned bgrid = (unsigned)((m->cap + 255) / 256);
-    hipLaunchKernelGGL(bucket_kernel, dim3(bgrid), dim3(256), 0, st, m->dargs, nc, m->cap, m->gmap, m->lists,
+    hipLaunchKernelGGL(bucket_kernel, dim3(bgrid), dim3(256), 0, st, m->dargs, nc, ng, m->cap, m->gmap, m->lists,
                        m->counts);
     if ((r = hip_check(hipGetLastError(), "bucket launch")) != POLAR_OK) return r;
     if ((r = hip_check(hipEventRecord(m->ev_fork, st), "event record")) != POLAR_OK) return r;
     for (int s = 0; s < m->nbr; ++s)
         if ((r = hip_check(hipStreamWaitEvent(m->br[s], m->ev_fork, 0), "stream wait")) != POLAR_OK) return r;
-    for (int g = 0; g < ng; ++g) {
-        hipStream_t bs = m->br[g % m->nbr];
+    // the longest chains first, so that they get the first places on the chip
+    for (int i = 0; i < ng; ++i) {
+        const int g = m->order[i];
+        hipStream_t bs = m->br[i % m->nbr];
         const polar_code* code = m->codes[m->rep[g]];
-        if ((r = launch_bp_gather(code, &m->dargs->io, m->lists + (int64_t)g * m->cap, m->counts + g, &m->params[g],
-                                  m->u, m->maxN, m->iters, m->ok, m->queues, m->cap, m->counts + nc, m->bp_grid[g],
-                                  bs)) != POLAR_OK)
+        if ((r = launch_bp_gather(code, &m->dargs->io, m->lists + (int64_t)g * m->cap, m->counts + g,
+                                  m->counts + 2 * nc + g, &m->params[g], m->iters, m->ok, m->queues, m->cap,
+                                  m->counts + nc, m->bp_grid[g], bs)) != POLAR_OK)
             return r;
-        if ((r = launch_scl(code, m->scl[g], nullptr, m->L, m->work[g], m->u, m->scl_ok, nullptr, m->glob[g], bs,
-                            &m->dargs->io, m->maxN)) != POLAR_OK)
+        SclOut out;
+        out.crc_ok = m->scl_ok;
+        if ((r = launch_scl(code, m->scl[g], nullptr, m->L, m->work[g], out, m->glob[g], bs, &m->dargs->io)) !=
+            POLAR_OK)
             return r;
     }
     for (int s = 0; s < m->nbr; ++s) {
         if ((r = hip_check(hipEventRecord(m->ev_join[s], m->br[s]), "event record")) != POLAR_OK) return r;
         if ((r = hip_check(hipStreamWaitEvent(st, m->ev_join[s], 0), "stream wait")) != POLAR_OK) return r;
     }
-    hipLaunchKernelGGL(mixed_merge_kernel, dim3((unsigned)m->cap), dim3(64), 0, st, m->dargs, m->dcodes, nc, m->u,
-                       (int64_t)m->maxN, m->ok, m->iters, m->scl_ok);
-    return hip_check(hipGetLastError(), "mixed merge launch");
+    hipLaunchKernelGGL(mixed_flags_kernel, dim3(bgrid), dim3(256), 0, st, m->dargs, nc, m->ok, m->iters, m->scl_ok);
+    return hip_check(hipGetLastError(), "mixed flags launch");
 }
 
 static polar_status mixed_set_args(polar_mixed* m, int64_t B, const float* llr, const int32_t* code_of_frame,
@@ -330,10 +348,10 @@ static polar_status mixed_set_args(polar_mixed* m, int64_t B, const float* llr, 
     a.io.off = llr_off;
     a.io.code_of = code_of_frame;
     a.io.codes = m->dcodes;
+    a.io.info = info_hat;
+    a.io.out_off = out_off;
     a.B = B;
     a.code_of_frame = code_of_frame;
-    a.out_off = out_off;
-    a.info_hat = info_hat;
     a.used_scl = used_scl;
     a.stats = stats;
     hipLaunchKernelGGL(set_args_kernel, dim3(1), dim3(64), 0, stream, m->dargs, a);

@@ -429,7 +429,6 @@ struct Layout {
     int64_t toff;    // byte offset of the trace inside the slice
     int tboff;       // byte offset of the LDS trace (the traceback's block words sit below it)
     int nblk;        // blocks of the largest block length the layout holds (trace rows)
-    int64_t u_stride;  // u_hat row stride of a ragged batch
 };
 
 // Active path a of the wavefront's frames (lists of 2^lg paths, L slots a frame)
@@ -649,9 +648,8 @@ struct TraceRows {
 
 template <int L, int BL, int RANK>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void scl_kernel(
-    CodeDev code_in, const float* __restrict__ llr, SclWork work, uint8_t* __restrict__ u_hat,
-    uint8_t* __restrict__ crc_ok, float* __restrict__ pm_out, unsigned char* __restrict__ glob_all, Layout lay,
-    const MixedIo* __restrict__ mio) {
+    CodeDev code_in, const float* __restrict__ llr, SclWork work, SclOut out, unsigned char* __restrict__ glob_all,
+    Layout lay, const MixedIo* __restrict__ mio) {
     constexpr int BS = 1 << BL;  // bits per block
     constexpr int LOGL = ctz_c(L);
     extern __shared__ __attribute__((aligned(16))) unsigned char sm[];
@@ -708,9 +706,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
             return ids ? (int64_t)ids[q] : q;
         };
         CodeDev code = code_in;
-        if (mio && mio->codes) {
-            // (several codes in one launch: the layout holds the largest;
-            // level offsets inside a slot do not depend on n)
+        if (mio) {
             code = mio->codes[code_id];
             code.frozen_bits = uniform_ptr(code.frozen_bits);
             code.da_bits = uniform_ptr(code.da_bits);
@@ -728,8 +724,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
         const uint32_t fzv0 = lane < nw ? fzb[lane] : 0u, fzv1 = 64 + lane < nw ? fzb[64 + lane] : 0u;
         const uint32_t dav0 = lane < nw ? dab[lane] : 0u, dav1 = 64 + lane < nw ? dab[64 + lane] : 0u;
         const glb_ptr<const uint32_t> synp = as_glb<const uint32_t>(code.syn);
-        // rows of frame f: LLRs at row_off[f] (ragged batch) or f * N; u_hat at
-        // f * u_stride (ragged batch) or f * N
+        // LLR row of a lane's frame: at row_off[f] (ragged batch) or f * N
         auto chan_of = [&]() -> const float* {
             const int64_t f = frame_of(sub);
             return llr_base + (row_off ? row_off[f] : f * N);
@@ -1020,13 +1015,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
                 s = tg ? tra_g[jj * SLOTS + s] : tra_l[jj * SLOTS + s];
             }
             const int64_t f = frame_of(sub);
-            crc_ok[f] = best_ok ? 1 : 0;
-            if (pm_out) pm_out[f] = best_pm;
+            out.crc_ok[f] = best_ok ? 1 : 0;
+            if (out.pm) out.pm[f] = best_pm;
         }
         wave_mem_order();
         for (int s = 0; s < nf; ++s) {
             const int64_t f = frame_of(s);
-            uint8_t* const urow = u_hat + f * (row_off ? lay.u_stride : (int64_t)N);
+            // information bits of a hybrid's frame, each from its block's word
+            if (uint8_t* const row = mio ? mio->info + mio->out_off[f] : out.info ? out.info + f * code.K : nullptr)
+                for (int q = lane; q < code.K; q += 64) {
+                    const int pos = code.info_pos[q];
+                    row[q] = (uint8_t)((words[s * nblk + (pos >> BL)] >> (pos & (BS - 1))) & 1u);
+                }
+            if (!out.u_hat) continue;
+            uint8_t* const urow = out.u_hat + f * (int64_t)N;
             const glb_ptr<uint8_t> urow_p = as_glb<uint8_t>(urow);
             const bool aligned4 = (reinterpret_cast<uintptr_t>(urow) & 3u) == 0;
             for (int it = 4 * lane; it < N; it += 256) {
@@ -1044,8 +1046,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
     }
 }
 
-using KernelFn = void (*)(CodeDev, const float*, SclWork, uint8_t*, uint8_t*, float*, unsigned char*, Layout,
-                          const MixedIo*);
+using KernelFn = void (*)(CodeDev, const float*, SclWork, SclOut, unsigned char*, Layout, const MixedIo*);
 
 template <int L, int RANK>
 KernelFn pick_bl(int bl) {
@@ -1128,6 +1129,17 @@ static int rank_kind() {
 static std::atomic<int64_t> g_scl_lds_budget{0};
 constexpr size_t kLdsPerCu = 160 * 1024;
 
+static size_t scl_budget(scl::KernelFn fn) {
+    size_t budget = (size_t)g_scl_lds_budget.load(std::memory_order_relaxed);
+    if (budget == 0) {
+        int by_regs = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&by_regs, fn, 64, 0) != hipSuccess || by_regs < 1) by_regs = 1;
+        budget = (kLdsPerCu / (size_t)by_regs) & ~(size_t)255;
+        if (budget < 4096) budget = 4096;
+    }
+    return budget;
+}
+
 // Wavefronts to fill before one takes a second frame: two per SIMD.  Up to
 // there a frame's latency decides, which a second frame in the wavefront makes
 // longer (2048 frames of N = 1024, L = 32: 610 us with one frame each, 714 us
@@ -1153,14 +1165,7 @@ polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan, int 
     // the budget, else in the global slice
     bool tg = false;
     scl::LdsPlan lp = scl::lds_plan(L, slots, n, tg);
-    size_t budget = (size_t)g_scl_lds_budget.load(std::memory_order_relaxed);
-    if (budget == 0) {
-        int by_regs = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&by_regs, fn, 64, 0) != hipSuccess || by_regs < 1) by_regs = 1;
-        budget = (kLdsPerCu / (size_t)by_regs) & ~(size_t)255;
-        if (budget < 4096) budget = 4096;
-    }
-    if (lp.bytes > budget) {
+    if (lp.bytes > scl_budget(fn)) {
         tg = true;
         lp = scl::lds_plan(L, slots, n, tg);
     }
@@ -1189,9 +1194,21 @@ polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan, int 
     return POLAR_OK;
 }
 
+// The share of one list decode by which hybrid_decode_batch_static takes or
+// refuses a batch: every LLR level above 5 of L paths, and the trace where it
+// did not fit the LDS budget beside a frame's whole state (level 5, all partial
+// sums from level 5 on, 64 candidates).
+size_t scl_static_share(int n, int L) {
+    const size_t trace = scl::trace_bytes(L, n);
+    size_t lds = (size_t)L * ((n > 5 ? 36 : 4) + (n <= 5 ? 1 : (1 << (n - 5)) - 1)) * 4 + 256;
+    const size_t chain = align_up(((size_t)1 << (n - (n < 5 ? n : 5))) * 4, 16);
+    lds = align_up(align_up(lds > chain ? lds : chain, 16) + trace, 16);
+    const size_t levels = n > 6 ? ((size_t)L << n) * 4 : 0;
+    return align_up(levels + (lds > scl_budget(scl::pick(L, n, rank_kind())) ? trace : 0), 256);
+}
+
 polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float* llr, int L, const SclWork& work,
-                        uint8_t* u_hat, uint8_t* crc_ok, float* pm, void* glob, hipStream_t stream, const MixedIo* io,
-                        int64_t u_stride) {
+                        const SclOut& out, void* glob, hipStream_t stream, const MixedIo* io) {
     scl::KernelFn fn = scl::pick(L, plan.lay_n, rank_kind());
     scl::Layout lay;
     lay.slots = plan.slots;
@@ -1203,10 +1220,9 @@ polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float
     lay.gbytes = (int64_t)plan.glob_per_wg;
     lay.toff = (int64_t)plan.trace_off;
     lay.tboff = plan.tb_off;
-    lay.u_stride = u_stride;
     unsigned char* gb = plan.glob_per_wg ? reinterpret_cast<unsigned char*>(glob) : nullptr;
-    hipLaunchKernelGGL(fn, dim3(plan.grid), dim3(64), plan.lds_bytes, stream, code->dev(), llr, work, u_hat, crc_ok,
-                       pm, gb, lay, io);
+    hipLaunchKernelGGL(fn, dim3(plan.grid), dim3(64), plan.lds_bytes, stream, code->dev(), llr, work, out, gb, lay,
+                       io);
     return hip_check(hipGetLastError(), "scl_kernel launch");
 }
 
@@ -1226,7 +1242,11 @@ extern "C" polar_status scl_decode_batch(const polar_code* code, const float* ll
     if (B == 0) return ok_status();
     const size_t need = plan.glob_per_wg * plan.grid;
     if (need && (!ws || ws_bytes < need)) return set_error(POLAR_ERR_WORKSPACE, "scl_decode_batch: workspace too small");
-    st = launch_scl(code, plan, llr, L, SclWork::list(frame_ids, nullptr, B), u_hat, crc_ok, pm, ws, stream);
+    SclOut out;
+    out.u_hat = u_hat;
+    out.crc_ok = crc_ok;
+    out.pm = pm;
+    st = launch_scl(code, plan, llr, L, SclWork::list(frame_ids, nullptr, B), out, ws, stream);
     return st == POLAR_OK ? ok_status() : st;
 }
 
