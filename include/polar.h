@@ -200,15 +200,10 @@ polar_status scl_decode_batch(const polar_code* code, const float* llr, int64_t 
  * stats     dev int64 [8] or NULL, accumulated (not cleared):
  *           [0] frames, [1] BP ok, [2] SCL frames, [3] BP iterations summed,
  *           [4] SCL frames whose CRC failed, [5..7] reserved (0).
- * Graphs: the kernels of a call are fixed by (device, code, B, params, L,
- * the buffer pointers, the list decoder's tuning settings).  The first call
- * with such a combination launches them directly; the second captures them
- * into one hipGraph and every later call with the same combination replays
- * it on `stream` (the kernels read the buffers, including the weights, when
- * they run, so their contents may change between calls).  The library keeps
- * the graphs of the 8 most recently used combinations.  Calls on a stream
- * that is being captured launch directly.  polar_set_hybrid_graphs(0) turns
- * the replay off (process-wide), 1 (the default) on.
+ * A call is three kernels on `stream` (four with stats), launched directly.
+ * polar_set_hybrid_graphs keeps a process-wide setting, 0 or 1 (the default),
+ * for callers written when 1 meant replaying a captured graph of a call's
+ * kernels; both values launch directly, which takes less time now.
  * ------------------------------------------------------------------------- */
 polar_status hybrid_decode_batch(const polar_code* code, const float* llr, int64_t B,
                                  const bp_params* params, int32_t L, uint8_t* info_hat,

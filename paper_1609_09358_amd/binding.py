@@ -269,8 +269,8 @@ def polar_get_scl_ranking() -> int:
 
 
 def polar_set_hybrid_graphs(mode: int):
-    """hybrid_decode_batch: 1 (default) replay a captured graph from the second
-    call with the same arguments on, 0 launch the kernels directly."""
+    """A kept setting, 0 or 1 (default); hybrid_decode_batch launches its kernels
+    directly either way."""
     _check(lib().polar_set_hybrid_graphs(int(mode)))
 
 
@@ -305,9 +305,11 @@ def scl_decode_batch(code: PolarCode, llr: torch.Tensor, L, frame_ids=None, out=
         _dev(frame_ids, torch.int32, (B,), "frame_ids")
     dev = llr.device
     if out is None:
-        out = dict(u_hat=torch.zeros((rows, code.N), dtype=torch.uint8, device=dev),
-                   crc_ok=torch.zeros(rows, dtype=torch.uint8, device=dev),
-                   pm=torch.zeros(rows, dtype=torch.float32, device=dev))
+        # every row is written unless a list of frames picks some: then the others read 0
+        new = torch.empty if frame_ids is None else torch.zeros
+        out = dict(u_hat=new((rows, code.N), dtype=torch.uint8, device=dev),
+                   crc_ok=new(rows, dtype=torch.uint8, device=dev),
+                   pm=new(rows, dtype=torch.float32, device=dev))
     need = polar_workspace_size(code, B, L)
     if workspace is None and need:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
