@@ -38,20 +38,46 @@ __device__ __forceinline__ void g_partials(float a, float b, float& da, float& d
 // reads of a row come soon after the first, from the caches).  N = 1024, T = 20,
 // 1024 frames, 3.36 GB: 1275 us with each column's operands loaded when it is
 // reached, 855 us with the next column's in flight (3.9 TB/s); N = 256, T = 10,
-// 4096 frames, 1.34 GB: 441 and 324 us.
-template <int NLOG, int RLOG>
-__global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
+// 4096 frames, 1.34 GB: 441 and 324 us; with the sum over frames, and the
+// frames of a group added before they are written (below), 1803 -> 1181 -> 798
+// and 2088 -> 489 -> 227 us.
+// FG > 1: a workgroup takes FG frames through the columns in step and adds their
+// weight gradients, column by column, in frame order and double precision,
+// before anything is written: the double goes over the slots of the group's
+// first two frames (low word, high word; a last group of one frame keeps its
+// float), so instead of FG floats written here and read by the sum over frames
+// it is two.  The frames' values of a column meet in LDS, one barrier per column
+// (two buffers in turn), thread (g, t) adding registers g, g + FG, ...
+template <class G, int FG>
+struct BwdGeom {
+    static constexpr int WG = FG == 1 ? G::WG : FG * G::T;
+    static constexpr int FPG = FG == 1 ? G::FPW : FG;                 // frames per workgroup
+    static constexpr int TBS = G::T < 64 ? WG / 64 : WG / G::T;       // transpose buffers
+    static constexpr int XCH = FG == 1 ? 1 : 2 * FG * G::N;           // words of the exchange
+};
+
+template <int NLOG, int RLOG, int FG>
+__global__ __launch_bounds__((BwdGeom<Geom<NLOG, RLOG>, FG>::WG)) void wbp_bwd_kernel(
     CodeDev code, const float* __restrict__ llr, int64_t B, int T, float lmax, const float* __restrict__ W,
     float* __restrict__ saved, const float* __restrict__ dlam, int dlam_iters, float* __restrict__ dllr) {
     using G = Geom<NLOG, RLOG>;
+    using BG = BwdGeom<G, FG>;
     constexpr int n = G::n, N = G::N, V = G::V, KL = G::NWIN - 1;
-    __shared__ float tb[G::TAB.words];
+    __shared__ float tb_all[BG::TBS * G::TAB.words];
+    __shared__ float xch[BG::XCH];
 
     const int tid = lid_x();
-    const int t = (G::T < 64) ? (tid & (G::T - 1)) : tid;
-    const int slot = (G::T < 64) ? (tid >> G::P) : 0;
-    const int64_t frame = gid_x() * G::FPW + slot;
-    if (G::T < 64 && frame >= B) return;
+    const int t = tid & (G::T - 1);
+    // frame of the workgroup (the same for a whole wavefront where it has one)
+    const int gf = G::T >= 64 ? __builtin_amdgcn_readfirstlane(tid >> G::P) : tid >> G::P;
+    const int slot = (G::T < 64) ? ((tid & 63) >> G::P) : 0;  // and of the wavefront
+    float* const tb = tb_all + (G::T < 64 ? tid >> 6 : gf) * G::TAB.words;
+    const int64_t first = gid_x() * BG::FPG;
+    const bool valid = first + gf < B;
+    if (FG == 1 && G::T < 64 && !valid) return;
+    // a group's missing frames go along on the last one and add nothing
+    const int64_t frame = valid ? first + gf : B - 1;
+    const int group = (int)(B - first < FG ? B - first : FG);  // frames of this group
 
     int bfrom[G::NB > 0 ? G::NB : 1], bto[G::NB > 0 ? G::NB : 1];
     static_for<0, G::NB>([&](auto J) {
@@ -97,7 +123,9 @@ __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
     auto fetch = [&](auto DC, auto SC, int it) {
         constexpr int dir = decltype(DC)::value, s = decltype(SC)::value;
         constexpr int k = s / G::r;
-        const int ib = idx_base<G, k>(t);
+        int to = t;
+        if constexpr (FG > 1) asm volatile("" : "+v"(to));
+        const int ib = idx_base<G, k>(to);
         const float* Sy = S + (size_t)it * 2 * n * N;
         const int lt = dir == 1 ? it : it - 1;
         const float* Sx = S + (size_t)(lt > 0 ? lt : 0) * 2 * n * N;
@@ -111,8 +139,50 @@ __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
         }
     };
     fetch(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{}, T - 1);
+    // the weight gradient of column s, direction dir, over the messages it no
+    // longer needs
+    auto put_gradient = [&](auto DC, auto SC, int it, const float (&dWv)[V]) {
+        constexpr int dir = decltype(DC)::value, s = decltype(SC)::value;
+        constexpr int wb = G::wbase(s / G::r);
+        const size_t row = ((size_t)it * 2 + dir) * n * N + (size_t)s * N;
+        if constexpr (FG == 1) {
+            const int ib = idx_base<G, s / G::r>(t);
+#pragma unroll
+            for (int v = 0; v < V; ++v) S[row + ib + (v << wb)] = dWv[v];
+        } else {
+            // the thread index made opaque here, so that the addresses of all
+            // columns are not computed ahead and held in registers
+            int to = t;
+            asm volatile("" : "+v"(to));
+            const int ib = idx_base<G, s / G::r>(to);
+            constexpr int buf = (dir == 1 ? s : s + 1) & 1;  // columns alternate: L 0 .. n - 1, R n - 1 .. 0
+            float* xb = xch + buf * FG * N;
+#pragma unroll
+            for (int v = 0; v < V; ++v) xb[gf * N + v * G::T + to] = valid ? dWv[v] : 0.0f;
+            __syncthreads();
+            float* const S0 = saved + (size_t)first * T * 2 * n * N + row;
+            float* const S1 = S0 + (size_t)T * 2 * n * N;
+#pragma unroll
+            for (int q = 0; q < (V + FG - 1) / FG; ++q) {
+                const int v = gf + q * FG;
+                if (v < V) {
+                    double acc = 0.0;
+#pragma unroll
+                    for (int g = 0; g < FG; ++g) acc += (double)xb[g * N + v * G::T + to];
+                    const uint64_t w = (uint64_t)__double_as_longlong(acc);
+                    const int off = ib + (v << wb);
+                    S0[off] = group > 1 ? __uint_as_float((uint32_t)w) : (float)acc;
+                    if (group > 1) S1[off] = __uint_as_float((uint32_t)(w >> 32));
+                }
+            }
+        }
+    };
 
-    for (int it = T - 1; it >= 0; --it) {
+    for (int itc = T - 1; itc >= 0; --itc) {
+        // the iteration made opaque, so that the loop carries one counter and
+        // not an address for every row
+        int it = itc;
+        asm volatile("" : "+s"(it));
         // the loss reads LLR(u) after this iteration (every iteration, or only
         // the last); row 0 of L feeds nothing else, so its adjoint is d loss / d lambda
         if (dlam_iters == T || it == T - 1) {
@@ -121,18 +191,15 @@ __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
 #pragma unroll
             for (int v = 0; v < V; ++v) aL[0][v] = dl[ib + v];
         }
-        float* St = S + (size_t)it * 2 * n * N;
         // ---------------- undo the L sweep: columns 0..n-1
         static_for<0, G::NWIN>([&](auto KC) {
             constexpr int k = decltype(KC)::value;
             if constexpr (k > 0) {
                 transpose_row<G, k - 1, k - 1, k, false>(aL[G::cbeg(k)], tb, bfrom[k - 1], bto[k - 1]);
             }
-            const int ib = idx_base<G, k>(t);
             static_for<G::cbeg(k), G::cend(k)>([&](auto SC) {
                 constexpr int s = decltype(SC)::value;
                 constexpr int q = s - G::wbase(k);
-                constexpr int wb = G::wbase(k);
                 float A[V], Rr[V], Wr[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
@@ -171,8 +238,7 @@ __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
                     aL[s + 1][v2] = aL[s + 1][v2] + dj;
                 }
                 // L^t_s is no longer read: its slot takes the weight gradient
-#pragma unroll
-                for (int v = 0; v < V; ++v) St[(size_t)(1 * n + s) * N + ib + (v << wb)] = dWv[v];
+                put_gradient(std::integral_constant<int, 1>{}, SC, it, dWv);
             });
         });
         // ---------------- undo the R sweep: columns n-1..0
@@ -181,11 +247,9 @@ __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
             if constexpr (k < G::NWIN - 1) {
                 transpose_row<G, k, k + 1, k, true>(aR[G::cend(k)], tb, bto[k], bfrom[k]);
             }
-            const int ib = idx_base<G, k>(t);
             static_for_rev<G::cbeg(k), G::cend(k)>([&](auto SC) {
                 constexpr int s = decltype(SC)::value;
                 constexpr int q = s - G::wbase(k);
-                constexpr int wb = G::wbase(k);
                 float Lp[V], Rr[V], Wr[V];
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
@@ -224,12 +288,11 @@ __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG)) void wbp_bwd_kernel(
                     if (s > 0) aR[s][v2] = aR[s][v2] + dj;
                 }
                 // R^t_{s+1} is no longer read: its slot takes the weight gradient
-#pragma unroll
-                for (int v = 0; v < V; ++v) St[(size_t)(0 * n + s) * N + ib + (v << wb)] = dWv[v];
+                put_gradient(std::integral_constant<int, 0>{}, SC, it, dWv);
             });
         });
     }
-    if (dllr) {
+    if (dllr && valid) {
         const int ib = idx_base<G, KL>(t);
 #pragma unroll
         for (int v = 0; v < V; ++v)
@@ -242,11 +305,24 @@ using BwdFn = void (*)(CodeDev, const float*, int64_t, int, float, const float*,
 struct BwdEntry {
     BwdFn fn;
     int wg, fpw;
+    // the grouped form (or null)
+    BwdFn group_fn;
+    int group_wg, group;
 };
+
+// Frames per group where the grouped form exists: the layout of r that leaves
+// room for at least four frames in a workgroup of 512 threads with its registers
+template <int NL, int RL>
+constexpr int bwd_group() {
+    return (NL == 7 || NL == 8) && RL == 2 ? 8 : NL == 9 && RL == 3 ? 8 : NL == 10 && RL == 3 ? 4 : 1;
+}
 
 template <int NL, int RL>
 constexpr BwdEntry make_bwd() {
-    return BwdEntry{&wbp_bwd_kernel<NL, RL>, Geom<NL, RL>::WG, Geom<NL, RL>::FPW};
+    using G = Geom<NL, RL>;
+    constexpr int FG = bwd_group<NL, RL>();
+    return BwdEntry{&wbp_bwd_kernel<NL, RL, 1>, G::WG, G::FPW, FG > 1 ? &wbp_bwd_kernel<NL, RL, FG> : nullptr,
+                    BwdGeom<G, FG>::WG, FG};
 }
 
 const BwdEntry* lookup_bwd(int n, int r) {
@@ -279,6 +355,23 @@ namespace {
 // 128 registers and spill more than r = 3 (865 against 818 us for 256 frames).
 int bwd_default_variant(int n) { return n <= 11 ? 2 : 3; }
 
+// The grouped adjoint: its layout, and the batches it serves -- those whose
+// groups fill enough of the places for them on the chip (workgroups of 256 or
+// 512 threads: this many per CU by registers), over all rounds: half up to N =
+// 512, where the adjoint and the sum over frames take less than half the time
+// when all places are filled (4096 frames of N = 256, T = 10: 227 against 531
+// us; 2048 of N = 512: 271 against 545), seven tenths at N = 1024 (1024 frames,
+// T = 20: 798 against 1182 us); with fewer groups the frames one by one spread
+// better.
+int bwd_group_variant(int n) { return n <= 8 ? 2 : 3; }
+bool bwd_grouped(int n, int64_t B) {
+    if (n < 7 || n > 10) return false;
+    const int64_t group = n == 10 ? 4 : 8, per_cu = n == 7 ? 3 : n == 8 ? 2 : 1;
+    const int64_t groups = B / group, places = (int64_t)device_cu_count() * per_cu;
+    const int64_t rounds = (groups + places - 1) / places;
+    return groups > 0 && (n == 10 ? 10 * groups >= 7 * rounds * places : 2 * groups >= rounds * places);
+}
+
 // Sum of the per-frame gradients part[f][q] over the frames, in double.  One
 // thread per VEC columns q would leave the chip idle (P / 256 workgroups, a
 // serial chain of B loads each), so the frames are split into segments of
@@ -290,6 +383,9 @@ int bwd_default_variant(int n) { return n <= 11 ? 2 : 3; }
 // segment the partial sums add at most an eighth.  Measured: T = 10, N = 256,
 // B = 4096 (671 MB) 1647 us with one thread per column, 165 us; T = 20,
 // N = 1024, B = 1024 (1.7 GB) 528 us, 326 us.
+// Grouped rows (group > 1, the adjoint's sums over `group` frames): row g is
+// the double in rows group g and group g + 1, the last a float where its group
+// has one frame.
 constexpr int kReduceUnroll = 8;
 constexpr int64_t kReduceMinRows = 32;
 
@@ -298,85 +394,133 @@ struct alignas(4 * VEC) FloatVec {
     float v[VEC];
 };
 
-template <int VEC, bool PARTIAL>
-__global__ __launch_bounds__(256) void wbp_reduce_kernel(float* part, int64_t B, int64_t P, int segments,
+// VEC doubles kept as low and high words in two rows
+template <int VEC>
+__device__ __forceinline__ void load_pair(const float* lo, const float* hi, double (&d)[VEC]) {
+    using Vec = FloatVec<VEC>;
+    const Vec l = *reinterpret_cast<const Vec*>(lo), h = *reinterpret_cast<const Vec*>(hi);
+#pragma unroll
+    for (int j = 0; j < VEC; ++j)
+        d[j] = __longlong_as_double((long long)(((uint64_t)__float_as_uint(h.v[j]) << 32) | __float_as_uint(l.v[j])));
+}
+template <int VEC>
+__device__ __forceinline__ void store_pair(float* lo, float* hi, const double (&d)[VEC]) {
+    using Vec = FloatVec<VEC>;
+    Vec l, h;
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) {
+        const uint64_t w = (uint64_t)__double_as_longlong(d[j]);
+        l.v[j] = __uint_as_float((uint32_t)w);
+        h.v[j] = __uint_as_float((uint32_t)(w >> 32));
+    }
+    *reinterpret_cast<Vec*>(lo) = l;
+    *reinterpret_cast<Vec*>(hi) = h;
+}
+template <int VEC>
+__device__ __forceinline__ void store_float(float* p, const double (&d)[VEC]) {
+    FloatVec<VEC> o;
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) o.v[j] = (float)d[j];
+    *reinterpret_cast<FloatVec<VEC>*>(p) = o;
+}
+
+// rows: frames (group = 1) or groups of frames
+template <int VEC, bool PARTIAL, bool GROUPED>
+__global__ __launch_bounds__(256) void wbp_reduce_kernel(float* part, int64_t B, int group, int64_t P, int segments,
                                                          float* __restrict__ dW) {
     const int64_t q = (gid_x() * 256 + lid_x()) * VEC;
     if (q >= P) return;
+    const int64_t rows = GROUPED ? (B + group - 1) / group : B;
     const int64_t s = PARTIAL ? gid_y() : 0;
-    const int64_t r0 = PARTIAL ? B * s / segments : 0, r1 = PARTIAL ? B * (s + 1) / segments : B;
+    const int64_t r0 = PARTIAL ? rows * s / segments : 0, r1 = PARTIAL ? rows * (s + 1) / segments : rows;
+    const int64_t stride = (GROUPED ? group : 1) * P;
     double acc[VEC];
 #pragma unroll
     for (int j = 0; j < VEC; ++j) acc[j] = 0.0;
     using Vec = FloatVec<VEC>;
+    constexpr int U = GROUPED ? kReduceUnroll / 2 : kReduceUnroll;
+    // the last group of a single frame is a float
+    const int64_t pairs = GROUPED && r1 == rows && (B - 1) % group == 0 ? r1 - 1 : r1;
     int64_t f = r0;
-    for (; f + kReduceUnroll <= r1; f += kReduceUnroll) {
-        Vec x[kReduceUnroll];
+    for (; f + U <= pairs; f += U) {
+        double x[U][VEC];
 #pragma unroll
-        for (int k = 0; k < kReduceUnroll; ++k) x[k] = *reinterpret_cast<const Vec*>(part + (f + k) * P + q);
+        for (int k = 0; k < U; ++k) {
+            const float* p = part + (f + k) * stride + q;
+            if constexpr (GROUPED) {
+                load_pair<VEC>(p, p + P, x[k]);
+            } else {
+                const Vec v = *reinterpret_cast<const Vec*>(p);
 #pragma unroll
-        for (int k = 0; k < kReduceUnroll; ++k)
+                for (int j = 0; j < VEC; ++j) x[k][j] = (double)v.v[j];
+            }
+        }
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) acc[j] += (double)x[k].v[j];
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) acc[j] += x[k][j];
     }
     for (; f < r1; ++f) {
-        const Vec x = *reinterpret_cast<const Vec*>(part + f * P + q);
+        const float* p = part + f * stride + q;
+        if (GROUPED && f < pairs) {
+            double x[VEC];
+            load_pair<VEC>(p, p + P, x);
 #pragma unroll
-        for (int j = 0; j < VEC; ++j) acc[j] += (double)x.v[j];
-    }
-    Vec lo, hi;
+            for (int j = 0; j < VEC; ++j) acc[j] += x[j];
+        } else {
+            const Vec v = *reinterpret_cast<const Vec*>(p);
 #pragma unroll
-    for (int j = 0; j < VEC; ++j) {
-        const uint64_t w = (uint64_t)__double_as_longlong(acc[j]);
-        lo.v[j] = PARTIAL ? __uint_as_float((uint32_t)w) : (float)acc[j];
-        hi.v[j] = __uint_as_float((uint32_t)(w >> 32));
+            for (int j = 0; j < VEC; ++j) acc[j] += (double)v.v[j];
+        }
     }
-    if constexpr (PARTIAL) {
-        *reinterpret_cast<Vec*>(part + r0 * P + q) = lo;
-        *reinterpret_cast<Vec*>(part + (r0 + 1) * P + q) = hi;
-    } else {
-        *reinterpret_cast<Vec*>(dW + q) = lo;
-    }
+    if constexpr (PARTIAL) store_pair<VEC>(part + r0 * stride + q, part + r0 * stride + P + q, acc);
+    else store_float<VEC>(dW + q, acc);
 }
 
 template <int VEC>
-__global__ __launch_bounds__(256) void wbp_reduce_segments_kernel(const float* __restrict__ part, int64_t B, int64_t P,
-                                                                  int segments, float* __restrict__ dW) {
+__global__ __launch_bounds__(256) void wbp_reduce_segments_kernel(const float* __restrict__ part, int64_t rows,
+                                                                  int64_t stride, int64_t P, int segments,
+                                                                  float* __restrict__ dW) {
     const int64_t q = (gid_x() * 256 + lid_x()) * VEC;
     if (q >= P) return;
-    using Vec = FloatVec<VEC>;
     double acc[VEC];
 #pragma unroll
     for (int j = 0; j < VEC; ++j) acc[j] = 0.0;
 #pragma unroll 4
     for (int s = 0; s < segments; ++s) {
-        const int64_t r0 = B * s / segments;
-        const Vec lo = *reinterpret_cast<const Vec*>(part + r0 * P + q);
-        const Vec hi = *reinterpret_cast<const Vec*>(part + (r0 + 1) * P + q);
+        const float* p = part + rows * s / segments * stride + q;
+        double x[VEC];
+        load_pair<VEC>(p, p + P, x);
 #pragma unroll
-        for (int j = 0; j < VEC; ++j)
-            acc[j] += __longlong_as_double(
-                (long long)(((uint64_t)__float_as_uint(hi.v[j]) << 32) | __float_as_uint(lo.v[j])));
+        for (int j = 0; j < VEC; ++j) acc[j] += x[j];
     }
-    Vec o;
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) o.v[j] = (float)acc[j];
-    *reinterpret_cast<Vec*>(dW + q) = o;
+    store_float<VEC>(dW + q, acc);
 }
 
+// group: frames summed by the adjoint (1: none)
 template <int VEC>
-polar_status launch_reduce(float* part, int64_t B, int64_t P, float* dW, hipStream_t stream) {
+polar_status launch_reduce(float* part, int64_t B, int group, int64_t P, float* dW, hipStream_t stream) {
     const int64_t bx = (P / VEC + 255) / 256;
-    // about eight workgroups per CU
+    const int64_t rows = (B + group - 1) / group;
+    // about eight workgroups per CU; a segment's first row is never a last
+    // group of one frame, since it has more rows than that
     int64_t segments = (int64_t)device_cu_count() * 8 / bx;
-    if (segments > B / kReduceMinRows) segments = B / kReduceMinRows;
+    const int64_t most = rows / (group > 1 ? kReduceMinRows / 4 : kReduceMinRows);
+    if (segments > most) segments = most;
+    const dim3 one((unsigned)bx), many((unsigned)bx, (unsigned)(segments > 1 ? segments : 1));
     if (segments > 1) {
-        hipLaunchKernelGGL((wbp_reduce_kernel<VEC, true>), dim3((unsigned)bx, (unsigned)segments), dim3(256), 0, stream,
-                           part, B, P, (int)segments, dW);
-        hipLaunchKernelGGL(wbp_reduce_segments_kernel<VEC>, dim3((unsigned)bx), dim3(256), 0, stream, part, B, P,
+        if (group > 1)
+            hipLaunchKernelGGL((wbp_reduce_kernel<VEC, true, true>), many, dim3(256), 0, stream, part, B, group, P,
+                               (int)segments, dW);
+        else
+            hipLaunchKernelGGL((wbp_reduce_kernel<VEC, true, false>), many, dim3(256), 0, stream, part, B, group, P,
+                               (int)segments, dW);
+        hipLaunchKernelGGL(wbp_reduce_segments_kernel<VEC>, one, dim3(256), 0, stream, part, rows, group * P, P,
                            (int)segments, dW);
+    } else if (group > 1) {
+        hipLaunchKernelGGL((wbp_reduce_kernel<VEC, false, true>), one, dim3(256), 0, stream, part, B, group, P, 1, dW);
     } else {
-        hipLaunchKernelGGL((wbp_reduce_kernel<VEC, false>), dim3((unsigned)bx), dim3(256), 0, stream, part, B, P, 1, dW);
+        hipLaunchKernelGGL((wbp_reduce_kernel<VEC, false, false>), one, dim3(256), 0, stream, part, B, group, P, 1, dW);
     }
     return hip_check(hipGetLastError(), "wbp_reduce launch");
 }
@@ -629,20 +773,23 @@ extern "C" polar_status wbp_backward(const polar_code* code, const float* llr, i
     if (B < 0 || T < 1 || !(llr_max > 0.0f)) return set_error(POLAR_ERR_INVALID_ARG, "wbp_backward: bad sizes");
     if (dlam_iters != 1 && dlam_iters != T)
         return set_error(POLAR_ERR_INVALID_ARG, "wbp_backward: dlam_iters must be 1 or T");
-    const int v = variant ? variant : bwd_default_variant(code->n);
+    const bool grouped = variant == 0 && bwd_grouped(code->n, B);
+    const int v = variant ? variant : grouped ? bwd_group_variant(code->n) : bwd_default_variant(code->n);
     const bp::BwdEntry* e = bp::lookup_bwd(code->n, v);
     if (!e) return set_error(POLAR_ERR_UNSUPPORTED, "wbp_backward: no kernel variant for this block length");
     const int64_t P = (int64_t)T * 2 * code->n * code->N;
     if (B > 0) {
-        const int64_t blocks = (B + e->fpw - 1) / e->fpw;
-        hipLaunchKernelGGL(e->fn, dim3((unsigned)blocks), dim3(e->wg), 0, stream, code->dev(), llr, B, T, llr_max, W,
-                           saved, dlam, dlam_iters, dllr);
+        const int64_t per = grouped ? e->group : e->fpw;
+        hipLaunchKernelGGL((grouped ? e->group_fn : e->fn), dim3((unsigned)((B + per - 1) / per)),
+                           dim3(grouped ? e->group_wg : e->wg), 0, stream, code->dev(), llr, B, T, llr_max, W, saved,
+                           dlam, dlam_iters, dllr);
         polar_status st = hip_check(hipGetLastError(), "wbp_bwd launch");
         if (st != POLAR_OK) return st;
     }
+    const int group = grouped ? e->group : 1;
     // 16-byte accesses where both buffers allow them (P is a multiple of 4)
-    polar_status st = aligned16(saved) && aligned16(dW) ? launch_reduce<4>(saved, B, P, dW, stream)
-                                                        : launch_reduce<1>(saved, B, P, dW, stream);
+    polar_status st = aligned16(saved) && aligned16(dW) ? launch_reduce<4>(saved, B, group, P, dW, stream)
+                                                        : launch_reduce<1>(saved, B, group, P, dW, stream);
     return st == POLAR_OK ? ok_status() : st;
 }
 

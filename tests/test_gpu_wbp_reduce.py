@@ -121,3 +121,32 @@ def test_column_weights_and_their_gradient(N, shift):
     got = PB.wbp_column_grad(code, torch.from_numpy(g).cuda()).cpu().numpy().astype(np.float64)
     ref = g.astype(np.float64).sum(3)
     assert np.all(np.abs(got - ref) <= 2.0 ** -24 * np.abs(ref) + 1e-12)
+
+
+# frame counts that take the grouped adjoint: full groups, and a last group of one, two and all but one frame
+@pytest.mark.parametrize("N,group,per_cu", [(128, 8, 3), (256, 8, 2), (512, 8, 1), (1024, 4, 1)])
+@pytest.mark.parametrize("extra", [0, 1, 2, -1])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_grouped_adjoint_equals_frames_one_by_one(N, group, per_cu, extra, shift):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    # extra frames beyond a count that fills the chip's places to three quarters
+    B = (3 * per_cu * cus // 4 + 1) * group + extra
+    code = PB.PolarCode(N, N // 2, 8, 0, 2.0)
+    n, T = code.n, 2
+    g = torch.Generator(device="cuda").manual_seed(N + extra)
+    llr = 4.0 * torch.randn((B, N), generator=g, device="cuda") + 2.0
+    W = 0.7 + 0.4 * torch.rand((T, 2, n, N), generator=g, device="cuda")
+    dlam = torch.randn((B, T, N), generator=g, device="cuda")
+    out = []
+    for variant in (0, 2):  # 0: grouped, 2: one by one
+        sv = shifted(PB.wbp_forward(code, llr, W, save=True)["saved"], shift)
+        dW, dllr = torch.zeros_like(W), torch.zeros_like(llr)
+        p = lambda t: C.c_void_p(t.data_ptr())  # noqa: E731
+        PB._check(PB.lib().wbp_backward(code.handle, p(llr), B, p(W), T, 20.0, variant, p(sv), p(dlam), T, p(dW),
+                                        p(dllr), C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+        out.append((dW.double(), dllr))
+    assert torch.equal(out[0][1], out[1][1])  # a frame's own gradient does not depend on its neighbours
+    a, b = out[0][0], out[1][0]
+    # one rounding to float each of double sums taken in different orders
+    assert bool(torch.all((a - b).abs() <= 2.0 ** -23 * b.abs() + 1e-13 * b.abs().max()))
+    assert float(b.abs().sum()) > 0
