@@ -76,11 +76,10 @@ constexpr uint64_t low_half_mask(int d) {
     return m;
 }
 
-// u G == x on the packed words of one frame; every checker lane gets the answer
-template <class G, bool PACKED>
-__device__ __forceinline__ bool reencode_check(const uint8_t* ub, const uint8_t* xb, int lane) {
-    uint64_t u = lane_bits<G, PACKED>(ub, lane);
-    uint64_t x = lane_bits<G, PACKED>(xb, lane);
+// u G == x on the words of one frame's checker lanes; every one of them gets
+// the answer
+template <class G>
+__device__ __forceinline__ bool reencode_words(uint64_t u, uint64_t x, int lane) {
     // butterflies inside a word: distances 1, 2, .. CB/2 (masks fixed at compile time)
     static_for<0, 6>([&](auto D) {
         constexpr int d = 1 << decltype(D)::value;
@@ -104,6 +103,39 @@ __device__ __forceinline__ bool reencode_check(const uint8_t* ub, const uint8_t*
         bad = (bad >> grp) & ((1ull << G::TL) - 1ull);
     }
     return bad == 0;
+}
+
+// the same on decisions in LDS
+template <class G, bool PACKED>
+__device__ __forceinline__ bool reencode_check(const uint8_t* ub, const uint8_t* xb, int lane) {
+    return reencode_words<G>(lane_bits<G, PACKED>(ub, lane), lane_bits<G, PACKED>(xb, lane), lane);
+}
+
+// Frames of at most one wavefront whose threads hold at least as many lanes as
+// registers (T >= V, T >= 8): a checker lane's bits of u are its own thread's,
+// nodes V t .. V t + V - 1 of window 0, so u never goes through LDS.  Its bits of
+// x are V bits of one of the ballots taken in the last window, where lane t
+// holds node t + (v << P) in register v.
+template <class G>
+constexpr bool own_bits() {
+    return G::T <= 64 && G::T >= 8 && G::T >= G::V && (G::V == 4 || G::V == 8);
+}
+
+template <class G>
+__device__ __forceinline__ uint32_t own_x_bits(const uint64_t* words, int t, int slot) {
+    const int i = G::V * t;                               // first node
+    const int b = slot * G::T + (i & (G::T - 1));         // its bit in the ballot of register i >> P
+    const uint32_t byte = reinterpret_cast<const uint8_t*>(words)[((i >> G::P) << 3) + (b >> 3)];
+    return (byte >> (b & 7)) & ((1u << G::V) - 1u);
+}
+
+template <class G>
+__device__ __forceinline__ bool own_crc(const CodeDev& code, uint32_t bits, int t) {
+    if (code.c == 0) return true;
+    const uint32_t* tab = code.syn_nib + (size_t)t * (G::V / 4) * 16;
+    uint32_t s = tab[bits & 15u];
+    if constexpr (G::V == 8) s ^= tab[16 + (bits >> 4)];
+    return group_xor<G::TL>(s) == 0;
 }
 
 template <class G, bool PACKED>
@@ -202,7 +234,10 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
     // thread of window 0, its eight consecutive nodes; x: one ballot per
     // register and wavefront, since in the last window a wavefront's lanes
     // hold 64 consecutive nodes)
-    constexpr bool BITPACK = G::V == 8 && G::T >= 64;
+    // Frames of one wavefront keep u in registers (own_bits above): N = 128, 1000
+    // frames of at most 100 iterations 104 us with both in LDS, 99 us this way
+    constexpr bool OWN = own_bits<G>();
+    constexpr bool BITPACK = G::V == 8 && G::T >= 64 && !OWN;
     float* tb = sh.tb;
     const int lane = (G::T < 64) ? t : (lid_x() & 63);
     uint8_t* ub = sh.ubytes + slot * N;
@@ -322,7 +357,16 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
             }
         });
         if (stop != 2) {
-            if constexpr (BITPACK) {
+            if constexpr (OWN) {
+                uint64_t m[V];
+#pragma unroll
+                for (int v = 0; v < V; ++v) m[v] = __ballot((Lm[n][v] + Rm[n][v]) < 0.0f);
+                if (t == 0) {  // (every frame still running writes the same)
+                    uint64_t* xw = reinterpret_cast<uint64_t*>(sh.xbytes);
+#pragma unroll
+                    for (int v = 0; v < V; ++v) xw[v] = m[v];
+                }
+            } else if constexpr (BITPACK) {
                 // thread t holds node t + (v << P): the wavefront's ballot for
                 // register v is 64-bit word (v << (P - 6)) + w of the array
                 uint64_t m[V];
@@ -406,7 +450,7 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
             }
         });
         // ---------------- decisions in window 0 (register bits are the low bits)
-        if constexpr (BITPACK) {
+        if constexpr (BITPACK || OWN) {
             // nodes 8t .. 8t + 7: byte t of the bit array.  LLR(u) = L + prior
             // is never -0 (the prior is +0 or lmax > 0, and a sum of zeros of
             // opposite signs rounds to +0), so its sign bit is the test
@@ -419,7 +463,7 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
             ubits &= ~fmask;
             // the CRC stop tests every thread's own bits and stores them once,
             // after the loop
-            if (stop != 2) ub[t] = (uint8_t)ubits;
+            if (BITPACK && stop != 2) ub[t] = (uint8_t)ubits;
         } else {
             uint64_t pack = 0;
 #pragma unroll
@@ -442,7 +486,19 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
         }
         ++it;
         const bool last = it >= max_iter;
-        if (stop == 1) {
+        if constexpr (OWN) {
+            if (stop == 1 || (stop == 0 && last)) {
+                frame_sync<G>();
+                gok = reencode_words<G>(ubits, own_x_bits<G>(reinterpret_cast<const uint64_t*>(sh.xbytes), t, slot), lane);
+                if (gok || last) {
+                    cok = own_crc<G>(code, ubits, t);
+                    break;
+                }
+            } else if (stop == 2) {
+                cok = own_crc<G>(code, ubits, t);
+                if (cok || last) break;
+            }
+        } else if (stop == 1) {
             frame_sync<G>();
             gok = reencode_check<G, BITPACK>(ub, xb, lane);
             if (gok || last) {
@@ -477,6 +533,9 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
 #pragma unroll
                 for (int v = 0; v < V; ++v) bytes |= (uint64_t)((ubits >> v) & 1u) << (8 * v);
                 *reinterpret_cast<uint64_t*>(uo) = bytes;
+            } else if constexpr (OWN) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) uo[v] = (uint8_t)((ubits >> v) & 1u);
             } else {
                 const uint8_t* src = ub + ib;
 #pragma unroll
@@ -490,6 +549,12 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
             // leaves right after the decisions that read it)
             for (int v = 0; v < V; ++v) lo[v] = Lm[0][v] + prior[v];
         }
+        if constexpr (OWN) {
+            if (io.info && okv) {
+                ub[t] = (uint8_t)ubits;  // V bits a byte
+                frame_sync<G>();
+            }
+        }
         if constexpr (BITPACK) {
             if (stop == 2 && io.info && okv) {
                 // the CRC stop left the bits in registers (frame-uniform branch)
@@ -501,7 +566,9 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
             // the hybrid keeps BP's result: its information bits go out here
             for (int q = t; q < code.K; q += G::T) {
                 const int pos = code.info_pos[q];
-                io.info[q] = BITPACK ? (uint8_t)((ub[pos >> 3] >> (pos & 7)) & 1u) : ub[pos];
+                io.info[q] = BITPACK ? (uint8_t)((ub[pos >> 3] >> (pos & 7)) & 1u)
+                             : OWN   ? (uint8_t)((ub[pos / V] >> (pos % V)) & 1u)
+                                     : ub[pos];
             }
         }
         if (t == 0) {
