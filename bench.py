@@ -7,14 +7,13 @@ information bits, BPSK over AWGN at Eb/N0 = 2.5 dB (rate K/N).
 One step is one hybrid decode of a resident batch of frames: weighted
 (learned) min-sum BP with at most T = 20 iterations, stopping as soon as the
 CRC of its decided information bits holds (Sec. II-B allows the CRC in place
-of the re-encoding check), device-side compaction of the frames it did not
-finish,
+of the re-encoding check), which queues the frames it did not finish on the
+device,
 CA-SCL with list size 32 on them (with the decision aiding of Sec. II-A on the
 320 most reliable information positions: on 39192 frames the learned BP
 failed at 2.5 dB it made the same frame errors as plain CA-SCL for every count
-up to 320), merge.  Steps run through the two-stream
-pipeline (BP and compaction of step j + 1 overlap the CA-SCL and merge of
-step j, the asynchronous scheduling of Sec. III); the single-stream time is
+up to 320).  Steps run through the two-stream
+pipeline (BP of step j + 1 overlaps the CA-SCL of step j, the asynchronous scheduling of Sec. III); the single-stream time is
 reported beside.  The LLRs are in HBM before the timed region starts; host
 transfers are excluded.
 
@@ -79,9 +78,9 @@ ITER_SCHEDULE = ((1e-3, 1500),)
 # written), from rocprofv3 FETCH_SIZE and WRITE_SIZE scaled by a device copy of
 # known size; valid only for the kernel sources they were measured on (hash of
 # the files below) and that stop rule
-BP_TRAFFIC = {"bytes": 354132792, "frames": 65536, "stop": 2, "src_sha256_16": "7fbfbbecc642d8ec"}
+BP_TRAFFIC = {"bytes": 354126438, "frames": 65536, "stop": 2, "src_sha256_16": "5236b73bf3c687a9"}
 BP_SOURCES = ("paper_1609_09358_amd/csrc/bp.hip", "paper_1609_09358_amd/csrc/bp_common.hpp",
-              "paper_1609_09358_amd/csrc/bp_geom.hpp")
+              "paper_1609_09358_amd/csrc/bp_geom.hpp", "paper_1609_09358_amd/csrc/lane_ops.hpp")
 
 
 def bp_traffic(frames):
@@ -501,8 +500,8 @@ def kernel_times(code, llr, W, T, L, reps):
 
 
 def scl_ranking_ab(code, llr, bp_out, W, T, reps=3):
-    """List decoding with the pruned pseudo sort, a bitonic sort of the
-    candidates (Sec. II-A describes both) and threshold selection, on the
+    """List decoding with survivors chosen by the pruned pseudo sort, a bitonic
+    network (Sec. II-A describes both) and threshold selection, on the
     frames the learned BP failed in one batch (latency-bound) and on 8192
     frames (throughput-bound)."""
     import torch
@@ -567,9 +566,9 @@ def c5_points(code, learned_pipe, plain_pipe, learned, plain, B, ebn0s=(2.0, 3.0
 def latency_study(code, learned, T, W, reps=20):
     """Decode-call latency of the learned hybrid (the latency of every frame
     in the call) for small batches over Eb/N0, median and worst over `reps`
-    calls, in the spirit of the paper's latency figure; each with the call's
-    kernels replayed as one captured graph (the default) and launched one by
-    one."""
+    calls, in the spirit of the paper's latency figure; each under both
+    values of polar_set_hybrid_graphs (a call launches its kernels directly
+    under either)."""
     import torch
 
     from paper_1609_09358_amd import binding as PB

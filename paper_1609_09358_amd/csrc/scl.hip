@@ -2,7 +2,7 @@
 //
 // One wavefront decodes up to 64 / L frames of one code at a time; workgroups
 // stay resident and walk lists of frames whose lengths may live on the device
-// (the hybrid decoder feeds it the compacted BP failures without a host round
+// (the hybrid decoder feeds it the queue of BP failures without a host round
 // trip).  Frames of one code take the same branches -- which bits are frozen,
 // how long the list is -- so path slot l of the wavefront's frame s is lane
 // s L + l, and every instruction and lane exchange of the bit loop serves all
