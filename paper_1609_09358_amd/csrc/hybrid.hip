@@ -110,7 +110,7 @@ std::atomic<int> g_pipe_bp_wgs{0};
 std::atomic<int> g_pipe_scl_wgs{0};
 
 // per-batch states in flight in the pipelined hybrid: batch j + kPipeSlots
-// reuses batch j's state, so its BP waits for batch j's merge (three states
+// reuses batch j's state, so its BP waits for batch j's list decoding (three states
 // measured no faster than two: the list decoder and the next BP compete for
 // the same CUs, not for the state)
 constexpr int kPipeSlots = 2;
@@ -239,7 +239,7 @@ extern "C" polar_status hybrid_decode_batch(const polar_code* code, const float*
     if (B == 0) return ok_status();
     // Direct launches on the caller's stream (recorded there if it is being
     // captured).  Replaying a captured graph of these three or four kernels cost
-    // 29 us of host time a call, launching them 16 us; with six and more kernels
+    // 29 us of host time a call, launching them 13 us; with six and more kernels
     // it had been the other way round.
     st = enqueue_hybrid(code, plan, llr, B, p, L, info_hat, used_scl, stats, ws, stream);
     return st == POLAR_OK ? ok_status() : st;
