@@ -599,14 +599,14 @@ __attribute__((amdgpu_waves_per_eu(bp_waves_per_eu<NLOG, RLOG, WEIGHTED, SAVE, W
     CodeDev code, const float* __restrict__ llr, int64_t B, int max_iter, int stop, float lmax,
     const float* __restrict__ W, uint8_t* __restrict__ u_hat, uint8_t* __restrict__ info_out,
     float* __restrict__ llr_u, int32_t* __restrict__ iters_out, uint8_t* __restrict__ ok_out,
-    float* __restrict__ saved, BpQueue queue) {
+    float* __restrict__ saved, BpQueue queue, int grid) {
     using G = Geom<NLOG, RLOG>;
     constexpr int N = G::N;
     __shared__ BpShared<G> sh;
     const int tid = lid_x();
     const int t = (G::T < 64) ? (tid & (G::T - 1)) : tid;
     const int slot = (G::T < 64) ? (tid >> G::P) : 0;
-    const int64_t stride = PERSIST ? num_groups_x() * G::FPW : 0;
+    const int64_t stride = PERSIST ? (int64_t)grid * G::FPW : 0;
     // per-stage weights all within [-1, 1]: the clip-free form applies (every
     // wavefront reads the max_iter * 2n weights, which sit in the caches)
     bool unit = false;
@@ -665,7 +665,7 @@ __attribute__((amdgpu_waves_per_eu(gather_waves_per_eu<NLOG, RLOG, WEIGHTED>()))
     const MixedIo* __restrict__ mio, const int32_t* __restrict__ ids, const int32_t* __restrict__ count,
     int32_t* __restrict__ ticket, int max_iter, int stop, float lmax, const float* __restrict__ W,
     int32_t* __restrict__ iters_out, uint8_t* __restrict__ ok_out, int32_t* __restrict__ fail_ids,
-    int64_t fail_stride, int32_t* __restrict__ fail_count) {
+    int64_t fail_stride, int32_t* __restrict__ fail_count, int grid) {
     using G = Geom<NLOG, RLOG>;
     __shared__ BpShared<G> sh;
     const int tid = lid_x();
@@ -696,17 +696,17 @@ __attribute__((amdgpu_waves_per_eu(gather_waves_per_eu<NLOG, RLOG, WEIGHTED>()))
         if (t == 0 && !okv) fail_ids[cid * fail_stride + atomicAdd(&fail_count[cid], 1)] = id;
         if (tid == 0) next_first = ticket_now;
         frame_sync<G>();
-        q0 = num_groups_x() * G::FPW + next_first;
+        q0 = (int64_t)grid * G::FPW + next_first;
     }
 }
 
 // ------------------------------------------------------------------ dispatch
 
 using KernelFn = void (*)(CodeDev, const float*, int64_t, int, int, float, const float*, uint8_t*, uint8_t*,
-                          float*, int32_t*, uint8_t*, float*, BpQueue);
+                          float*, int32_t*, uint8_t*, float*, BpQueue, int);
 
 using GatherFn = void (*)(const MixedIo*, const int32_t*, const int32_t*, int32_t*, int, int, float, const float*,
-                          int32_t*, uint8_t*, int32_t*, int64_t, int32_t*);
+                          int32_t*, uint8_t*, int32_t*, int64_t, int32_t*, int);
 
 struct Entry {
     KernelFn plain, weighted, weighted_save, exact, weighted_stage;
@@ -808,7 +808,7 @@ polar_status launch_bp(const polar_code* code, const float* llr, int64_t B, cons
         }
     }
     hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(e->wg), 0, stream, code->dev(), llr, B, p->max_iter, p->stop,
-                       p->llr_max, p->weights, u_hat, info_out, llr_u, iters, ok, (float*)nullptr, queue);
+                       p->llr_max, p->weights, u_hat, info_out, llr_u, iters, ok, (float*)nullptr, queue, (int)grid);
     return hip_check(hipGetLastError(), "bp_kernel launch");
 }
 
@@ -834,7 +834,7 @@ polar_status launch_bp_gather(const polar_code* code, const MixedIo* io, const i
     if (!e) return set_error(POLAR_ERR_UNSUPPORTED, "bp: no kernel variant for this block length");
     bp::GatherFn fn = p->weights ? e->gather_weighted : e->gather_plain;
     hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(e->wg), 0, stream, io, ids, count, ticket, p->max_iter,
-                       p->stop, p->llr_max, p->weights, iters, ok, fail_ids, fail_stride, fail_count);
+                       p->stop, p->llr_max, p->weights, iters, ok, fail_ids, fail_stride, fail_count, grid);
     return hip_check(hipGetLastError(), "bp_gather_kernel launch");
 }
 
@@ -852,7 +852,7 @@ polar_status launch_bp_save(const polar_code* code, const float* llr, int64_t B,
     const int64_t blocks = (B + e->fpw - 1) / e->fpw;
     bp::KernelFn fn = saved ? e->weighted_save : e->weighted;
     hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(e->wg), 0, stream, code->dev(), llr, B, T, 0, llr_max, W,
-                       u_hat, (uint8_t*)nullptr, llr_u, (int32_t*)nullptr, ok, saved, BpQueue());
+                       u_hat, (uint8_t*)nullptr, llr_u, (int32_t*)nullptr, ok, saved, BpQueue(), (int)blocks);
     return hip_check(hipGetLastError(), "bp_kernel launch");
 }
 

@@ -70,7 +70,7 @@ __device__ __forceinline__ void store_bits(uint8_t* dst, uint32_t b) {
 template <int NLOG, bool ALIGNED>
 __global__ __launch_bounds__(ENC_THREADS) void encode_kernel(CodeDev code, const uint8_t* __restrict__ info, int64_t B,
                                                              uint8_t* __restrict__ u_out,
-                                                             uint8_t* __restrict__ x_out) {
+                                                             uint8_t* __restrict__ x_out, int grid) {
     using E = EncGeom<NLOG>;
     constexpr int PPL = E::PPL, TL = E::TL, G = E::G, FPW = E::FPW, STEPS = E::STEPS;
     constexpr uint32_t FULL = (1u << PPL) - 1u;
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_kernel(CodeDev code, const
     };
 
     const uint8_t* const info_end = info + B * (int64_t)K;
-    const int64_t stride = num_groups_x() * (ENC_WAVES * FPW);
+    const int64_t stride = (int64_t)grid * (ENC_WAVES * FPW);
     for (int64_t f0 = (gid_x() * ENC_WAVES + wave) * FPW; f0 < B; f0 += stride) {
         // ---- information bytes of the wavefront's frames, as bits in LDS
         const int64_t left = B - f0;
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(ENC_THREADS) void encode_kernel(CodeDev code, const
     }
 }
 
-using EncodeFn = void (*)(CodeDev, const uint8_t*, int64_t, uint8_t*, uint8_t*);
+using EncodeFn = void (*)(CodeDev, const uint8_t*, int64_t, uint8_t*, uint8_t*, int);
 
 struct EncodeEntry {
     EncodeFn aligned, any;
@@ -278,7 +278,8 @@ extern "C" polar_status polar_encode(const polar_code* code, const uint8_t* info
     // 16-byte stores need the outputs on such boundaries (any other pointer:
     // one byte at a time)
     const EncodeFn fn = aligned_to(x_out, 16) && (!u_out || aligned_to(u_out, 16)) ? e.aligned : e.any;
-    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(ENC_THREADS), 0, stream, code->dev(), info, B, u_out, x_out);
+    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(ENC_THREADS), 0, stream, code->dev(), info, B, u_out, x_out,
+                       (int)grid);
     return hip_check(hipGetLastError(), "encode_kernel launch") == POLAR_OK ? ok_status() : POLAR_ERR_DEVICE;
 }
 

@@ -35,10 +35,10 @@ __global__ void clear_count_kernel(int32_t* count) {
 // workgroup.
 __global__ __launch_bounds__(256) void stats_kernel(const uint8_t* __restrict__ ok, const int32_t* __restrict__ iters,
                                                     const uint8_t* __restrict__ scl_ok, int64_t B,
-                                                    unsigned long long* __restrict__ stats) {
+                                                    unsigned long long* __restrict__ stats, int grid) {
     __shared__ unsigned long long red[4][4];
     unsigned long long s[4] = {0, 0, 0, 0};  // ok, list-decoded, iterations, CRC failures
-    for (int64_t f = gid_x() * 256 + lid_x(); f < B; f += num_groups_x() * 256) {
+    for (int64_t f = gid_x() * 256 + lid_x(); f < B; f += (int64_t)grid * 256) {
         const bool good = ok[f] != 0;
         s[0] += good;
         s[1] += !good;
@@ -163,7 +163,7 @@ polar_status enqueue_scl_part(const polar_code* code, const SclPlan& plan, const
     int64_t grid = (B + 255) / 256;
     if (grid > 64) grid = 64;
     hipLaunchKernelGGL(stats_kernel, dim3((unsigned)grid), dim3(256), 0, stream, w.ok, w.iters, w.scl_ok, B,
-                       reinterpret_cast<unsigned long long*>(stats));
+                       reinterpret_cast<unsigned long long*>(stats), (int)grid);
     return hip_check(hipGetLastError(), "stats launch");
 }
 

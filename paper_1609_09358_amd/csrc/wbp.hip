@@ -713,7 +713,7 @@ __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ w, const 
                                                    float* __restrict__ m, float* __restrict__ v, int64_t count,
                                                    float lr, float b1, float b2, float eps, float c1, float c2,
                                                    float lo, float hi) {
-    const int64_t q = gid_x() * wg_size_x() + lid_x();
+    const int64_t q = gid_x() * 256 + lid_x();
     if (q >= count) return;
     const float gq = g[q];
     const float mq = b1 * m[q] + (1.0f - b1) * gq;
