@@ -581,21 +581,17 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
 
 // PERSIST: a grid smaller than the batch walks it (frame slots advance by the
 // grid size), so a capped grid leaves room on every CU for other kernels.
-// From N = 1024 on the inference kernels with eight nodes per thread are held
-// to 128 VGPRs (from 126 to 162), so that four waves share a SIMD instead of
-// three, at N = 4096 two frames a CU instead of one; what they spill (0 to 80
-// bytes per lane) is read outside the iteration loop or once per iteration.
-// Plain BP, re-encoding stop: N = 1024, 65536 frames 2509 -> 2402 us, N = 4096,
-// 4096 frames 4619 -> 3689 us; exact rule, N = 4096: 5788 -> 5177 us.  A weight
-// per node needs more registers.
-template <int NLOG, int RLOG, bool WEIGHTED, bool SAVE, bool WSTAGE, bool PERSIST>
-constexpr int bp_waves_per_eu() {
-    return (NLOG >= 10 && RLOG == 3 && (!WEIGHTED || WSTAGE) && !SAVE && !PERSIST) ? 4 : 1;
-}
-
-template <int NLOG, int RLOG, bool WEIGHTED, bool SAVE, int RULE = 0, bool WSTAGE = false, bool PERSIST = false>
+// DENSE (N >= 1024, eight nodes per thread, no weight per node, which needs
+// more registers): held to 128 VGPRs (from 126 to 162), so that four waves share
+// a SIMD instead of three, at N = 4096 two frames a CU instead of one; what the
+// kernel spills (0 to 80 bytes per lane) is read outside the iteration loop or
+// once per iteration.  Plain BP, re-encoding stop: N = 1024, 65536 frames
+// 2509 -> 2402 us, N = 4096, 4096 frames 4619 -> 3689 us; exact rule, N = 4096:
+// 5788 -> 5177 us.  For batches that fill the chip (dense_batch below).
+template <int NLOG, int RLOG, bool WEIGHTED, bool SAVE, int RULE = 0, bool WSTAGE = false, bool PERSIST = false,
+          bool DENSE = false>
 __global__ __launch_bounds__((Geom<NLOG, RLOG>::WG))
-__attribute__((amdgpu_waves_per_eu(bp_waves_per_eu<NLOG, RLOG, WEIGHTED, SAVE, WSTAGE, PERSIST>()))) void bp_kernel(
+__attribute__((amdgpu_waves_per_eu(DENSE ? 4 : 1))) void bp_kernel(
     CodeDev code, const float* __restrict__ llr, int64_t B, int max_iter, int stop, float lmax,
     const float* __restrict__ W, uint8_t* __restrict__ u_hat, uint8_t* __restrict__ info_out,
     float* __restrict__ llr_u, int32_t* __restrict__ iters_out, uint8_t* __restrict__ ok_out,
@@ -710,6 +706,7 @@ using GatherFn = void (*)(const MixedIo*, const int32_t*, const int32_t*, int32_
 
 struct Entry {
     KernelFn plain, weighted, weighted_save, exact, weighted_stage;
+    KernelFn dense_plain, dense_exact, dense_weighted_stage;  // or the ones above
     KernelFn persist_plain, persist_weighted_stage;
     GatherFn gather_plain, gather_weighted;
     int wg, fpw;
@@ -717,8 +714,11 @@ struct Entry {
 
 template <int NL, int RL>
 constexpr Entry make_entry() {
+    constexpr bool D = NL >= 10 && RL == 3;
     return Entry{&bp_kernel<NL, RL, false, false>, &bp_kernel<NL, RL, true, false>, &bp_kernel<NL, RL, true, true>,
                  &bp_kernel<NL, RL, false, false, 1>, &bp_kernel<NL, RL, true, false, 0, true>,
+                 &bp_kernel<NL, RL, false, false, 0, false, false, D>, &bp_kernel<NL, RL, false, false, 1, false, false, D>,
+                 &bp_kernel<NL, RL, true, false, 0, true, false, D>,
                  &bp_kernel<NL, RL, false, false, 0, false, true>, &bp_kernel<NL, RL, true, false, 0, true, true>,
                  &bp_gather_kernel<NL, RL, false>, &bp_gather_kernel<NL, RL, true>, Geom<NL, RL>::WG,
                  Geom<NL, RL>::FPW};
@@ -775,6 +775,22 @@ static int bp_auto_variant(int n, int64_t B, const bp_params* p) {
     return bp_default_variant(n);
 }
 
+// Batches that the DENSE kernels serve: those that do not fit the chip at once
+// with the registers the other kernels take -- more than three frames a CU at N =
+// 2048, one at N = 4096.  Below, the spills only make every iteration longer (N =
+// 4096, 256 frames of at most 60 iterations, re-encoding stop: 212 us DENSE, 181
+// us not; N = 2048, 768 frames: 215 and 204); beyond, the frames in flight count
+// (300 frames: 309 and 353 us; 1024: 264 and 290; at 3 dB, where a few frames
+// run long after the others, the shorter iteration still wins up to 700 frames
+// of N = 4096, 193 and 157 us).  At N = 1024 it is six a CU with weights (1536
+// frames: 72 and 64 us; 2000: 88 and 106) or without an early stop (2000: 87 and
+// 103), eight otherwise (2048: 231 and 218 us; 2600: 259 and 265; 16384: 1064
+// and 1130).
+static bool dense_batch(int n, int64_t B, const bp_params* p) {
+    const int64_t per_cu = n == 10 ? (p->weights || p->stop == 0 ? 6 : 8) : n == 11 ? 3 : 1;
+    return n >= 10 && B > per_cu * device_cu_count();
+}
+
 int bp_list_variants(int n, int32_t* ids, int cap) {
     int c = 0;
     for (int r = 2; r <= 3; ++r)
@@ -794,10 +810,11 @@ polar_status launch_bp(const polar_code* code, const float* llr, int64_t B, cons
     if (B == 0) return POLAR_OK;
     const int64_t blocks = (B + e->fpw - 1) / e->fpw;
     if (blocks > (int64_t)INT32_MAX) return set_error(POLAR_ERR_INVALID_ARG, "bp: batch too large");
-    bp::KernelFn fn = p->rule == 1 ? e->exact
-                      : !p->weights        ? e->plain
-                      : p->weight_layout   ? e->weighted_stage
-                                           : e->weighted;
+    const bool dense = dense_batch(code->n, B, p);
+    bp::KernelFn fn = p->rule == 1       ? (dense ? e->dense_exact : e->exact)
+                      : !p->weights      ? (dense ? e->dense_plain : e->plain)
+                      : p->weight_layout ? (dense ? e->dense_weighted_stage : e->weighted_stage)
+                                         : e->weighted;
     int64_t grid = blocks;
     if (wgs_per_cu > 0 && p->rule == 0 && (!p->weights || p->weight_layout == 1)) {
         // capped persistent grid: leaves room on every CU for concurrent kernels

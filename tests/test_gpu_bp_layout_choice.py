@@ -55,3 +55,27 @@ def test_short_blocks_match_oracle(N, c, variant, stop):
     out = PB.HybridDecoder(code, max_iter=T, L=4, stop=stop, variant=variant)(llr)
     assert (out["info"].cpu().numpy() == ref["info"]).all()
     assert (out["used_scl"].cpu().numpy() == ref["used_scl"]).all()
+
+
+@pytest.mark.parametrize("N,per_cu", [(1024, 8), (2048, 3), (4096, 1)])
+@pytest.mark.parametrize("kind", ["plain", "exact", "column"])
+@pytest.mark.parametrize("stop", [0, 1, 2])
+def test_kernels_of_full_and_partial_chips_agree(N, per_cu, kind, stop):
+    """The last batch of the kernels for a chip that is not full and the first one beyond give each frame the same
+    results, soft outputs included."""
+    if N == 1024 and (kind == "column" or stop == 0):
+        per_cu = 6
+    B = per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+    code = PB.PolarCode(N, N // 2, 16, 0, 2.0)
+    g = torch.Generator(device="cuda").manual_seed(N + stop)
+    x = PB.polar_encode(code, torch.randint(0, 2, (B + 1, code.K), generator=g, device="cuda", dtype=torch.uint8)).float()
+    s2 = O.sigma2(2.0, 0.5)
+    llr = (2.0 * (1.0 - 2.0 * x + s2 ** 0.5 * torch.randn(x.shape, generator=g, device="cuda")) / s2).contiguous()
+    T = 6
+    kw = dict(max_iter=T, stop=stop, soft=True, variant=3, rule=1 if kind == "exact" else 0)
+    if kind == "column":
+        kw["weights"] = torch.rand((T, 2, code.n), generator=g, device="cuda") * 0.4 + 0.7
+    a = PB.bp_decode_batch(code, llr, **kw)
+    b = PB.bp_decode_batch(code, llr[:B].contiguous(), **kw)
+    for k in ("u_hat", "iters", "ok", "llr_u"):
+        assert torch.equal(a[k][:B], b[k]), k
