@@ -758,19 +758,22 @@ int bp_default_variant(int n) { return n >= 9 ? 3 : 2; }
 // which ends its iterations sooner as long as the chip holds all frames at once:
 // N = 1024 up to three frames per CU (256 frames, at most 100 iterations: 160
 // against 202 us; 768: 213 against 230; 8192: 674 both; 65536: 4253 against
-// 4040), N = 2048 one (256: 236 against 245 us; 512: 322 against 277); never
-// at N = 4096 (16 frames: 376 against 339 us).  With a weight per node the
+// 4040), N = 2048 one (256: 133 against 135 us, with weights 48 against 52; 512:
+// 185 against 156) unless the CRC stops it, whose test costs r = 2 an LDS round
+// trip more (256: 181 against 137 us, with weights 63 against 51); never at N =
+// 4096 (16 frames: 376 against 339 us).  With a weight per node the
 // registers r = 3 holds weights in cost it wavefronts: N = 512 is faster with
 // r = 2 at every size (16 frames 25 against 42 us, 65536: 699 against 876) and
-// so is N = 4096 (768: 227 against 566 us), N = 1024 and 2048 up to three
-// frames per CU (768: 38 against 40, 77 against 87 us).
+// so is N = 4096 (768: 227 against 566 us), N = 1024 and, without the CRC stop,
+// 2048 up to three frames per CU (768: 38 against 40, 77 against 87 us; with it
+// N = 2048 takes 111 against 87).
 static int bp_auto_variant(int n, int64_t B, const bp_params* p) {
     const int64_t cus = device_cu_count();
     if (p->rule == 0 && p->weights && p->weight_layout == 0) {
         if (n == 9 || n == 12) return 2;
-        if ((n == 10 || n == 11) && B <= 3 * cus) return 2;
+        if ((n == 10 || (n == 11 && p->stop != 2)) && B <= 3 * cus) return 2;
     } else if (p->rule == 0) {
-        if ((n == 10 && B <= 3 * cus) || (n == 11 && B <= cus)) return 2;
+        if ((n == 10 && B <= 3 * cus) || (n == 11 && B <= cus && p->stop != 2)) return 2;
     }
     return bp_default_variant(n);
 }
