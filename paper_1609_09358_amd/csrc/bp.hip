@@ -235,8 +235,11 @@ __device__ __forceinline__ bool bp_frame(const CodeDev& code, const FrameIO& io,
     // register and wavefront, since in the last window a wavefront's lanes
     // hold 64 consecutive nodes)
     // Frames of one wavefront keep u in registers (own_bits above): N = 128, 1000
-    // frames of at most 100 iterations 104 us with both in LDS, 99 us this way
-    constexpr bool OWN = own_bits<G>();
+    // frames of at most 100 iterations 104 us with both in LDS, 99 us this way.
+    // Not for decoding with a weight per node: the compiler then holds fewer weights
+    // ahead (N = 512, r = 3, 256 frames of at most 10 iterations 42 us with both in
+    // LDS, 62 us without)
+    constexpr bool OWN = own_bits<G>() && (!WEIGHTED || WSTAGE || SAVE);
     constexpr bool BITPACK = G::V == 8 && G::T >= 64 && !OWN;
     float* tb = sh.tb;
     const int lane = (G::T < 64) ? t : (lid_x() & 63);
