@@ -556,9 +556,9 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// zeros at the frozen nodes of a gradient row
-__device__ __forceinline__ void zero_frozen(const CodeDev& code, float* row, int lane) {
-    for (int i = lane; i < code.N; i += 64)
+// zeros at the frozen nodes first, first + step, .. of a gradient row
+__device__ __forceinline__ void zero_frozen(const CodeDev& code, float* row, int first, int step) {
+    for (int i = first; i < code.N; i += step)
         if ((code.frozen_bits[i >> 5] >> (i & 31)) & 1u) row[i] = 0.0f;
 }
 
@@ -592,7 +592,7 @@ __global__ __launch_bounds__(kLossThreads) void wbp_bce_kernel(CodeDev code, con
             acc += softplus_of(z, e);
             drow[i] = (float)(scale * s * sigmoid_of(z, e));
         }
-        if (rows > 1 || wave == 0) zero_frozen(code, drow, lane);
+        zero_frozen(code, drow, q_first, q_step);
     }
     if (loss) {
         acc = wave_sum(acc);
@@ -638,18 +638,33 @@ __global__ __launch_bounds__(kLossThreads) void wbp_frame_loss_kernel(CodeDev co
     const int64_t f = gid_x();
     const int N = code.N, n = code.n, k = code.k, lane = lid_x() & 63, wave = lid_x() >> 6;
     stage_positions(code, u + f * N, pos);
-    for (int t = wave; t < T; t += kLossWaves) {
+    // one or two iterations of more than a wavefront's width: all wavefronts share
+    // each (T = 1, one frame of N = 4096: 40 us with one wavefront, 14 us with all;
+    // T = 3, 2048 frames of N = 256: 17 us by wavefronts, 19 us shared)
+    const bool share = 2 * T <= kLossWaves && k > 64;
+    const int t_first = share ? 0 : wave, t_step = share ? 1 : kLossWaves;
+    const int q_first = share ? lid_x() : lane, q_step = share ? kLossThreads : 64;
+    for (int t = t_first; t < T; t += t_step) {
         const float* lrow = saved + (((size_t)f * T + t) * 2 * n + n) * N;
         double acc = 0.0;
-        for (int q = lane; q < k; q += 64) {
+        for (int q = q_first; q < k; q += q_step) {
             const double z = ((pos[q] & 0x8000) ? 1.0 : -1.0) * (double)lrow[pos[q] & 0x7FFF];
             acc += softplus_of(z, exp(-fabs(z)));
         }
         acc = wave_sum(acc);
-        if (lane == 0) S[t] = acc;
+        if (lane == 0) {
+            if (share) dS[t * kLossWaves + wave] = acc;  // added below
+            else S[t] = acc;
+        }
     }
     __syncthreads();
     if (lid_x() == 0) {
+        if (share)
+            for (int t = 0; t < T; ++t) {
+                double s = 0.0;
+                for (int w = 0; w < kLossWaves; ++w) s += dS[t * kLossWaves + w];
+                S[t] = s;
+            }
         double P = 1.0, L = 0.0;
         for (int t = 0; t < T; ++t) {
             dS[t] = P;  // the product of the q before t
@@ -665,17 +680,17 @@ __global__ __launch_bounds__(kLossThreads) void wbp_frame_loss_kernel(CodeDev co
         }
     }
     __syncthreads();
-    for (int t = wave; t < T; t += kLossWaves) {
+    for (int t = t_first; t < T; t += t_step) {
         const float* lrow = saved + (((size_t)f * T + t) * 2 * n + n) * N;
         float* drow = dlam + ((size_t)f * T + t) * N;
         const double g = scale * dS[t];
-        for (int q = lane; q < k; q += 64) {
+        for (int q = q_first; q < k; q += q_step) {
             const int i = pos[q] & 0x7FFF;
             const double sg = (pos[q] & 0x8000) ? 1.0 : -1.0;
             const double z = sg * (double)lrow[i];
             drow[i] = (float)(g * sg * sigmoid_of(z, exp(-fabs(z))));
         }
-        zero_frozen(code, drow, lane);
+        zero_frozen(code, drow, q_first, q_step);
     }
 }
 

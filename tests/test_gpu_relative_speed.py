@@ -74,3 +74,17 @@ def test_bp_with_a_weight_per_node(N):
         return lambda: PB.bp_decode_batch(code, llr, max_iter=T, stop=0, weights=W, variant=v, out=out)
 
     assert ratio(call(3), call(2)) < 2.1
+
+
+def test_frame_loss_of_one_iteration():
+    """One iteration's loss shares the workgroup: faster than four iterations, which take a wavefront each (1.0 while
+    one wavefront did it alone)."""
+    N = 4096
+    code = PB.PolarCode(N, N // 2, 16, 0, 2.0)
+    u = torch.zeros((1, N), dtype=torch.uint8, device="cuda")
+
+    def call(T):
+        saved = torch.randn((1, T, 2, code.n, N), device="cuda")
+        return lambda: PB.wbp_frame_loss(code, saved, u, T)
+
+    assert ratio(call(1), call(4)) < 0.85

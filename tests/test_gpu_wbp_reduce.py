@@ -150,3 +150,11 @@ def test_grouped_adjoint_equals_frames_one_by_one(N, group, per_cu, extra, shift
     # one rounding to float each of double sums taken in different orders
     assert bool(torch.all((a - b).abs() <= 2.0 ** -23 * b.abs() + 1e-13 * b.abs().max()))
     assert float(b.abs().sum()) > 0
+
+
+@pytest.mark.parametrize("N,K,T,B", [(128, 64, 1, 3), (128, 65, 1, 3), (128, 65, 2, 3), (128, 128, 2, 1),
+                                     (256, 255, 1, 2), (4096, 2000, 1, 2)])
+@pytest.mark.parametrize("kind", ["frame", "iter"])
+def test_frame_losses_shared_by_all_wavefronts(N, K, T, B, kind):
+    """One and two iterations on either side of the wavefront's width from which the workgroup shares them."""
+    test_losses_match_double(N, K, T, B, kind)
