@@ -337,8 +337,8 @@ int64_t polar_get_scl_lds_budget(void);
  * measured fastest on MI355X.  All decide survival by the strict order
  * (metric, parent position, bit) and keep the survivors in the order the
  * candidates are listed (parent position, then bit), so results are
- * identical.  Process-wide; host only; mode outside 0..3 gives
- * POLAR_ERR_INVALID_ARG. */
+ * identical.  Process-wide; host only; it applies to mixed plans made
+ * afterwards; mode outside 0..3 gives POLAR_ERR_INVALID_ARG. */
 polar_status polar_set_scl_ranking(int32_t mode);
 int32_t polar_get_scl_ranking(void);
 

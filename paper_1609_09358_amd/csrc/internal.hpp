@@ -129,6 +129,7 @@ struct SclPlan {
     int grid;            // workgroups launched
     int target;          // wavefronts to fill before one takes a second frame
     int lay_n;           // log2 of the largest block length the layout holds
+    int rank;            // survivor selection the plan is laid out for
 };
 // at most max_fpw frames per workgroup at once (their state then takes no more
 // room than that)

@@ -37,7 +37,7 @@
 // (found with two wavefront ballots) and slot index and list position coincide.
 // Each lane holds its path's two candidates.  Which survive follows from the
 // L-th smallest metric of the frame, found by a sorting network on the metrics
-// alone (or bit by bit, or by counting, see select below); candidates that tie
+// alone (or bit by bit, or by counting, see below); candidates that tie
 // with it are taken in candidate order.  The CRC is tracked per path as a
 // running syndrome (linear in the decided bits).  Each path carries its
 // decided bits of the current block in a register word and the slot it held
@@ -102,6 +102,7 @@ using glb_ptr = __attribute__((address_space(1))) T*;
 // named address space)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 template <typename T>
 __device__ __forceinline__ lds_ptr<T> as_lds(void* p) {
@@ -329,20 +330,6 @@ __device__ __forceinline__ uint64_t frame_lanes(int lane) {
     return ((1ull << L) - 1ull) << (lane & ~(L - 1));
 }
 
-// Threshold selection of the same value: found bit by bit from the top as the
-// largest value with fewer than L metrics of the frame below it.
-template <int L>
-__device__ __forceinline__ uint32_t lth_smallest_by_bits(uint32_t kh, uint32_t kf, bool alive, int lane) {
-    const uint64_t mine = frame_lanes<L>(lane);
-    uint32_t tau = 0u;
-    for (int b = 30; b >= 0; --b) {
-        const uint32_t trial = tau | (1u << b);
-        const uint64_t h = __ballot(alive && kh < trial), f = __ballot(alive && kf < trial);
-        tau = mask_count(h & mine) + mask_count(f & mine) < (uint32_t)L ? trial : tau;
-    }
-    return tau;
-}
-
 // Which of this lane's candidates are among the frame's L smallest under
 // (metric, parent, bit), given the L-th smallest metric tau: all below it, and
 // of those equal to it the first in candidate order, as many as are missing.
@@ -359,8 +346,32 @@ __device__ __forceinline__ void keep_ties(uint32_t kh, uint32_t kf, uint32_t tau
     keep_f = lt_f || (eq_f && before + (!hard1 && eq_h ? 1 : 0) < need);
 }
 
+// Threshold selection of the same value for a single frame, its paths on the
+// first L lanes: found bit by bit from the top as the largest value with fewer
+// than L metrics below it.  A step waits for the one before, so the 2 L metrics
+// are spread over as many lanes, which makes a step one comparison, and value and
+// count stay in scalar registers (N = 1024, L = 32, one frame: 1478 us with two
+// comparisons and counts per lane, 677 us so; with eight steps unrolled 770).
+template <int L>
+__device__ __forceinline__ uint32_t lth_smallest_by_bits(uint32_t kh, uint32_t kf, bool alive, int lane) {
+    static_assert(L == 8 || L == 32, "list size");
+    uint32_t moved;  // kf of lane - L
+    if constexpr (L == 32) moved = __builtin_amdgcn_permlane32_swap(kf, kf, false, false)[0];
+    else moved = lane_xor<8>(kf);
+    const uint32_t key = alive ? kh : lane < 2 * L ? moved : 0xFFFFFFFFu;
+    uint32_t tau = 0u;
+#pragma unroll
+    for (int b = 30; b >= 0; --b) {
+        const uint32_t trial = tau | (1u << b);
+        const uint64_t m = __ballot(key < trial);
+        tau = (L == 32 ? mask_count(m) : (uint32_t)__builtin_popcount((uint32_t)m)) < (uint32_t)L ? trial : tau;
+    }
+    return tau;
+}
+
 // The pruned pseudo sort: each candidate counts the frame's candidates before
-// it.  The metrics go through LDS once, candidate by candidate.
+// it.  The metrics go through LDS once, candidate by candidate.  Two candidates
+// a lane, for the frames whose candidates do not all find a lane.
 template <int L>
 __device__ __forceinline__ void keep_by_count(lds_ptr<u32x2> cand, uint32_t kh, uint32_t kf, bool hard1, bool alive,
                                               int lane, bool& keep_h, bool& keep_f) {
@@ -385,6 +396,68 @@ __device__ __forceinline__ void keep_by_count(lds_ptr<u32x2> cand, uint32_t kh, 
     keep_f = hard1 ? keep0 : keep1;
 }
 
+// Counting and threshold selection with one candidate a lane: candidate c (bit c
+// & 1 of the path of lane c >> 1) of the wavefront's frames, 2 L to a frame, on
+// lane c, so at most 32 / L frames fit.  A lane decides whether its candidate
+// survives, by counting the frame's candidates before it, read from LDS in
+// vectors of four, or (several frames) against the L-th smallest metric, found bit
+// by bit.  N = 1024, L = 8: 1559 frames, one a wavefront, 765 us by counting with
+// two candidates a lane, 528 us so; 3000 frames, two a wavefront, 1922 us by
+// threshold with two candidates a lane, 874 us so.
+template <int L, int RANK>
+__device__ __forceinline__ uint32_t select_one_a_lane(lds_ptr<u32x2> surv, float lam0, float& PM, int nf, bool alive,
+                                                      int lane) {
+    constexpr int NC = 2 * L;
+    const bool hard1 = lam0 < 0.0f;
+    const uint32_t kh = __float_as_uint(PM), kf = __float_as_uint(PM + fabsf(lam0));
+    if (alive) surv[lane] = u32x2{hard1 ? kf : kh, hard1 ? kh : kf};
+    wave_mem_order();
+    const lds_ptr<const uint32_t> key = (lds_ptr<const uint32_t>)surv;
+    const bool mine = lane < nf * NC;
+    const int first = mine ? lane & ~(NC - 1) : 0;  // the frame's first candidate
+    const uint32_t own = mine ? key[lane] : 0xFFFFFFFFu;
+    bool keep;
+    if constexpr (RANK == kRankCount) {
+        constexpr int G = NC / 4 > 4 ? 4 : NC / 4;  // vectors in flight
+        int rank = 0;
+        for (int c0 = first; c0 < first + NC; c0 += 4 * G) {
+            u32x4 v[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) v[g] = ((lds_ptr<const u32x4>)(key + c0))[g];
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    rank += (v[g][i] < own || (v[g][i] == own && c0 + 4 * g + i < lane)) ? 1 : 0;
+        }
+        keep = mine && rank < L;
+    } else {
+        static_assert(NC < 32, "a frame's lanes within half a wavefront");
+        const bool upper = lane >= 32;
+        auto count = [&](uint64_t m) -> int {  // of the frame's lanes
+            return __builtin_popcount(((upper ? (uint32_t)(m >> 32) : (uint32_t)m) >> (first & 31)) & ((1u << NC) - 1u));
+        };
+        uint32_t tau = 0u;
+        for (int b = 30; b >= 0; --b) {
+            const uint32_t trial = tau | (1u << b);
+            tau = count(__ballot(own < trial)) < L ? trial : tau;
+        }
+        const uint64_t eq = __ballot(own == tau);
+        const int need = L - count(__ballot(own < tau));
+        const int before = mask_below(eq) - __builtin_popcountll(eq & ((1ull << first) - 1ull));
+        keep = own < tau || (own == tau && before < need);
+    }
+    wave_mem_order();
+    const uint64_t m = __ballot(keep);
+    if (keep) surv[mask_below(m)] = u32x2{(uint32_t)lane, own};
+    wave_mem_order();
+    u32x2 r{0u, 0u};
+    if (alive) r = surv[lane];
+    wave_mem_order();
+    PM = __uint_as_float(r.y);
+    return r.x;
+}
+
 // The survivors of one branching bit of frames with full lists (nf frames).
 // They keep the candidate order, so a survivor goes to the slot with as many
 // survivors before it; frames before this one hold L each, so the count over
@@ -393,14 +466,21 @@ __device__ __forceinline__ void keep_by_count(lds_ptr<u32x2> cand, uint32_t kh, 
 template <int L, int RANK>
 __device__ __forceinline__ uint32_t select_survivors(lds_ptr<u32x2> surv, float lam0, float& PM, int nf, bool alive,
                                                      int lane) {
+    // (a plan for these two holds at most frames_room frames a wavefront)
+    if constexpr (RANK != kRankNetwork && L == 8) {
+        if (RANK == kRankCount || nf > 1) return select_one_a_lane<L, RANK>(surv, lam0, PM, nf, alive, lane);
+    } else if constexpr (RANK == kRankCount) {
+        if (nf == 1) return select_one_a_lane<L, RANK>(surv, lam0, PM, nf, alive, lane);
+    }
     const bool hard1 = lam0 < 0.0f;
     const uint32_t kh = __float_as_uint(PM), kf = __float_as_uint(PM + fabsf(lam0));
     bool keep_h, keep_f;
     if constexpr (RANK == kRankCount) {
         keep_by_count<L>(surv, kh, kf, hard1, alive, lane, keep_h, keep_f);
     } else {
-        const uint32_t tau = RANK == kRankNetwork ? lth_smallest<L>(kh, kf, lane)
-                                                  : lth_smallest_by_bits<L>(kh, kf, alive, lane);
+        uint32_t tau;
+        if constexpr (RANK == kRankThreshold) tau = lth_smallest_by_bits<L>(kh, kf, alive, lane);
+        else tau = lth_smallest<L>(kh, kf, lane);
         keep_h = alive && kh <= tau;
         keep_f = alive && kf <= tau;
         // every frame keeps at least L this way; more only where metrics tie
@@ -1141,24 +1221,46 @@ static size_t scl_budget(scl::KernelFn fn) {
     return budget;
 }
 
+// whether a list decode uses counting or threshold selection (elsewhere those
+// modes fall back to the network)
+static bool other_ranking(int n, int L, int rank) {
+    return rank != scl::kRankNetwork && n >= 5 && (L == 8 || L == 32);
+}
+
+// Frames a wavefront may take at once: as many as its lanes hold lists; half as
+// many where a selection other than the network wants a lane for each candidate
+// (L = 8: 16384 frames of N = 1024 by counting 957 us with four, 1086 with eight,
+// by threshold 1522 and 2133 us; threshold with L = 32: 8192 frames 2620
+// with one, 3091 us with two).  Counting with L = 32 takes two once the chip is
+// full (8192 frames 3747 us with one, 2878 with two).
+static int frames_room(int n, int L, int rank) {
+    const bool half = other_ranking(n, L, rank) && (L == 8 || rank == scl::kRankThreshold);
+    return half ? 32 / L : 64 / L;
+}
+
 // Wavefronts to fill before one takes a second frame: two per SIMD.  Up to
 // there a frame's latency decides, which a second frame in the wavefront makes
 // longer (2048 frames of N = 1024, L = 32: 610 us with one frame each, 714 us
 // with two on half the wavefronts); beyond, issue slots and memory do (4096
-// frames of L = 8: 497 us with two each, 665 us with one).
-static int64_t scl_target() { return (int64_t)device_cu_count() * 8; }
+// frames of L = 8: 497 us with two each, 665 us with one).  Counting with L = 32
+// works frame by frame, so it fills the chip first (3000 frames 1555 us, 2025 with
+// two each).
+static int64_t scl_target(int n, int L, int rank) {
+    return (int64_t)device_cu_count() * (other_ranking(n, L, rank) && L == 32 ? 16 : 8);
+}
 
 polar_status scl_plan(const polar_code* code, int L, int64_t max_frames, SclPlan* plan, int max_fpw) {
     return scl_plan_dims(code->n, L, max_frames, plan, max_fpw);
 }
 
 polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan, int max_fpw) {
-    scl::KernelFn fn = scl::pick(L, n, rank_kind());
+    const int rank = rank_kind();
+    scl::KernelFn fn = scl::pick(L, n, rank);
     if (!fn) return set_error(POLAR_ERR_INVALID_ARG, "scl: L must be a power of two in [1, 32]");
     // frames a wavefront may take at once: as many as its lanes hold lists,
     // if there can be that many frames
     int fpw = 1;
-    while (2 * fpw <= 64 / L && 2 * fpw <= max_fpw && fpw * scl_target() < max_frames) fpw *= 2;
+    while (2 * fpw <= frames_room(n, L, rank) && 2 * fpw <= max_fpw && fpw * scl_target(n, L, rank) < max_frames) fpw *= 2;
     const int slots = L * fpw;
     // tree levels: level 5 in LDS (read by every bit of a block), the levels
     // above in the workgroup's global slice (each written and read once per
@@ -1190,8 +1292,9 @@ polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan, int 
     plan->trace_off = lam_b;
     plan->glob_per_wg = align_up(lam_b + (tg ? scl::trace_bytes(slots, n) : 0), 256);
     plan->grid = (int)grid;
-    plan->target = (int)scl_target();
+    plan->target = (int)scl_target(n, L, rank);
     plan->lay_n = n;
+    plan->rank = rank;
     return POLAR_OK;
 }
 
@@ -1210,7 +1313,7 @@ size_t scl_static_share(int n, int L) {
 
 polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float* llr, int L, const SclWork& work,
                         const SclOut& out, void* glob, hipStream_t stream, const MixedIo* io) {
-    scl::KernelFn fn = scl::pick(L, plan.lay_n, rank_kind());
+    scl::KernelFn fn = scl::pick(L, plan.lay_n, plan.rank);
     scl::Layout lay;
     lay.slots = plan.slots;
     lay.fpw = plan.slots / L;

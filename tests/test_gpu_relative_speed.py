@@ -88,3 +88,30 @@ def test_frame_loss_of_one_iteration():
         return lambda: PB.wbp_frame_loss(code, saved, u, T)
 
     assert ratio(call(1), call(4)) < 0.85
+
+
+@pytest.mark.parametrize("L", [8, 32])
+@pytest.mark.parametrize("mode,most", [(1, {8: 1.5, 32: 3.2}), (3, {8: 2.4, 32: 2.2})])
+@pytest.mark.parametrize("per_cu", [4, 12])
+def test_list_decoder_ranking_modes(L, mode, most, per_cu):
+    """The other survivor selections against the network, one frame per wavefront and several (threshold selection
+    took 2.4 times as long as it had while it counted per lane)."""
+    N = 256
+    code = PB.PolarCode(N, N // 2, 16, 0, 2.5)
+    B = per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+    llr = torch.randn((B, N), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda") * 4.0
+    out = PB.scl_decode_batch(code, llr, L)
+    ws = torch.empty(2 * PB.polar_workspace_size(code, B, L) + 256, dtype=torch.uint8, device="cuda")
+
+    def call(m):
+        def go():
+            PB.polar_set_scl_ranking(m)
+            PB.scl_decode_batch(code, llr, L, out=out, workspace=ws)
+        return go
+
+    try:
+        r = ratio(call(mode), call(2), calls=10, rounds=5)
+    finally:
+        PB.polar_set_scl_ranking(0)
+    print(f"ratio L={L} mode={mode} per_cu={per_cu}: {r:.3f}", flush=True)
+    assert r < most[L]

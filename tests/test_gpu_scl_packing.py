@@ -127,3 +127,47 @@ def test_mixed_queue_of_several_codes_packs_per_code():
         assert np.array_equal(used[sel], gu)
         got = np.stack([info[out_off[f]: out_off[f] + code.K] for f in sel])
         assert np.array_equal(got, gi)
+
+
+@pytest.mark.parametrize("N,c", [(32, 8), (256, 16)])
+@pytest.mark.parametrize("L", [8, 32])
+@pytest.mark.parametrize("per_cu,extra", [(1, 3), (8, 3), (16, 5), (20, 1), (56, 5)])
+def test_ranking_modes_agree(N, c, L, per_cu, extra):
+    """Counting and threshold selection against the network with one to four frames per wavefront, ties included."""
+    B = per_cu * cus() + extra
+    code = PB.PolarCode(N, N // 2 - (c if N <= 32 else 0), c, 0, 2.0, da_bits=N // 8)
+    llr = llrs(code, B, 1.5, N + L)
+    llr[: B // 2] = torch.round(llr[: B // 2])
+    llr[: B // 8] = torch.sign(llr[: B // 8])
+    ref = PB.scl_decode_batch(code, llr, L)
+    try:
+        for mode in (1, 3):
+            PB.polar_set_scl_ranking(mode)
+            out = PB.scl_decode_batch(code, llr, L)
+            for k in KEYS:
+                assert torch.equal(out[k], ref[k]), (mode, k)
+    finally:
+        PB.polar_set_scl_ranking(0)
+
+
+@pytest.mark.parametrize("made,used", [(0, 3), (0, 1), (3, 0), (1, 3)])
+def test_ranking_mode_changed_after_a_mixed_plan(made, used):
+    """A mixed plan keeps the selection it was made with."""
+    code = PB.PolarCode(64, 32, 8, 0, 2.0)
+    B = 30 * cus() + 7
+    llr = llrs(code, B, 1.0, 9)
+    cf = np.zeros(B, np.int32)
+    got = []
+    try:
+        for m in ((0, 0), (made, used)):
+            PB.polar_set_scl_ranking(m[0])
+            plan = PB.MixedPlan([code], B, max_iter=2, L=32)
+            PB.polar_set_scl_ranking(m[1])
+            llr_off, out_off, _, nk = plan.layout(cf)
+            info = torch.zeros(nk, dtype=torch.uint8, device="cuda")
+            plan(llr.reshape(-1), torch.from_numpy(cf).cuda(), torch.from_numpy(llr_off).cuda(),
+                 torch.from_numpy(out_off).cuda(), info)
+            got.append(info)
+    finally:
+        PB.polar_set_scl_ranking(0)
+    assert torch.equal(got[0], got[1])
