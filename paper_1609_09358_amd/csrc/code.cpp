@@ -248,6 +248,7 @@ polar_status polar_build_code(const polar_code_desc* d, polar_code** out) {
     code->poly = poly;
     code->frozen = frozen;
     code->da = da;
+    code->n_da = d->da_bits;
     (void)hipGetDevice(&code->device);
     for (int i = 0; i < N; ++i)
         if (!frozen[i]) code->info_pos.push_back((int16_t)i);

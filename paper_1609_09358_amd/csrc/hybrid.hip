@@ -333,10 +333,18 @@ extern "C" polar_status hybrid_decode_pipelined(const polar_code* code, int64_t 
     if (st != POLAR_OK) return st;
     SclPlan plan;
     if ((st = scl_plan(code, L, B > 0 ? B : 1, &plan)) != POLAR_OK) return st;
-    // beside BP the list decoder's wavefronts matter more than its latency: half
-    // as many as alone before they take several frames (six batches of 65536,
-    // 1600 list-decoded: 7.04 ms, against 7.34 ms with as many as alone)
-    plan.target /= 2;
+    // Wavefronts before one takes several frames.  Beside the BP of a long batch
+    // their number matters more than their latency: four per CU (six batches of
+    // 65536, 1600 list-decoded: 7.04 ms, against 7.34 ms with eight; L = 8, four
+    // batches of 8192, N = 512, 2181 list-decoded: 1002 us, with eight 1014).  With
+    // L = 32 the list decoding of shorter batches is the longer of the two: eight
+    // below 256 frames a CU (four batches of 16384, N = 1024, 1367 list-decoded:
+    // 2775 us with four, 2380 with eight), as many as alone up to 64 a CU (8192, N =
+    // 512, 2181: 1455 with eight, 1306 with twelve; but 32768, N = 1024, 2700: 3655
+    // and 4113)
+    const int64_t cus = device_cu_count();
+    if (L != 32 || B >= 256 * cus) plan.target = (int)(4 * cus);
+    else if (B > 64 * cus && plan.target > 8 * cus) plan.target = (int)(8 * cus);
     // fewer persistent list-decoder workgroups (each walks more of the queue)
     // use fewer global slices, so the workspace size query stays an upper bound
     if (const int cap_wgs = g_pipe_scl_wgs.load(); cap_wgs > 0) {

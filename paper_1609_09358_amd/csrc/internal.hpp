@@ -44,6 +44,7 @@ struct polar_code {
     std::vector<uint8_t> frozen;    // host [N]
     std::vector<int16_t> info_pos;  // host [k]
     std::vector<uint8_t> da;        // host [N], decision-aided positions
+    int32_t n_da;                   // how many
     // device allocations (owned)
     uint32_t* d_frozen_bits = nullptr;
     int16_t* d_info_pos = nullptr;
@@ -134,8 +135,9 @@ struct SclPlan {
 // at most max_fpw frames per workgroup at once (their state then takes no more
 // room than that)
 polar_status scl_plan(const polar_code* code, int L, int64_t max_frames, SclPlan* plan, int max_fpw = 64);
-// a plan that holds any code with n <= max_n (n >= 5)
-polar_status scl_plan_dims(int max_n, int L, int64_t max_frames, SclPlan* plan, int max_fpw = 64);
+// a plan that holds any code with n <= max_n (n >= 5); aided: for frames with many
+// decision-aided positions
+polar_status scl_plan_dims(int max_n, int L, int64_t max_frames, SclPlan* plan, int max_fpw = 64, bool aided = false);
 
 // bytes beside the per-batch state that hybrid_decode_batch_static asks for
 size_t scl_static_share(int n, int L);

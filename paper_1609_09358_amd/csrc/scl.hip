@@ -1238,29 +1238,43 @@ static int frames_room(int n, int L, int rank) {
     return half ? 32 / L : 64 / L;
 }
 
-// Wavefronts to fill before one takes a second frame: two per SIMD.  Up to
-// there a frame's latency decides, which a second frame in the wavefront makes
-// longer (2048 frames of N = 1024, L = 32: 610 us with one frame each, 714 us
-// with two on half the wavefronts); beyond, issue slots and memory do (4096
-// frames of L = 8: 497 us with two each, 665 us with one).  Counting with L = 32
-// works frame by frame, so it fills the chip first (3000 frames 1555 us, 2025 with
-// two each).
-static int64_t scl_target(int n, int L, int rank) {
-    return (int64_t)device_cu_count() * (other_ranking(n, L, rank) && L == 32 ? 16 : 8);
+// Wavefronts to fill before one takes a second frame, per CU.  As long as a
+// frame's latency decides, one frame each is faster (2048 frames of N = 1024, L =
+// 32: 610 us, 714 us with two on half the wavefronts); beyond, issue slots and
+// memory do (4096 frames of L = 8: 497 us with two each, 665 us with one).
+// The line, one frame each against two (us, 256 CUs):
+//   - L <= 16: eight (L = 8, N = 1024, 2049 frames: 505 and 437; L = 16: 565 and
+//     519, with half the positions decision-aided 395 and 397);
+//   - L = 32, where two lists fill the wavefront and share less: ten at N = 512 and
+//     1024 (N = 1024, 2304 frames: 698 and 732; 3000: 767 and 745), twelve with
+//     two fifths or more of the positions decision-aided, which leaves less work
+//     that two frames share (2304: 515 and 576; 3000: 574 and 594; 3300: 646 and
+//     609; N = 512, 2600: 240 and 273), twelve at N = 4096 (2600: 3624 and 3915;
+//     3500: 4355 and 4349); eight at N = 256 (2304: 169 and 160) and N = 2048
+//     (2600: 1683 and 1623);
+//   - counting and threshold selection with L = 32 work frame by frame, so they
+//     fill the chip first (counting, 3000 frames: 1555 and 2025).
+static int64_t scl_target(int n, int L, int rank, bool aided) {
+    int per_cu = 8;
+    if (other_ranking(n, L, rank) && L == 32) per_cu = 16;
+    else if (L == 32 && (n == 9 || n == 10)) per_cu = aided ? 12 : 10;
+    else if (L == 32 && n == 12) per_cu = 12;
+    return (int64_t)device_cu_count() * per_cu;
 }
 
 polar_status scl_plan(const polar_code* code, int L, int64_t max_frames, SclPlan* plan, int max_fpw) {
-    return scl_plan_dims(code->n, L, max_frames, plan, max_fpw);
+    return scl_plan_dims(code->n, L, max_frames, plan, max_fpw, 5 * code->n_da >= 2 * code->k);
 }
 
-polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan, int max_fpw) {
+polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan, int max_fpw, bool aided) {
     const int rank = rank_kind();
     scl::KernelFn fn = scl::pick(L, n, rank);
     if (!fn) return set_error(POLAR_ERR_INVALID_ARG, "scl: L must be a power of two in [1, 32]");
     // frames a wavefront may take at once: as many as its lanes hold lists,
     // if there can be that many frames
     int fpw = 1;
-    while (2 * fpw <= frames_room(n, L, rank) && 2 * fpw <= max_fpw && fpw * scl_target(n, L, rank) < max_frames) fpw *= 2;
+    const int64_t target = scl_target(n, L, rank, aided);
+    while (2 * fpw <= frames_room(n, L, rank) && 2 * fpw <= max_fpw && fpw * target < max_frames) fpw *= 2;
     const int slots = L * fpw;
     // tree levels: level 5 in LDS (read by every bit of a block), the levels
     // above in the workgroup's global slice (each written and read once per
@@ -1292,7 +1306,7 @@ polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan, int 
     plan->trace_off = lam_b;
     plan->glob_per_wg = align_up(lam_b + (tg ? scl::trace_bytes(slots, n) : 0), 256);
     plan->grid = (int)grid;
-    plan->target = (int)scl_target(n, L, rank);
+    plan->target = (int)target;
     plan->lay_n = n;
     plan->rank = rank;
     return POLAR_OK;

@@ -171,3 +171,34 @@ def test_ranking_mode_changed_after_a_mixed_plan(made, used):
     finally:
         PB.polar_set_scl_ranking(0)
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("N,aided,per_cu", [(256, True, 8), (512, False, 10), (512, True, 12), (1024, False, 10),
+                                            (1024, True, 12), (2048, True, 8), (4096, False, 12)])
+@pytest.mark.parametrize("extra", [0, 1])
+def test_list_of_32_at_the_second_frame(N, aided, per_cu, extra):
+    """The last batch of one frame per wavefront and the first of two at L = 32, by block length and decision aiding,
+    against small batches."""
+    B = per_cu * cus() + extra
+    code = PB.PolarCode(N, N // 2, 16, 0, 2.0, da_bits=N // 4 if aided else 0)
+    llr = llrs(code, B, 1.5, N)
+    all_ = PB.scl_decode_batch(code, llr, 32)
+    for f in range(0, B, 4 * cus()):
+        one = PB.scl_decode_batch(code, llr[f: f + 4 * cus()].contiguous(), 32)
+        for k in KEYS:
+            assert torch.equal(all_[k][f: f + 4 * cus()], one[k]), (k, f)
+
+
+@pytest.mark.parametrize("per_cu", [13, 63, 65, 257])
+def test_pipelined_lists_of_32_by_batch_size(per_cu):
+    """Pipelined batches on either side of the sizes at which the list decoder beside BP packs frames sooner."""
+    B = per_cu * cus() + 1
+    code = PB.PolarCode(128, 64, 16, 0, 2.0, da_bits=40)
+    ll = [llrs(code, B, e, 30 + j) for j, e in enumerate((1.0, 3.0, 0.0))]
+    stats = torch.zeros(8, dtype=torch.int64, device="cuda")
+    outs = PB.HybridPipeline(code, max_iter=5, L=32, stop=2)(ll, stats=stats, want_used=True)
+    st = torch.zeros(8, dtype=torch.int64, device="cuda")
+    for o, x in zip(outs, ll):
+        ref = PB.HybridDecoder(code, max_iter=5, L=32, stop=2)(x, stats=st)
+        assert torch.equal(o["info"], ref["info"]) and torch.equal(o["used_scl"], ref["used_scl"])
+    assert torch.equal(stats, st) and int(st[2]) > 8 * cus()
