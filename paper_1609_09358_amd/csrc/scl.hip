@@ -502,7 +502,7 @@ __device__ __forceinline__ uint32_t select_survivors(lds_ptr<u32x2> surv, float 
 struct Layout {
     int slots;   // path slots of a workgroup: L times the most frames it decodes at once, a power of two
     int fpw;     // slots / L
-    int grid;    // workgroups launched
+    int grid[1]; // workgroups launched
     int target;  // wavefronts to fill before one takes a second frame
     int soff;    // LDS byte offset of the survivor list
     int tg;      // 1: the trace lives in the global slice
@@ -766,7 +766,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
     const int nf_max = uniform_int((int)(want < 1 ? 1 : want > lay.fpw ? lay.fpw : want));
     const bool deep = nf_max > 1;
 
-    for (int64_t unit = gid_x();; unit += lay.grid) {
+    // the grid size, read again where it is used (behind an index the compiler
+    // cannot see through): held in a register over a frame's decode it costs spills
+    auto grid = [&]() -> int64_t {
+        int i = 0;
+        asm volatile("" : "+s"(i));
+        return lay.grid[i];
+    };
+    for (int64_t unit = gid_x();; unit += grid()) {
         // the unit's queue and its first entry there
         int64_t q0 = unit, len = 0;
         int k = 0;
@@ -1331,7 +1338,7 @@ polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float
     scl::Layout lay;
     lay.slots = plan.slots;
     lay.fpw = plan.slots / L;
-    lay.grid = plan.grid;
+    lay.grid[0] = plan.grid;
     lay.target = plan.target < plan.grid ? plan.target : plan.grid;
     lay.soff = plan.surv_off;
     lay.tg = plan.trace_glob;
