@@ -474,6 +474,10 @@ __device__ __forceinline__ uint32_t select_survivors(lds_ptr<u32x2> surv, float 
     }
     const bool hard1 = lam0 < 0.0f;
     const uint32_t kh = __float_as_uint(PM), kf = __float_as_uint(PM + fabsf(lam0));
+    if constexpr (L == 1) {
+        // the hard decision, or bit 0 where the metrics tie
+        return ((uint32_t)lane << 1) | (hard1 && kf != kh ? 1u : 0u);
+    }
     bool keep_h, keep_f;
     if constexpr (RANK == kRankCount) {
         keep_by_count<L>(surv, kh, kf, hard1, alive, lane, keep_h, keep_f);
@@ -1003,7 +1007,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
                     const uint32_t syn_i = (uint32_t)__builtin_amdgcn_readlane((int)synv, r);
                     // pull the parent's state: syndrome and live registers
                     // (lanes without a path pull some lane's state, which no one reads)
-                    SYN = __shfl(SYN, par, 64) ^ (bit ? syn_i : 0u);
+                    // a list of one stays on its lane: nothing to pull
+                    auto pull = [&](auto v) {
+                        if constexpr (L == 1) return v;
+                        else return __shfl(v, par, 64);
+                    };
+                    SYN = pull(SYN) ^ (bit ? syn_i : 0u);
                     // partial-sum level d is written at the bits r with r mod
                     // 2^(d+1) = 2^d - 1 and read at those with r mod 2^(d+1) in
                     // [2^d, 2^(d+1) - 1] (g at level d, then the fold at the
@@ -1011,17 +1020,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
                     // be read exactly when bit d of r is set
                     static_for<0, BL>([&](auto DC) {
                         constexpr int d = decltype(DC)::value;
-                        if constexpr ((r >> d) & 1) ps[d] = __shfl(ps[d], par, 64);
+                        if constexpr ((r >> d) & 1) ps[d] = pull(ps[d]);
                     });
                     static_for<1, BL>([&](auto DC) {
                         constexpr int d = decltype(DC)::value;
                         if constexpr ((live_levels >> (d - 1)) & 1u) {
 #pragma unroll
-                            for (int e = 1 << d; e < (2 << d); ++e) lv[e] = __shfl(lv[e], par, 64);
+                            for (int e = 1 << d; e < (2 << d); ++e) lv[e] = pull(lv[e]);
                         }
                     });
-                    anc = __shfl(anc, par, 64);
-                    ublk = (r > 0 ? __shfl(ublk, par, 64) : 0u) | (bit << r);
+                    anc = pull(anc);
+                    ublk = (r > 0 ? pull(ublk) : 0u) | (bit << r);
                 }
                 // ---- partial sums: the finished block of 2^t bits becomes level t
                 if constexpr (tb < BL) ps[tb] = combine<tb>(bit, ps);

@@ -115,3 +115,17 @@ def test_list_decoder_ranking_modes(L, mode, most, per_cu):
     finally:
         PB.polar_set_scl_ranking(0)
     assert r < most[L]
+
+
+def test_list_of_one_against_two():
+    """A list of one ranks nothing: clearly faster than a list of two (0.95 while it went through the selection)."""
+    N = 1024
+    code = PB.PolarCode(N, 512, 16, 0, 2.5)
+    llr = torch.randn((1, N), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda") * 4.0
+
+    def call(L):
+        out = PB.scl_decode_batch(code, llr, L)
+        ws = torch.empty(PB.polar_workspace_size(code, 1, L) + 256, dtype=torch.uint8, device="cuda")
+        return lambda: PB.scl_decode_batch(code, llr, L, out=out, workspace=ws)
+
+    assert ratio(call(1), call(2), calls=20) < 0.85

@@ -202,3 +202,22 @@ def test_pipelined_lists_of_32_by_batch_size(per_cu):
         ref = PB.HybridDecoder(code, max_iter=5, L=32, stop=2)(x, stats=st)
         assert torch.equal(o["info"], ref["info"]) and torch.equal(o["used_scl"], ref["used_scl"])
     assert torch.equal(stats, st) and int(st[2]) > 8 * cus()
+
+
+@pytest.mark.parametrize("N,K,c", [(8, 4, 0), (16, 9, 0), (32, 20, 8), (128, 64, 8), (256, 128, 16)])
+@pytest.mark.parametrize("scale", [0.0, 1.0, 3e38])
+def test_list_of_one_matches_oracle(N, K, c, scale):
+    """A list of one, which decides without a ranking, with LLRs of three values: metrics that tie, LLRs of zero,
+    metrics too large for a penalty to change."""
+    B = 300
+    code = PB.PolarCode(N, K, c, 0, 2.0, da_bits=K // 4)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    llr = torch.randint(-1, 2, (B, N), generator=g, device="cuda").float()
+    if scale > 1:
+        llr[:, ::3] *= 1e9
+    elif scale == 0:
+        llr[: B // 2] = 0.0
+    out = {k: v.cpu().numpy() for k, v in PB.scl_decode_batch(code, llr.contiguous(), 1).items()}
+    ref = O.scl_batch(llr.cpu().numpy(), code.frozen, 1, c, POLY[c], prec="f32", da=code.decision_aided)
+    for k in KEYS:
+        assert np.array_equal(out[k], ref[k].astype(out[k].dtype)), k
