@@ -46,16 +46,19 @@ __device__ __forceinline__ float wave_max(float v) {
 // min(max(v, -m), m) for every non-NaN v, signed zeros included
 __device__ __forceinline__ float clipf(float v, float m) { return __builtin_amdgcn_fmed3f(v, -m, m); }
 
-// ln y for y in [1, 2]: the hardware base-2 logarithm times ln 2, the product
-// taken with ln 2 as the sum of two floats so that it rounds like one of twice
-// the precision.  The general logarithm returns the same bits here; what it
-// spends on tiny, infinite and negative arguments (seven of its instructions)
-// cannot act.
+// ln y for y in [1, 2]: the hardware base-2 logarithm times ln 2, with ln 2 as the
+// nearest float and the rest.  The product's rounding error is recovered by a fused
+// multiply-add (the error-free product of Dekker, A floating-point technique for
+// extending the available precision, 1971), which makes the result the correctly
+// rounded l ln 2 for every float l in [2^-24, 1].  __logf, which LLVM's AMDGPU
+// back end also ends in a compensated product with ln 2, returns the same bits
+// here; the range handling before it cannot act on these arguments.
 __device__ __forceinline__ float ln_1_to_2(float y) {
-    constexpr float kLn2Hi = 0x1.62e42ep-1f, kLn2Lo = 0x1.efa39ep-25f;
+    constexpr double kLn2 = 0.693147180559945309417;
+    constexpr float kNear = (float)kLn2, kRest = (float)(kLn2 - (double)kNear);
     const float l = __builtin_amdgcn_logf(y);
-    const float h = l * kLn2Hi;
-    return h + __fmaf_rn(l, kLn2Lo, __fmaf_rn(l, kLn2Hi, -h));
+    const float h = l * kNear;
+    return h + __fmaf_rn(l, kRest, __fmaf_rn(l, kNear, -h));
 }
 
 // The exact check-node rule of Sec. II-B, ln((1 + e^(a+b)) / (e^a + e^b)),
