@@ -269,7 +269,7 @@ def main():
 
     def run_pipe(pipe, o, steps, warmup):
         # consecutive batches of a call write different outputs (two buffers
-        # alternate; batch j + 2 starts after batch j is merged)
+        # alternate; batch j + 2 starts after the list decoding of batch j)
         o2 = {"info": torch.empty_like(o["info"])}
         alt = lambda k: [o if i % 2 == 0 else o2 for i in range(k)]
         pipe([llr] * warmup, outs=alt(warmup))
@@ -566,12 +566,9 @@ def c5_points(code, learned_pipe, plain_pipe, learned, plain, B, ebn0s=(2.0, 3.0
 def latency_study(code, learned, T, W, reps=20):
     """Decode-call latency of the learned hybrid (the latency of every frame
     in the call) for small batches over Eb/N0, median and worst over `reps`
-    calls, in the spirit of the paper's latency figure; each under both
-    values of polar_set_hybrid_graphs (a call launches its kernels directly
-    under either)."""
+    calls, in the spirit of the paper's latency figure."""
     import torch
 
-    from paper_1609_09358_amd import binding as PB
     from paper_1609_09358_amd import train_wbp as TW
 
     gen = TW.Trainer(code, 1, 16, seed=5555)
@@ -579,23 +576,18 @@ def latency_study(code, learned, T, W, reps=20):
     for e in (1.5, 2.5, 3.5):
         for B in (1, 64, 4096):
             _, _, llr = gen.frames(B, ebn0=e)
-            row = {"ebn0_db": e, "frames": B}
-            for mode, tag in ((1, "graph"), (0, "direct")):
-                PB.polar_set_hybrid_graphs(mode)
-                out = learned(llr)
+            out = learned(llr)
+            learned(llr, out=out)
+            torch.cuda.synchronize()
+            ts = []
+            for _ in range(reps):
+                t0 = time.perf_counter()
                 learned(llr, out=out)
                 torch.cuda.synchronize()
-                ts = []
-                for _ in range(reps):
-                    t0 = time.perf_counter()
-                    learned(llr, out=out)
-                    torch.cuda.synchronize()
-                    ts.append((time.perf_counter() - t0) * 1e3)
-                ts.sort()
-                row[f"{tag}_median_ms"] = round(ts[len(ts) // 2], 4)
-                row[f"{tag}_worst_ms"] = round(ts[-1], 4)
-            PB.polar_set_hybrid_graphs(1)
-            rows.append(row)
+                ts.append((time.perf_counter() - t0) * 1e3)
+            ts.sort()
+            rows.append({"ebn0_db": e, "frames": B, "median_ms": round(ts[len(ts) // 2], 4),
+                         "worst_ms": round(ts[-1], 4)})
     return rows
 
 
