@@ -382,7 +382,7 @@ def polar_pipeline_workspace_size(code: PolarCode, B, L, params: bp_params) -> i
 
 
 class HybridPipeline:
-    """hybrid_decode_pipelined (BP on the current stream, CA-SCL and merge on a
+    """hybrid_decode_pipelined (BP on the current stream, CA-SCL on a
     second stream of default priority) with its workspace kept between calls."""
 
     def __init__(self, code: PolarCode, max_iter=200, L=8, stop=1, llr_max=20.0, weights=None, variant=0):

@@ -104,9 +104,7 @@ __device__ __forceinline__ void frame_sync() {
     if constexpr (G::NWAVES > 1) {
         __syncthreads();
     } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_sync();
     }
 }
 
@@ -120,9 +118,7 @@ __device__ __forceinline__ void transpose_row(float (&row)[G::V], float* tb, int
     if constexpr (G::TAB.b[J].cross) {
         __syncthreads();
     } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_sync();
     }
 #pragma unroll
     for (int v = 0; v < G::V; ++v) row[v] = p[base_to + G::reg_off(J, KT, v)];

@@ -154,7 +154,6 @@ void polar_free_code(polar_code* code) {
     (void)hipFree(code->d_info_pos);
     (void)hipFree(code->d_syn);
     (void)hipFree(code->d_syn_nib);
-    (void)hipFree(code->d_enc_crc);
     (void)hipFree(code->d_da_bits);
     if (prev >= 0) (void)hipSetDevice(prev);
     delete code;
@@ -260,12 +259,9 @@ polar_status polar_build_code(const polar_code_desc* d, polar_code** out) {
     std::vector<uint32_t> dbits(std::max(N / 32, 1), 0u);
     for (int i = 0; i < N; ++i)
         if (da[i]) dbits[i / 32] |= 1u << (i % 32);
-    std::vector<uint32_t> enc(K, 0u);
-    if (c)
-        for (int q = 0; q < K; ++q) enc[q] = crc_of_single_one(poly, c, K - 1 - q);
     std::vector<uint32_t> syn(N, 0u);
     if (c) {
-        for (int q = 0; q < K; ++q) syn[code->info_pos[q]] = enc[q];
+        for (int q = 0; q < K; ++q) syn[code->info_pos[q]] = crc_of_single_one(poly, c, K - 1 - q);
         for (int j = 0; j < c; ++j) syn[code->info_pos[K + j]] = 1u << (c - 1 - j);
     }
     std::vector<uint32_t> nib((size_t)(N / 4) * 16, 0u);
@@ -281,7 +277,6 @@ polar_status polar_build_code(const polar_code_desc* d, polar_code** out) {
         (st = upload(&code->d_info_pos, code->info_pos)) != POLAR_OK ||
         (st = upload(&code->d_syn, syn)) != POLAR_OK ||
         (st = upload(&code->d_syn_nib, nib)) != POLAR_OK ||
-        (st = upload(&code->d_enc_crc, enc)) != POLAR_OK ||
         (st = upload(&code->d_da_bits, dbits)) != POLAR_OK) {
         polar_free_code(code);
         return st;

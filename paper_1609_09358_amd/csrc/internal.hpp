@@ -30,7 +30,6 @@ struct CodeDev {
     const int16_t* info_pos;      // [k] non-frozen positions in ascending order
     const uint32_t* syn;          // [N] CRC syndrome contribution of u_i = 1
     const uint32_t* syn_nib;      // [N/4][16] syndrome of each nibble value
-    const uint32_t* enc_crc;      // [K] CRC of the unit vector at info bit q
     const uint32_t* da_bits;      // [max(N/32,1)] decision-aided positions of the list decoder
     int32_t N, n, K, c, k;
 };
@@ -50,7 +49,6 @@ struct polar_code {
     int16_t* d_info_pos = nullptr;
     uint32_t* d_syn = nullptr;
     uint32_t* d_syn_nib = nullptr;
-    uint32_t* d_enc_crc = nullptr;
     uint32_t* d_da_bits = nullptr;
     polarhip::CodeDev dev() const {
         polarhip::CodeDev d;
@@ -58,7 +56,6 @@ struct polar_code {
         d.info_pos = d_info_pos;
         d.syn = d_syn;
         d.syn_nib = d_syn_nib;
-        d.enc_crc = d_enc_crc;
         d.da_bits = d_da_bits;
         d.N = N;
         d.n = n;
@@ -99,8 +96,7 @@ polar_status launch_bp_save(const polar_code* code, const float* llr, int64_t B,
 struct MixedIo {
     const float* llr;     // LLR rows
     const int64_t* off;   // row of frame f starts at element off[f]
-    // several codes in one launch (or null): frame f is decoded with
-    // codes[code_of[f]] instead of the kernel's code argument
+    // frame f is decoded with codes[code_of[f]]
     const int32_t* code_of;
     const CodeDev* codes;
     uint8_t* info;           // K information bits of frame f from element out_off[f] on
