@@ -401,13 +401,14 @@ polar_status wbp_iteration_loss(const polar_code* code, const float* saved, cons
 /* One weight per stage column (the column layout of bp_params): W dev
  * [T][2][n][N] = Wc dev [T][2][n] repeated over the N nodes of each column
  * (wbp_column_weights); dWc dev [T][2][n] = dW dev [T][2][n][N] summed over
- * each column's nodes in node order, in double (wbp_column_grad) -- the
- * gradient of a weight the whole column shares. */
+ * each column's nodes in double, in an order fixed by N (wbp_column_grad) --
+ * the gradient of a weight the whole column shares. */
 polar_status wbp_column_weights(const polar_code* code, const float* Wc, int32_t T, float* W, hipStream_t stream);
 polar_status wbp_column_grad(const polar_code* code, const float* dW, int32_t T, float* dWc, hipStream_t stream);
 
 /* Reverse-mode gradient of the weighted BP: dW dev [T][2][n][N] = sum over the
- * B frames (in frame order, accumulated in double) of d(loss)/dW given dlam
+ * B frames (accumulated in double, in an order that a device's size, B, T, N and
+ * variant fix) of d(loss)/dW given dlam
  * dev [B][dlam_iters][N]: d(loss)/d(llr_u) after the last iteration
  * (dlam_iters = 1) or after every iteration (dlam_iters = T); dllr dev [B][N]
  * or NULL = d(loss)/d(llr).  `saved` (from wbp_forward with the same llr, W,

@@ -310,8 +310,10 @@ struct BwdEntry {
     int group_wg, group;
 };
 
-// Frames per group where the grouped form exists: the layout of r that leaves
-// room for at least four frames in a workgroup of 512 threads with its registers
+// Frames per group where the grouped form exists: N = 128 to 1024, in the layout
+// of r that leaves room for at least four frames in a workgroup of 512 threads with
+// its registers (N = 2048 and 4096 have no such layout; shorter blocks would, but
+// were not measured)
 template <int NL, int RL>
 constexpr int bwd_group() {
     return (NL == 7 || NL == 8) && RL == 2 ? 8 : NL == 9 && RL == 3 ? 8 : NL == 10 && RL == 3 ? 4 : 1;
@@ -362,7 +364,9 @@ int bwd_default_variant(int n) { return n <= 11 ? 2 : 3; }
 // when all places are filled (4096 frames of N = 256, T = 10: 227 against 531
 // us; 2048 of N = 512: 271 against 545), seven tenths at N = 1024 (1024 frames,
 // T = 20: 798 against 1182 us); with fewer groups the frames one by one spread
-// better.
+// better.  All frames of a batch take one form, so a batch a little over whole
+// rounds goes back to single frames (N = 1024, T = 5: 1024 frames 208 us, 1100 frames
+// 346, 1500, whose groups fill seven tenths of two rounds again, 369).
 int bwd_group_variant(int n) { return n <= 8 ? 2 : 3; }
 bool bwd_grouped(int n, int64_t B) {
     if (n < 7 || n > 10) return false;
@@ -378,9 +382,11 @@ bool bwd_grouped(int n, int64_t B) {
 // equal length: workgroup (x, s) sums the rows of segment s in frame order and
 // leaves the double in that segment's first two rows of its own columns (low
 // word, high word -- entries that no other thread reads), and a second kernel
-// adds the segments in order.  The order of additions depends on B and P
-// alone.  Bound by HBM: the B P floats are read once; with at least 32 rows a
-// segment the partial sums add at most an eighth.  Measured: T = 10, N = 256,
+// adds the segments in order.  The order of additions depends on B, P and the
+// number of CUs.  Bound by HBM: the B P floats are read once; the partial sums, two floats
+// written and read again per segment and column, add at most an eighth with 32
+// rows a segment, at most a quarter with eight grouped rows of two floats (below).
+// Measured, ungrouped: T = 10, N = 256,
 // B = 4096 (671 MB) 1647 us with one thread per column, 165 us; T = 20,
 // N = 1024, B = 1024 (1.7 GB) 528 us, 326 us.
 // Grouped rows (group > 1, the adjoint's sums over `group` frames): row g is
@@ -502,9 +508,11 @@ template <int VEC>
 polar_status launch_reduce(float* part, int64_t B, int group, int64_t P, float* dW, hipStream_t stream) {
     const int64_t bx = (P / VEC + 255) / 256;
     const int64_t rows = (B + group - 1) / group;
-    // about eight workgroups per CU; a segment's first row is never a last
-    // group of one frame, since it has more rows than that
-    int64_t segments = (int64_t)device_cu_count() * 8 / bx;
+    // about eight workgroups per CU (of four columns a thread, also where the
+    // buffers' alignment allows one: it shall not change the order of the sum); a
+    // segment's first row is never a last group of one frame, since it has more rows
+    // than that
+    int64_t segments = (int64_t)device_cu_count() * 8 / ((P / 4 + 255) / 256);
     const int64_t most = rows / (group > 1 ? kReduceMinRows / 4 : kReduceMinRows);
     if (segments > most) segments = most;
     const dim3 one((unsigned)bx), many((unsigned)bx, (unsigned)(segments > 1 ? segments : 1));

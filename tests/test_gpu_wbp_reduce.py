@@ -158,3 +158,27 @@ def test_grouped_adjoint_equals_frames_one_by_one(N, group, per_cu, extra, shift
 def test_frame_losses_shared_by_all_wavefronts(N, K, T, B, kind):
     """One and two iterations on either side of the wavefront's width from which the workgroup shares them."""
     test_losses_match_double(N, K, T, B, kind)
+
+
+@pytest.mark.parametrize("N,T,B", [(512, 2, 4000), (64, 2, 3000)])
+def test_order_of_the_gradient_sum_ignores_alignment(N, T, B):
+    """Frames whose gradients cancel but for the double's rounding: any other order of the sum gives other bits."""
+    code = PB.PolarCode(N, N // 2, 0, 0, 2.0)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    h = torch.randn((B // 2, N), generator=g, device="cuda") * 3
+    llr = torch.cat([h, h.flip(0)]).contiguous()
+    d = torch.randn((B // 2, N), generator=g, device="cuda") * 10.0 ** torch.randint(0, 12, (B // 2, 1), generator=g,
+                                                                                    device="cuda")
+    dl = torch.cat([d, -d.flip(0)]).contiguous()
+    W = 0.7 + 0.4 * torch.rand((T, 2, code.n, N), generator=g, device="cuda")
+    p = lambda t: C.c_void_p(t.data_ptr())  # noqa: E731
+    res = []
+    for shift in (0, 1):
+        sv = shifted(PB.wbp_forward(code, llr, W, save=True)["saved"], shift)
+        dW = shifted(torch.zeros(W.numel(), device="cuda"), shift)
+        PB._check(PB.lib().wbp_backward(code.handle, p(llr), B, p(W), T, 20.0, 2, p(sv), p(dl), 1, p(dW), None,
+                                        C.c_void_p(torch.cuda.current_stream().cuda_stream)))
+        torch.cuda.synchronize()
+        res.append(dW.clone())
+    assert int((res[0] != 0).sum()) > 0
+    assert torch.equal(res[0], res[1])
