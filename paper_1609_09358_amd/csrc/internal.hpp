@@ -115,12 +115,17 @@ bool bp_variant_supported(int n, int variant);
 int bp_default_variant(int n);
 int bp_list_variants(int n, int32_t* ids, int cap);
 
+// Where a workgroup's state lies for a number of path slots
+struct SclForm {
+    int slots;       // L times the frames it may decode at once
+    int surv_off;    // LDS byte offset of the survivor list
+    int trace_glob;  // 1: the per-block trace lives in the global slice
+    int tb_off;      // LDS byte offset of the trace when !trace_glob
+};
+
 struct SclPlan {
-    int slots;           // path slots per workgroup: L times the frames it may decode at once
-    size_t lds_bytes;    // dynamic LDS per workgroup
-    int surv_off;        // LDS byte offset of the survivor list
-    int trace_glob;      // 1: the per-block trace lives in the global slice
-    int tb_off;          // LDS byte offset of the trace when !trace_glob
+    SclForm form[2];     // for one frame, for several
+    size_t lds_bytes;    // dynamic LDS per workgroup, either form
     size_t trace_off;    // byte offset of the trace inside the global slice
     size_t glob_per_wg;  // global slice bytes per workgroup (levels > 5, trace)
     int grid;            // workgroups launched

@@ -493,16 +493,13 @@ __device__ __forceinline__ uint32_t select_survivors(lds_ptr<u32x2> surv, float 
 }
 
 struct Layout {
-    int slots;   // path slots of a workgroup: L times the most frames it decodes at once, a power of two
-    int fpw;     // slots / L
+    SclForm form[2];  // for one frame a wavefront, for several (the traceback's block words sit below the LDS trace)
+    int fpw;     // most frames a wavefront decodes at once, a power of two
     int grid[1]; // workgroups launched
     int target;  // wavefronts to fill before one takes a second frame
-    int soff;    // LDS byte offset of the survivor list
-    int tg;      // 1: the trace lives in the global slice
+    int nblk;        // blocks of the largest block length the layout holds (trace rows)
     int64_t gbytes;  // bytes of the global slice per workgroup
     int64_t toff;    // byte offset of the trace inside the slice
-    int tboff;       // byte offset of the LDS trace (the traceback's block words sit below it)
-    int nblk;        // blocks of the largest block length the layout holds (trace rows)
 };
 
 // Active path a of the wavefront's frames (lists of 2^lg paths, L slots a frame)
@@ -729,26 +726,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
     extern __shared__ __attribute__((aligned(16))) unsigned char sm[];
     const int lane = lid_x();
     const int sub = lane >> LOGL, pl = lane & (L - 1);  // the lane's frame and path
-    const int SLOTS = lay.slots;
 
-    const lds_ptr<float> slam = as_lds<float>(sm);                          // [slots][32]
-    const lds_ptr<uint32_t> psw = (lds_ptr<uint32_t>)(slam + SLOTS * kSlotFloats);   // [slots][3]
-    const lds_ptr<u32x2> surv = as_lds<u32x2>(sm + lay.soff);               // [slots]
-    const lds_ptr<uint32_t> words = as_lds<uint32_t>(sm);                   // [fpw][nblk], reuses the LLR area at the end
-
-    unsigned char* gbase = glob_all ? glob_all + (size_t)gid_x() * (size_t)lay.gbytes : nullptr;
-    const glb_ptr<float> glam = as_glb<float>(gbase);         // [slots][2^rlog]
-    // the trace, per block and slot: the block's decided bits (bit r = bit r of
-    // the block) and the slot the path held at the block start; in LDS or, when
-    // tg, in the global slice
-    const size_t tra_off = (size_t)lay.nblk * SLOTS * sizeof(uint32_t);
-    const bool tg = lay.tg != 0;
-    const TraceRows tru{as_lds<uint32_t>(sm + lay.tboff), as_glb<uint32_t>(gbase + lay.toff), tg};  // [nblk][slots]
-    const lds_ptr<uint8_t> tra_l = as_lds<uint8_t>(sm + lay.tboff + tra_off);
-    const glb_ptr<uint8_t> tra_g = as_glb<uint8_t>(gbase + lay.toff + tra_off);
-
-    const float* const llr_base = mio ? mio->llr : llr;
-    const int64_t* const row_off = mio ? mio->off : nullptr;
     auto queue_len = [&](int k) -> int64_t {
         return work.count_dev ? (int64_t)work.count_dev[work.code_ids[k]] : work.count_host;
     };
@@ -758,7 +736,30 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void sc
     const int64_t want = (all + lay.target - 1) / lay.target;
     const int nf_max = uniform_int((int)(want < 1 ? 1 : want > lay.fpw ? lay.fpw : want));
     const bool deep = nf_max > 1;
+    // One frame has a layout of its own, whose trace finds room in LDS where that of
+    // several does not (hybrid of 4096 frames at 1.5 dB, N = 1024, L = 32, 2665
+    // list-decoded one by one: 734 us in the layout of several, 715 us)
+    const SclForm form = lay.form[deep ? 1 : 0];
+    const int SLOTS = form.slots;
 
+    const lds_ptr<float> slam = as_lds<float>(sm);                          // [slots][32]
+    const lds_ptr<uint32_t> psw = (lds_ptr<uint32_t>)(slam + SLOTS * kSlotFloats);   // [slots][3]
+    const lds_ptr<u32x2> surv = as_lds<u32x2>(sm + form.surv_off);               // [slots]
+    const lds_ptr<uint32_t> words = as_lds<uint32_t>(sm);                   // [fpw][nblk], reuses the LLR area at the end
+
+    unsigned char* gbase = glob_all ? glob_all + (size_t)gid_x() * (size_t)lay.gbytes : nullptr;
+    const glb_ptr<float> glam = as_glb<float>(gbase);         // [slots][2^rlog]
+    // the trace, per block and slot: the block's decided bits (bit r = bit r of
+    // the block) and the slot the path held at the block start; in LDS or, when
+    // tg, in the global slice
+    const size_t tra_off = (size_t)lay.nblk * SLOTS * sizeof(uint32_t);
+    const bool tg = form.trace_glob != 0;
+    const TraceRows tru{as_lds<uint32_t>(sm + form.tb_off), as_glb<uint32_t>(gbase + lay.toff), tg};  // [nblk][slots]
+    const lds_ptr<uint8_t> tra_l = as_lds<uint8_t>(sm + form.tb_off + tra_off);
+    const glb_ptr<uint8_t> tra_g = as_glb<uint8_t>(gbase + lay.toff + tra_off);
+
+    const float* const llr_base = mio ? mio->llr : llr;
+    const int64_t* const row_off = mio ? mio->off : nullptr;
     // the grid size, read again where it is used (behind an index the compiler
     // cannot see through): held in a register over a frame's decode it costs spills
     auto grid = [&]() -> int64_t {
@@ -1285,24 +1286,28 @@ polar_status scl_plan_dims(int n, int L, int64_t max_frames, SclPlan* plan, int 
     // above in the workgroup's global slice (each written and read once per
     // block start that reaches it, as a stream); the trace in LDS if it fits
     // the budget, else in the global slice
-    bool tg = false;
-    scl::LdsPlan lp = scl::lds_plan(L, slots, n, tg);
-    if (lp.bytes > scl_budget(fn)) {
-        tg = true;
-        lp = scl::lds_plan(L, slots, n, tg);
+    const size_t budget = scl_budget(fn);
+    plan->lds_bytes = 0;
+    bool tg = false;  // either form's trace in the slice
+    for (int several = 0; several < 2; ++several) {
+        const int s = several ? slots : L;
+        bool glob = false;
+        scl::LdsPlan lp = scl::lds_plan(L, s, n, glob);
+        if (lp.bytes > budget) {
+            glob = true;
+            lp = scl::lds_plan(L, s, n, glob);
+        }
+        if (lp.bytes > 160 * 1024) return set_error(POLAR_ERR_UNSUPPORTED, "scl: list too large for LDS");
+        plan->form[several] = SclForm{s, lp.soff, glob ? 1 : 0, lp.tboff};
+        if (lp.bytes > plan->lds_bytes) plan->lds_bytes = lp.bytes;
+        tg = tg || glob;
     }
-    if (lp.bytes > 160 * 1024) return set_error(POLAR_ERR_UNSUPPORTED, "scl: list too large for LDS");
     int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64, lp.bytes);
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64, plan->lds_bytes);
     if (e != hipSuccess || per_cu <= 0) per_cu = 1;
     int64_t grid = (int64_t)device_cu_count() * per_cu;
     if (max_frames < grid) grid = max_frames;
     if (grid < 1) grid = 1;
-    plan->slots = slots;
-    plan->lds_bytes = lp.bytes;
-    plan->trace_glob = tg ? 1 : 0;
-    plan->surv_off = lp.soff;
-    plan->tb_off = lp.tboff;
     size_t lam_b = 0;
     if (n > 6) {  // (level 5 alone needs no row)
         const size_t one = (size_t)L << scl::row_log(n, false), many = (size_t)slots << scl::row_log(n, true);
@@ -1334,16 +1339,14 @@ polar_status launch_scl(const polar_code* code, const SclPlan& plan, const float
                         const SclOut& out, void* glob, hipStream_t stream, const MixedIo* io) {
     scl::KernelFn fn = scl::pick(L, plan.lay_n, plan.rank);
     scl::Layout lay;
-    lay.slots = plan.slots;
-    lay.fpw = plan.slots / L;
+    lay.form[0] = plan.form[0];
+    lay.form[1] = plan.form[1];
+    lay.fpw = plan.form[1].slots / L;
     lay.grid[0] = plan.grid;
     lay.target = plan.target < plan.grid ? plan.target : plan.grid;
-    lay.soff = plan.surv_off;
-    lay.tg = plan.trace_glob;
     lay.nblk = (1 << plan.lay_n) >> (plan.lay_n < 5 ? plan.lay_n : 5);
     lay.gbytes = (int64_t)plan.glob_per_wg;
     lay.toff = (int64_t)plan.trace_off;
-    lay.tboff = plan.tb_off;
     unsigned char* gb = plan.glob_per_wg ? reinterpret_cast<unsigned char*>(glob) : nullptr;
     hipLaunchKernelGGL(fn, dim3(plan.grid), dim3(64), plan.lds_bytes, stream, code->dev(), llr, work, out, gb, lay,
                        io);

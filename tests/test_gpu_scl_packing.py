@@ -221,3 +221,23 @@ def test_list_of_one_matches_oracle(N, K, c, scale):
     ref = O.scl_batch(llr.cpu().numpy(), code.frozen, 1, c, POLY[c], prec="f32", da=code.decision_aided)
     for k in KEYS:
         assert np.array_equal(out[k], ref[k].astype(out[k].dtype)), k
+
+
+# A hybrid plans for its batch, whose frames may share wavefronts, while a launch
+# with few frames left gives each its own: the same words as a plan made for those alone
+@pytest.mark.parametrize("N,c,L", [(64, 8, 8), (1024, 24, 8), (1024, 24, 32), (4096, 16, 32)])
+@pytest.mark.parametrize("failing", [1, 3, 700])
+def test_shared_plan_with_one_frame_each(N, c, L, failing):
+    B = 24 * cus() + 1
+    code = PB.PolarCode(N, N // 2, c, 0, 2.0, da_bits=N // 8)
+    llr = llrs(code, B, 9.0, N + L)
+    bad = torch.randperm(B, device="cuda", generator=torch.Generator(device="cuda").manual_seed(L))[:failing]
+    llr[bad] = llrs(code, failing, -6.0, N - L)
+    bp = PB.bp_decode_batch(code, llr, max_iter=20, stop=2)
+    left = torch.nonzero(bp["ok"] == 0).flatten()
+    assert 0 < left.numel() <= 4 * cus()
+    out = PB.HybridDecoder(code, max_iter=20, L=L, stop=2)(llr)
+    one = PB.HybridDecoder(code, max_iter=20, L=L, stop=2)(llr[left].contiguous())
+    assert torch.equal(out["info"][left], one["info"])
+    assert torch.equal(out["used_scl"], (bp["ok"] == 0).to(torch.uint8))
+    assert bool(one["used_scl"].all())
