@@ -78,7 +78,7 @@ ITER_SCHEDULE = ((1e-3, 1500),)
 # written), from rocprofv3 FETCH_SIZE and WRITE_SIZE scaled by a device copy of
 # known size; valid only for the kernel sources they were measured on (hash of
 # the files below) and that stop rule
-BP_TRAFFIC = {"bytes": 354126438, "frames": 65536, "stop": 2, "src_sha256_16": "5236b73bf3c687a9"}
+BP_TRAFFIC = {"bytes": 354260275, "frames": 65536, "stop": 2, "src_sha256_16": "2498aae0e85f54ed"}
 BP_SOURCES = ("paper_1609_09358_amd/csrc/bp.hip", "paper_1609_09358_amd/csrc/bp_common.hpp",
               "paper_1609_09358_amd/csrc/bp_geom.hpp", "paper_1609_09358_amd/csrc/lane_ops.hpp")
 

@@ -28,7 +28,7 @@ constexpr int ENC_WAVES = ENC_THREADS / 64;
 //     1024 and up between a lane's groups.
 // Wavefronts are persistent, so the tables are read once per wavefront.
 // Measured at N = 1024, K = 512, CRC-24, 65536 frames (168 MB): 280 us for one
-// workgroup per frame with one byte per bit in LDS, 48 us this way.
+// workgroup per frame with one byte per bit in LDS, 39 us this way.
 template <int NLOG>
 struct EncGeom {
     static constexpr int N = 1 << NLOG;
