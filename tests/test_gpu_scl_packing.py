@@ -241,3 +241,24 @@ def test_shared_plan_with_one_frame_each(N, c, L, failing):
     assert torch.equal(out["info"][left], one["info"])
     assert torch.equal(out["used_scl"], (bp["ok"] == 0).to(torch.uint8))
     assert bool(one["used_scl"].all())
+
+
+# Threshold selection of one frame a wavefront ends its search early: metrics far apart, close together,
+# equal (few distinct values, all zero) and beyond the largest float
+@pytest.mark.parametrize("L", [8, 32])
+@pytest.mark.parametrize("scale,step", [(1.0, 0), (1.0, 0.5), (1.0, 4.0), (0.0, 0), (1e-30, 0), (1e37, 0), (3e38, 0)])
+def test_threshold_of_one_frame_equals_network(L, scale, step):
+    code = PB.PolarCode(256, 128, 8, 0, 2.0)
+    llr = llrs(code, 9, 0.0, L)
+    if step:
+        llr = torch.round(llr / step) * step
+    llr = torch.clamp(llr * scale, -3.4e38, 3.4e38)
+    try:
+        PB.polar_set_scl_ranking(2)
+        ref = PB.scl_decode_batch(code, llr, L)
+        PB.polar_set_scl_ranking(3)
+        out = PB.scl_decode_batch(code, llr, L)
+    finally:
+        PB.polar_set_scl_ranking(0)
+    for k in KEYS:
+        assert torch.equal(out[k], ref[k]), k
